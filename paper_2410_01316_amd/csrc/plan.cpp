@@ -1078,14 +1078,12 @@ fastsum_status fastsum_exec(fastsum_plan pl, const float* x, int64_t N, const fl
     if (pl->norms_dirty) FS_TRY(launch_clear_norms(pl->norms, st));
     pl->norms_dirty = true;
     const BoundCheck bc{pl->norms, pl->flag, pl->norm_lim, (same && !prefix) ? 1 : 0};
-    // a sorted plan keeps the targets in rows of their own
-    const bool shared = same && !(prefix && pl->sorted);
-    if (prefix && !pl->sorted)
+    if (prefix)
         FS_TRY(launch_point_norms(y, M, pl->d, (float)(1.0 / pl->r.p.R),
                                   pl->norms + kNormRoleUints, st));
     fastsum_status r = FASTSUM_OK;
     if (pl->sorted) {
-        r = sorted_pass(pl, x, w, N, y, M, s, shared, bc, st);
+        r = sorted_pass(pl, x, w, N, y, M, s, same, bc, st);
     } else if (pl->fused) {
         r = fused_pass(pl, x, w, N, y, M, s, bc, st);
     } else {
@@ -1105,7 +1103,7 @@ fastsum_status fastsum_exec(fastsum_plan pl, const float* x, int64_t N, const fl
     pl->norms_dirty = false;
     pl->have_exec = true;
     pl->have_proj = !pl->fused;
-    pl->last_same = shared;
+    pl->last_same = same;
     pl->last_x = x;
     pl->last_w = w;
     pl->last_y = y;

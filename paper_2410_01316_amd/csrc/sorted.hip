@@ -141,7 +141,7 @@ __device__ __forceinline__ void load_sorted(const float* __restrict__ kr,
 // i < N); keys / vals the sorted row with, for each key, its position
 // g = p L + i in the unsorted row: i < N is source i, i in [yoff, yoff + M)
 // target i - yoff, anything else padding that is skipped (same_xy: every
-// i < N is source and target i).  Writes
+// i < N is source i, and target i too if i < M).  Writes
 // V[p ldm + m] = coef * sum_n w_n |x~_n - y~_m|, coef = -c_d / tau, computed in
 // FP64 and stored in FP32 (relative rounding 6e-8 of one direction's sum;
 // the mean over the directions is taken in FP64 by sorted_reduce_kernel).
@@ -228,7 +228,7 @@ sorted_energy_kernel(
         int slot[kEnergyItems];
 #pragma unroll
         for (int j = 0; j < kEnergyItems; ++j) {
-            const bool tgt = same_xy ? (ii[j] >= 0 && ii[j] < N) : ii[j] >= yoff;   // < n_tot
+            const bool tgt = same_xy ? (ii[j] >= 0 && ii[j] < M) : ii[j] >= yoff;   // < n_tot
             slot[j] = -1;
             if (tgt) {
                 const int m = same_xy ? ii[j] : ii[j] - yoff;
@@ -354,8 +354,8 @@ hipError_t run_sort(void* temp, size_t& temp_bytes, const float* keys_in, float*
 
 // Adjoint of the sorted energy sums, from the ascending sort the exec made.
 // The row holds the sources x (weights w, positions i < N) and the targets
-// y (cotangent v, positions yoff + m; same_xy: every i < N is source and
-// target i).  Per direction, with coef = -c_d / tau and sign(0) = 0:
+// y (cotangent v, positions yoff + m; same_xy: every i < N is source i, and
+// target i too if i < M).  Per direction, with coef = -c_d / tau and sign(0) = 0:
 //   Ty[p][m] = coef sum_n w_n sign(y~_m - x~_n) = coef (W_< - W_>)   (d/dy~ of the sum)
 //   Tx[p][n] = coef sum_m v_m sign(x~_n - y~_m) = coef (V_< - V_>)   (d/dx~ of the transposed sum)
 //   U[p][n]  = coef sum_m v_m |x~_n - y~_m|                         (the transposed sum)
@@ -530,7 +530,7 @@ sorted_adjoint_kernel(const float* __restrict__ keys_in, const float* __restrict
             lw[j] = src ? w[pos] : 0.f;
             tw += (double)lw[j];
             if constexpr (FULL) {
-                const bool tgt = same_xy ? src : pos >= yoff;      // pos < n_tot
+                const bool tgt = same_xy ? (src && pos < M) : pos >= yoff;      // pos < n_tot
                 lv[j] = tgt ? v[pos - toff] : 0.f;
                 tv += (double)lv[j];
                 tsv += (double)lv[j] * (double)kk[j];
@@ -656,7 +656,7 @@ sorted_adjoint_kernel(const float* __restrict__ keys_in, const float* __restrict
 #pragma unroll
                 for (int j = 0; j < kAdjItems; ++j) {
                     const int pos = ii[j];
-                    const bool tgt = pos >= 0 && (same_xy ? pos < N : pos >= yoff);
+                    const bool tgt = pos >= 0 && (same_xy ? pos < M : pos >= yoff);
                     idx[j] = (tgt && start[j] != still_open) ? pos - toff : -1;
                     val[j] = slot_y[max(start[j], c0) - c0];
                 }
@@ -694,7 +694,7 @@ sorted_adjoint_kernel(const float* __restrict__ keys_in, const float* __restrict
                 if (want & 1) {
 #pragma unroll
                     for (int j = 0; j < kAdjItems; ++j) {
-                        const bool tgt = pos[j] >= 0 && (same_xy ? pos[j] < N : pos[j] >= yoff);
+                        const bool tgt = pos[j] >= 0 && (same_xy ? pos[j] < M : pos[j] >= yoff);
                         idx[j] = tgt ? pos[j] - toff : -1;
                         val[j] = slot_y[0];
                     }
@@ -802,7 +802,7 @@ hipError_t launch_sorted_grad(const float* keys_in, const float* keys_sorted,
                               float* Uv, unsigned short* Uo, int64_t ldm, int want,
                               hipStream_t stream) {
     const int n_tot = same_xy ? N : yoff + M;
-    if (N < 1 || M < 1 || (same_xy && M != N) || (!same_xy && yoff < N) || n_tot > L ||
+    if (N < 1 || M < 1 || (same_xy && M > N) || (!same_xy && yoff < N) || n_tot > L ||
         N > ldm || M > ldm || (int64_t)P * L >= ((int64_t)1 << 32))
         return hipErrorInvalidValue;
     const int nby = (M + kBucket - 1) >> kBucketShift, nbx = (N + kBucket - 1) >> kBucketShift;
@@ -834,7 +834,7 @@ hipError_t launch_sorted_energy(const float* keys_in, float* keys_out, unsigned 
                                 int M, int same_xy, const float* w, double coef, float* stv,
                                 unsigned short* sti, int64_t ldm, hipStream_t stream) {
     const int n_tot = same_xy ? N : yoff + M;
-    if (N < 1 || M < 1 || (!same_xy && yoff < N) || n_tot > L || M > ldm ||
+    if (N < 1 || M < 1 || (same_xy ? M > N : yoff < N) || n_tot > L || M > ldm ||
         (int64_t)P * L >= ((int64_t)1 << 32))
         return hipErrorInvalidValue;
     size_t bytes = temp_bytes;
