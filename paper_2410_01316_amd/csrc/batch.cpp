@@ -19,6 +19,7 @@ namespace {
 
 struct ProblemPlan {
     Resolved r;
+    WindowPlan win;
     GridGeom geom;
     int dpad = 0;
     int64_t n_max = 0, m_max = 0, ldx = 0, ldy = 0, ldm = 0;
@@ -26,7 +27,7 @@ struct ProblemPlan {
     // arena offsets (bytes); fused batches hold split tiles (at, xt, yt)
     // in place of A and the projections
     size_t off_A = 0, off_xproj = 0, off_yproj = 0, off_partial = 0, off_grid = 0,
-           off_spart = 0, off_exp = 0, off_mult = 0, off_tw = 0;
+           off_spart = 0, off_exp = 0, off_wscaled = 0, off_mult = 0, off_tw = 0;
     float bound = 0.f;
     float norm2_max = 0.f;     // fused range check: |x / R|^2 bound
     float norm_lim = 1.f;      // bound check: (1 + 1e-5) / max_p |xi_p|
@@ -38,8 +39,6 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct fastsum_batch_s {
     fastsum_params common{};
-    WindowPoly win;
-    WindowArgs win_args{};
     int P = 0, W = 4, pstage = 8, nprob = 0, device = 0, num_cu = 256;
     // projections computed inside spread and gather (every d <= 64, unless
     // FASTSUM_FLAG_MATERIALIZE asks for stored projections)
@@ -208,6 +207,7 @@ fastsum_status build_tasks(fastsum_batch_s* b, const fastsum_problem_io* io) {
         d.M = q.M;
         d.same_xy = (q.x == q.y) ? 1 : 0;
         if (b->fused) {
+            d.wscaled = reinterpret_cast<float*>(b->arena + pp.off_wscaled);
             d.at = reinterpret_cast<const uint16_t*>(b->arena + pp.off_A);
             d.xt = reinterpret_cast<uint16_t*>(b->arena + pp.off_xproj);
             d.yt = reinterpret_cast<uint16_t*>(b->arena + pp.off_yproj);
@@ -232,6 +232,8 @@ fastsum_status build_tasks(fastsum_batch_s* b, const fastsum_problem_io* io) {
         d.ldy = pp.ldy;
         d.ldm = pp.ldm;
         d.g = pp.geom;
+        d.swin = pack_window(pp.win.spread);
+        d.gwin = pack_window(pp.win.gather);
         d.d = pp.r.p.d;
         d.dpad = pp.dpad;
         d.bound = pp.bound;
@@ -289,10 +291,10 @@ fastsum_status launch_all(fastsum_batch_s* b, hipStream_t st) {
     for (int k = 0; k < kBatchPhases; ++k) {
         hipError_t e = b->fused
             ? launch_batch_phase_fused(k, b->W, b->d_probs, b->d_tasks + b->task_off[k],
-                                       b->task_cnt[k], b->P, b->win_args, b->flag, grid_blocks,
+                                       b->task_cnt[k], b->P, b->flag, grid_blocks,
                                        lds[k], st)
             : launch_batch_phase(k, b->W, b->d_probs, b->d_tasks + b->task_off[k],
-                                 b->task_cnt[k], b->P, b->pstage, b->win_args, b->flag,
+                                 b->task_cnt[k], b->P, b->pstage, b->flag,
                                  grid_blocks, lds[k], st);
         if (e != hipSuccess) return status_of(e);
     }
@@ -372,11 +374,22 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
         if (resolve_params(&q, pp.r) != FASTSUM_OK) { free_batch(b); return FASTSUM_EINVAL; }
         if (i == 0) {
             b->P = pp.r.p.P;
-            b->W = pp.r.p.window_w;
-            if (!build_window(b->W, b->win)) { free_batch(b); return FASTSUM_EINVAL; }
-            b->win_args = pack_window(b->win);
         }
-        const int n = pp.r.n;
+        if (!resolve_windows(pp.r, false, pp.win)) { free_batch(b); return FASTSUM_EINVAL; }
+    }
+    // one kernel per phase serves every problem: fitted windows only if all
+    // of them have the same width
+    b->W = b->plans[0].win.spread.W;
+    for (const ProblemPlan& pp : b->plans)
+        if (pp.win.spread.W != b->W) b->W = b->plans[0].r.p.window_w;
+    for (int i = 0; i < n_problems; ++i) {
+        const fastsum_problem_desc& pd = probs[i];
+        ProblemPlan& pp = b->plans[i];
+        if (pp.win.spread.W != b->W) {
+            pp.r.fitted = false;
+            if (!resolve_windows(pp.r, false, pp.win)) { free_batch(b); return FASTSUM_EINVAL; }
+        }
+        const int n = pp.win.n;
         pp.geom = make_geom(n, b->W, pp.r.tau * pp.r.p.R);
         pp.bound = (float)(pp.r.tau * pp.r.p.R * (1.0 + 1e-5) + 1e-7);
         pp.dpad = (int)round_up(pp.r.p.d, 4);
@@ -388,8 +401,7 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
         max_nr = std::max(max_nr, pp.geom.nr);
         max_n = std::max(max_n, n);
         std::vector<float2> mult_d;
-        build_tables(pp.r.p.kernel, pp.r.p.d, pp.r.p.scale, pp.r.tau, pp.r.p.n_ft, n, b->win,
-                     mults[i], mult_d, tws[i]);
+        build_tables(pp.r, pp.win, mults[i], mult_d, tws[i]);
         As[i].assign((size_t)b->P * pp.dpad, 0.f);
         double xi_norm_max = 0.0;
         for (int p = 0; p < b->P; ++p) {
@@ -429,8 +441,9 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
                        (b->fused ? kFuseDirs : b->pstage);
         pp.nchunk_cap = nc;
         pp.ngroup_cap = ng;
-        const int nr = pp.geom.nr, n = pp.r.n;
+        const int nr = pp.geom.nr, n = pp.win.n;
         if (b->fused) {
+            pp.off_wscaled = off; off = align256(off + sizeof(float) * (size_t)pp.n_max);
             pp.off_A = off; off = align256(off + Ats[i].size() * sizeof(uint16_t));
             pp.off_xproj = off; off = align256(off + (size_t)split_tiles_bytes(pp.n_max, pp.r.p.d));
             pp.off_yproj = off; off = align256(off + (size_t)split_tiles_bytes(pp.m_max, pp.r.p.d));
@@ -440,7 +453,8 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
             pp.off_yproj = off; off = align256(off + sizeof(float) * (size_t)P * pp.ldy);
         }
         pp.off_partial = off; off = align256(off + sizeof(float) * (size_t)nc * P * nr);
-        pp.off_grid = off; off = align256(off + sizeof(float) * (size_t)P * nr);
+        // whole groups of directions, the last one's missing rows zero
+        pp.off_grid = off; off = align256(off + sizeof(float) * (size_t)round_up(P, kFuseDirs) * nr);
         pp.off_spart = off; off = align256(off + sizeof(double) * (size_t)ng * pp.ldm);
         pp.off_exp = off; off = align256(off + sizeof(float) * (size_t)((pp.n_max + kSliceLen - 1) / kSliceLen));
         pp.off_mult = off; off = align256(off + sizeof(float2) * (size_t)n);
@@ -473,12 +487,16 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->last_use, hipEventDisableTiming);
     if (e != hipSuccess) { fastsum_status st = status_of(e); free_batch(b); return st; }
+    const int P = b->P;
     for (int i = 0; i < n_problems && e == hipSuccess; ++i) {
         const ProblemPlan& pp = b->plans[i];
         e = b->fused ? hipMemcpyAsync(b->arena + pp.off_A, Ats[i].data(),
                                       Ats[i].size() * sizeof(uint16_t), hipMemcpyHostToDevice, hs)
                      : hipMemcpyAsync(b->arena + pp.off_A, As[i].data(), As[i].size() * sizeof(float),
                                       hipMemcpyHostToDevice, hs);
+        if (e == hipSuccess && P % kFuseDirs)
+            e = hipMemsetAsync(b->arena + pp.off_grid + sizeof(float) * (size_t)P * pp.geom.nr, 0,
+                               sizeof(float) * (size_t)(round_up(P, kFuseDirs) - P) * pp.geom.nr, hs);
         if (e == hipSuccess)
             e = hipMemcpyAsync(b->arena + pp.off_mult, mults[i].data(), mults[i].size() * sizeof(float2),
                                hipMemcpyHostToDevice, hs);

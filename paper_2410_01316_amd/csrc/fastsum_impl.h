@@ -12,9 +12,11 @@ constexpr int kMaxPairs = 4;       // W/2 for W <= 8
 constexpr int kMaxHalfCoef = 4;    // coefficients per even/odd half-polynomial
 
 // Window weights of one point as polynomials of sp = frac(u) - 1/2, where u
-// is the point's position in grid cells.  Tap t (t < W/2) and its mirror tap
+// is the point's position in grid cells (odd W: plus half a cell, so sp is
+// the offset from the nearest cell).  Tap t (t < W/2) and its mirror tap
 // W-1-t share an even part E_t(sp^2) and an odd part sp*O_t(sp^2):
-//   weight_t = E_t + sp O_t,   weight_{W-1-t} = E_t - sp O_t.
+//   weight_t = E_t + sp O_t,   weight_{W-1-t} = E_t - sp O_t;
+// the centre tap of an odd W is even, weight_{W/2} = E_{W/2}.
 struct WindowArgs {
     float even[kMaxPairs][kMaxHalfCoef];
     float odd[kMaxPairs][kMaxHalfCoef];
@@ -184,7 +186,8 @@ bool fused_wide(int nr);
 // targets per fused gather workgroup (grids of nr cells, window width W)
 int64_t fused_gather_tile(int nr, int W);
 // resident workgroups per CU of the fused spread and gather kernels
-void fused_occupancy(int W, int d, int nr, int* spread_blocks, int* gather_blocks);
+// (Ws, Wg: window widths of the spread and of the gather)
+void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gather_blocks);
 // bytes of the split tiles of `rows` rows of dimension d
 int64_t split_tiles_bytes(int64_t rows, int d);
 
@@ -197,14 +200,15 @@ hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, ui
 
 // As launch_spread, with the projections computed in the kernel from the
 // split tiles of the sources (Xt, scale 1/R) and of the directions (At):
-// x~ = pscale * <xi, x / R>, pscale = tau R.
+// x~ = pscale * <xi, x / R>, pscale = tau R.  wscaled: scratch for N floats
+// (the weights in their slices' fixed point).
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
                                const float* w, int P, GridGeom g, float pscale, int nchunk,
-                               int64_t chunk_len, float* slice_max, const WindowArgs& win,
-                               float* partial, hipStream_t stream);
+                               int64_t chunk_len, float* slice_max, float* wscaled,
+                               const WindowArgs& win, float* partial, hipStream_t stream);
 
 // spart[b*ldm + m] = sum over directions p of range b (prange per range, a
-// multiple of kFuseDirs) of the interpolated grid at tau <xi_p, y_m>, FP64.
+// multiple of kFuseDirs; grid holds round_up(P, kFuseDirs) rows, zero past P) of the interpolated grid at tau <xi_p, y_m>, FP64.
 hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
                                int P, GridGeom g, float pscale, const float* grid, int prange,
                                const WindowArgs& win, double* spart, int64_t ldm,
@@ -294,11 +298,13 @@ struct BatchProblem {
     float* grid;           // P x nr
     double* spart;         // ngroup x ldm
     float* slice_max;      // ceil(N / kSliceLen)
+    float* wscaled;        // N weights in their slices' fixed point (fused; else nullptr)
     const float2* mult;    // n coefficient multipliers
     const float2* tw;      // n twiddles
     int64_t ldx, ldy, ldm;
     int64_t chunk_len;
     GridGeom g;
+    WindowArgs swin, gwin; // windows of the spread and of the gather
     int d, dpad;
     int nchunk, pg, ngroup;      // fused: pg = directions per gather range
     int same_xy;
@@ -345,14 +351,14 @@ constexpr int kGatherTile = 4 * kBlock; // targets per gather tile
 
 hipError_t launch_batch_phase(int phase, int W, const BatchProblem* probs,
                               const BatchTask* tasks, int ntasks, int P, int pstage,
-                              const WindowArgs& win, int* flag, int grid_blocks,
+                              int* flag, int grid_blocks,
                               size_t lds_bytes, hipStream_t stream);
 // The split, spread and gather phases of fused batches (every problem with
 // d <= kSplitMaxD); the other phases are shared with launch_batch_phase.
 // These three run one workgroup per task.
 hipError_t launch_batch_phase_fused(int phase, int W, const BatchProblem* probs,
                                     const BatchTask* tasks, int ntasks, int P,
-                                    const WindowArgs& win, int* flag, int grid_blocks,
+                                    int* flag, int grid_blocks,
                                     size_t lds_bytes, hipStream_t stream);
 // LDS bytes of the fused batch spread / gather workgroups for grids of nr cells
 size_t fused_spread_lds(int nr);

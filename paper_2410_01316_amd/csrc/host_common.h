@@ -37,6 +37,16 @@ struct Resolved {
     fastsum_params p;
     int n = 0;          // grid size
     double tau = 0.0;
+    bool fitted = false;   // neither window_w nor oversample was given: the windows and the
+                           // grid size may be fitted to the kernel (window_plan)
+};
+
+// Grid size and windows of a plan: the spread's, the gather's and the
+// derivative gather's.  The multipliers undo the spread's window and the
+// gather's own, so the three may differ.
+struct WindowPlan {
+    int n = 0;
+    WindowPoly spread, gather, deriv;
 };
 
 // c_k, k = 0..K (K = n_ft/2), of the 1-periodic rescaled 1-D kernel.
@@ -47,14 +57,23 @@ void fourier_coefficients_upto(int kernel, int d, double scale, double tau, int 
                                std::vector<double>& c);
 bool build_window(int W, WindowPoly& win);
 void window_transform(const WindowPoly& win, int n, int kmax, std::vector<double>& out);
+// transform of the window at angular frequency om per cell (analytic)
+double window_transform_at(const WindowPoly& win, double om);
+// Windows and grid size fitted to the spectrum of r's kernel (window.cpp).
+// `out` enters with the general window in every place and n = r.n; returns
+// false, with `out` as it was, if no cheaper choice keeps the error.
+bool window_plan(const Resolved& r, bool grad, WindowPlan& out);
+// The windows and the grid size of a plan: fitted where r.fitted allows and
+// it pays, else the general window of width r.p.window_w.
+bool resolve_windows(const Resolved& r, bool grad, WindowPlan& out);
 fastsum_status resolve_params(const fastsum_params* in, Resolved& r);
 GridGeom make_geom(int n, int W, double tauR);
 WindowArgs pack_window(const WindowPoly& win);
 uint16_t f32_to_bf16_host(float f);
-// multipliers c'_k / (n phihat_k)^2, derivative multipliers 2 pi i k m_k and
-// twiddles exp(-2 pi i k / n), each of length n
-void build_tables(int kernel, int d, double scale, double tau, int n_ft, int n,
-                  const WindowPoly& win, std::vector<float2>& mult,
+// multipliers c'_k / (n^2 phihat_s,k phihat_g,k) of the sum, the derivative's
+// (2 pi i k, with the derivative gather's phihat) and twiddles
+// exp(-2 pi i k / n), each of length wp.n
+void build_tables(const Resolved& r, const WindowPlan& wp, std::vector<float2>& mult,
                   std::vector<float2>& mult_d, std::vector<float2>& tw);
 int spread_chunks(int64_t N, int P);
 int64_t spread_chunk_len(int64_t N, int nchunk);

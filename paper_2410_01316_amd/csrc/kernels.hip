@@ -26,48 +26,61 @@ namespace fastsum {
 // ---------------------------------------------------------------------------
 
 template <int W> struct WinShape;
+template <> struct WinShape<3> { static constexpr int NE = 2, NO = 2; };  // degree 3
 template <> struct WinShape<4> { static constexpr int NE = 3, NO = 2; };  // degree 4
+template <> struct WinShape<5> { static constexpr int NE = 3, NO = 2; };  // degree 4
 template <> struct WinShape<6> { static constexpr int NE = 3, NO = 3; };  // degree 5
 template <> struct WinShape<8> { static constexpr int NE = 4, NO = 4; };  // degree 7
 
 // Per-thread constants of window evaluation on one grid.  The leading
 // Horner coefficients live in VGPRs: a VALU instruction reads at most one
-// scalar register and the first Horner step would otherwise need two.
+// scalar register and the first Horner step would otherwise need two.  For
+// odd W the taps are centred on the nearest cell: the position carries half a
+// cell more, and pair W/2 is the centre tap (even part only).
 template <int W>
 struct WinEval {
     float n, half_n;
-    int off;                      // W/2 - 1 + lo: first tap of cell 0, relative to lo
-    int maxb;                     // nr - W: largest first tap
-    float e_lead[W / 2], o_lead[W / 2];
+    int off, top;                 // floor(u) of the points whose first tap is cell 0, cell nr - W
+    float e_lead[(W + 1) / 2], o_lead[W / 2];
     // pscale: the kernel's projection values are x~ / pscale
     __device__ __forceinline__ WinEval(const GridGeom& g, const WindowArgs& win,
                                        float pscale = 1.f) {
         constexpr int NE = WinShape<W>::NE, NO = WinShape<W>::NO;
         n = (float)g.n * pscale;
-        half_n = 0.5f * (float)g.n;
-        off = W / 2 - 1 + g.lo;
-        maxb = g.nr - W;
+        half_n = 0.5f * (float)g.n + ((W % 2) ? 0.5f : 0.f);
+        off = (W - 1) / 2 + g.lo;
+        top = off + g.nr - W;
+#pragma unroll
+        for (int t = 0; t < (W + 1) / 2; ++t) {
+            e_lead[t] = win.even[t][NE - 1];
+            asm volatile("" : "+v"(e_lead[t]));
+        }
 #pragma unroll
         for (int t = 0; t < W / 2; ++t) {
-            e_lead[t] = win.even[t][NE - 1];
             o_lead[t] = win.odd[t][NO - 1];
-            asm volatile("" : "+v"(e_lead[t]));
             asm volatile("" : "+v"(o_lead[t]));
         }
     }
 };
 
+// Even part of tap t (and W-1-t) at offset sp (q = sp^2).
+template <int W>
+__device__ __forceinline__ float window_even(float q, int t, const WindowArgs& win,
+                                             const WinEval<W>& ev) {
+    float e = ev.e_lead[t];
+#pragma unroll
+    for (int j = WinShape<W>::NE - 2; j >= 0; --j) e = fmaf(e, q, win.even[t][j]);
+    return e;
+}
+
 // Even and odd parts of the taps of window pair t at offset sp (q = sp^2).
 template <int W>
 __device__ __forceinline__ void window_pair(float q, int t, const WindowArgs& win,
                                             const WinEval<W>& ev, float& e, float& o) {
-    constexpr int NE = WinShape<W>::NE, NO = WinShape<W>::NO;
-    e = ev.e_lead[t];
-#pragma unroll
-    for (int j = NE - 2; j >= 0; --j) e = fmaf(e, q, win.even[t][j]);
+    e = window_even<W>(q, t, win, ev);
     o = ev.o_lead[t];
 #pragma unroll
-    for (int j = NO - 2; j >= 0; --j) o = fmaf(o, q, win.odd[t][j]);
+    for (int j = WinShape<W>::NO - 2; j >= 0; --j) o = fmaf(o, q, win.odd[t][j]);
 }
 
 template <int W>
@@ -81,12 +94,14 @@ __device__ __forceinline__ void window_weights(float sp, const WindowArgs& win,
         wt[t] = fmaf(o, sp, e);
         wt[W - 1 - t] = fmaf(-o, sp, e);
     }
+    if constexpr (W % 2) wt[W / 2] = window_even<W>(q, W / 2, win, ev);
 }
 
-// Position u = x~ n + n/2 of a rescaled projection in grid cells: returns
-// the first tap floor(u) - (W/2 - 1) - lo, clamped to [0, nr - W] so that no
-// point (outside the bound, infinite or NaN) addresses a cell outside the
-// stored range, and sets sp = frac(u) - 1/2.  Points inside the bound are
+// Position u = x~ n + n/2 of a rescaled projection in grid cells (odd W: plus
+// 1/2): returns floor(u), which is the first tap plus ev.off (callers take
+// ev.off from the grid's base, where it costs nothing per point), clamped so
+// that no point (outside the bound, infinite or NaN) addresses a cell outside
+// the stored range, and sets sp = frac(u) - 1/2.  Points inside the bound are
 // never clamped (the stored range has a margin of a cell on each side).
 template <int W>
 __device__ __forceinline__ int tap0(float xt, const WinEval<W>& ev, float& sp) {
@@ -95,7 +110,7 @@ __device__ __forceinline__ int tap0(float xt, const WinEval<W>& ev, float& sp) {
     int j;
     asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(j) : "v"(u));
     int b;
-    asm("v_med3_i32 %0, %1, 0, %2" : "=v"(b) : "v"(j - ev.off), "v"(ev.maxb));
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(b) : "v"(j), "v"(ev.off), "v"(ev.top));
     return b;
 }
 
@@ -400,19 +415,29 @@ constexpr int kSlice = 4096;                       // sources per fixed-point sl
 constexpr int kSliceSteps = kSlice / (4 * kBlock); // float4 steps per thread and slice
 constexpr int kSpreadAcc = 2048 / kBlock;          // cell accumulators per thread (nr <= 2048)
 
-// slice_max[s] = max |w_i| over sources i of slice s
+// exponent k with mx * 2^k < 2^18 (0 for an empty, zero or non-finite slice)
+__device__ __forceinline__ int slice_exponent(float mx) {
+    int e = 0;
+    const bool ok = mx > 0.f && mx <= 3.4e38f;
+    if (ok) (void)frexpf(mx, &e);   // mx < 2^e
+    return ok ? 18 - e : 0;
+}
+
+// slice_max[s] = max |w_i| over the sources i of slice s, and (wscaled, if
+// given) their weights in the slice's fixed point, w_i 2^k
 __device__ __forceinline__ void slice_max_tile(float* red, const float* __restrict__ w,
-                                               int64_t N, int s, float* __restrict__ slice_max) {
+                                               int64_t N, int s, float* __restrict__ slice_max,
+                                               float* __restrict__ wscaled) {
     const int64_t i0 = (int64_t)s * kSlice;
     float v[kSlice / kBlock];
 #pragma unroll
     for (int q = 0; q < kSlice / kBlock; ++q) {
         const int64_t i = i0 + threadIdx.x + (int64_t)q * kBlock;
-        v[q] = (i < N) ? fabsf(w[i]) : 0.f;
+        v[q] = (i < N) ? w[i] : 0.f;
     }
     float m = 0.f;
 #pragma unroll
-    for (int q = 0; q < kSlice / kBlock; ++q) m = fmaxf(m, v[q]);
+    for (int q = 0; q < kSlice / kBlock; ++q) m = fmaxf(m, fabsf(v[q]));
     __syncthreads();               // red may still be read by a previous tile
     red[threadIdx.x] = m;
     __syncthreads();
@@ -421,20 +446,21 @@ __device__ __forceinline__ void slice_max_tile(float* red, const float* __restri
         __syncthreads();
     }
     if (threadIdx.x == 0) slice_max[s] = red[0];
+    if (wscaled != nullptr) {
+        const float scale = ldexpf(1.f, slice_exponent(red[0]));
+#pragma unroll
+        for (int q = 0; q < kSlice / kBlock; ++q) {
+            const int64_t i = i0 + threadIdx.x + (int64_t)q * kBlock;
+            if (i < N) wscaled[i] = v[q] * scale;
+        }
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void slice_max_kernel(
-    const float* __restrict__ w, int64_t N, float* __restrict__ slice_max) {
+    const float* __restrict__ w, int64_t N, float* __restrict__ slice_max,
+    float* __restrict__ wscaled) {
     __shared__ float red[kBlock];
-    slice_max_tile(red, w, N, blockIdx.x, slice_max);
-}
-
-// exponent k with mx * 2^k < 2^18 (0 for an empty, zero or non-finite slice)
-__device__ __forceinline__ int slice_exponent(float mx) {
-    int e = 0;
-    const bool ok = mx > 0.f && mx <= 3.4e38f;
-    if (ok) (void)frexpf(mx, &e);   // mx < 2^e
-    return ok ? 18 - e : 0;
+    slice_max_tile(red, w, N, blockIdx.x, slice_max, wscaled);
 }
 
 // Adds ws * weight_t, rounded to the nearest integer (ties to even), to the
@@ -444,9 +470,9 @@ __device__ __forceinline__ int slice_exponent(float mx) {
 // number of sources.
 template <int W>
 __device__ __forceinline__ void spread_point(float xt, float ws, const WinEval<W>& ev,
-                                             const WindowArgs& win, int* lds32) {
+                                             const WindowArgs& win, int* lds32, int base) {
     float sp;
-    int* __restrict__ c = lds32 + tap0<W>(xt, ev, sp);
+    int* __restrict__ c = lds32 + (base + tap0<W>(xt, ev, sp));
     const float q = sp * sp, spw = sp * ws;
 #pragma unroll
     for (int t = 0; t < W / 2; ++t) {
@@ -456,6 +482,8 @@ __device__ __forceinline__ void spread_point(float xt, float ws, const WinEval<W
         atomicAdd(c + t, __float2int_rn(fmaf(o, spw, e)));
         atomicAdd(c + W - 1 - t, __float2int_rn(fmaf(-o, spw, e)));
     }
+    if constexpr (W % 2)
+        atomicAdd(c + W / 2, __float2int_rn(window_even<W>(q, W / 2, win, ev) * ws));
 }
 
 template <int W>
@@ -490,10 +518,10 @@ __device__ __forceinline__ void spread_tile(
         }
 #pragma unroll
         for (int q = 0; q < kSliceSteps; ++q) {
-            spread_point<W>(xv[q].x, wv[q][0] * scale, ev, win, lds32);
-            spread_point<W>(xv[q].y, wv[q][1] * scale, ev, win, lds32);
-            spread_point<W>(xv[q].z, wv[q][2] * scale, ev, win, lds32);
-            spread_point<W>(xv[q].w, wv[q][3] * scale, ev, win, lds32);
+            spread_point<W>(xv[q].x, wv[q][0] * scale, ev, win, lds32, -ev.off);
+            spread_point<W>(xv[q].y, wv[q][1] * scale, ev, win, lds32, -ev.off);
+            spread_point<W>(xv[q].z, wv[q][2] * scale, ev, win, lds32, -ev.off);
+            spread_point<W>(xv[q].w, wv[q][3] * scale, ev, win, lds32, -ev.off);
         }
         __syncthreads();
         const float unscale = ldexpf(1.f, -k);
@@ -530,11 +558,13 @@ hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
                          int64_t chunk_len, float* slice_max, const WindowArgs& win,
                          float* partial, hipStream_t stream) {
     hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max);
+                       0, stream, w, N, slice_max, nullptr);
     dim3 grid((unsigned)P, (unsigned)nchunk);
     const size_t lds = stored_spread_lds(g.nr);
     switch (W) {
+        case 3: hipLaunchKernelGGL(spread_kernel<3>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
         case 4: hipLaunchKernelGGL(spread_kernel<4>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 5: hipLaunchKernelGGL(spread_kernel<5>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
         case 6: hipLaunchKernelGGL(spread_kernel<6>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
         case 8: hipLaunchKernelGGL(spread_kernel<8>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
         default: return hipErrorInvalidValue;
@@ -774,10 +804,10 @@ hipError_t launch_fftconv(const float* partial, int nchunk, int P, GridGeom g,
 constexpr int kGatherTPT = 4;   // consecutive targets per thread (one float4)
 
 template <int W>
-__device__ __forceinline__ float interp(float xt, const float* gl, const WinEval<W>& ev,
+__device__ __forceinline__ float interp(float xt, const float* gl, int base, const WinEval<W>& ev,
                                         const WindowArgs& win) {
     float sp;
-    const float* __restrict__ c = gl + tap0<W>(xt, ev, sp);
+    const float* __restrict__ c = gl + (base + tap0<W>(xt, ev, sp));
     float wt[W];
     window_weights<W>(sp, win, ev, wt);
     float t = 0.f;
@@ -825,11 +855,11 @@ __device__ __forceinline__ void gather_tile(
             for (int pp = 0; pp < np; ++pp) {
                 float4 nxt = cur;
                 if (pp + 1 < np) nxt = *reinterpret_cast<const float4*>(rowp + (int64_t)(pp + 1) * ld);
-                const float* gl = lds + pp * g.nr;
-                const float t0 = interp<W>(cur.x, gl, ev, win);
-                const float t1 = interp<W>(cur.y, gl, ev, win);
-                const float t2 = interp<W>(cur.z, gl, ev, win);
-                const float t3 = interp<W>(cur.w, gl, ev, win);
+                const int base = pp * g.nr - ev.off;
+                const float t0 = interp<W>(cur.x, lds, base, ev, win);
+                const float t1 = interp<W>(cur.y, lds, base, ev, win);
+                const float t2 = interp<W>(cur.z, lds, base, ev, win);
+                const float t3 = interp<W>(cur.w, lds, base, ev, win);
                 if (WRITE_T) {
                     *reinterpret_cast<float4*>(tout + (int64_t)(ps + pp) * ld_t + m) =
                         make_float4(t0, t1, t2, t3);
@@ -876,7 +906,9 @@ hipError_t launch_gather(int W, const float* proj, int64_t ld, int64_t M,
                        M, P, g, grid, pg, pstage, win, spart, ldm, tout, ld_t)
     const bool wt = tout != nullptr;
     switch (W) {
+        case 3: if (wt) FS_GATHER(3, true); else FS_GATHER(3, false); break;
         case 4: if (wt) FS_GATHER(4, true); else FS_GATHER(4, false); break;
+        case 5: if (wt) FS_GATHER(5, true); else FS_GATHER(5, false); break;
         case 6: if (wt) FS_GATHER(6, true); else FS_GATHER(6, false); break;
         case 8: if (wt) FS_GATHER(8, true); else FS_GATHER(8, false); break;
         default: return hipErrorInvalidValue;
@@ -1025,6 +1057,8 @@ constexpr int kGatherWaves = kGatherBlock / 64;
 constexpr int kGatherNB = 8;                               // 16-target batches per wave
 // wide grids: fewer batches (registers; W = 8 takes three)
 constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : (W >= 8 ? 3 : 4); }
+// row of the dispatch tables of window width W (-1: none)
+constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
 constexpr int kDmaBytes = 64 * 16;                         // one wave's 16-byte LDS-direct loads
 
 // split_points_kernel: one thread per (tile, lane), all k-blocks; rows >= N
@@ -1165,12 +1199,21 @@ __device__ __forceinline__ f32x4 split_mfma(const SplitOp<KB>& a, const SplitOp<
     return acc;
 }
 
+// Cells of a fused spread workgroup: whole groups of kFlushGroup per thread,
+// so that a flush needs no bounds checks.
+constexpr int kFlushGroup = 8;
+constexpr int spread_cells(int nr) {
+    constexpr int unit = kFlushGroup * kSpreadBlock;
+    return (kFuseDirs * nr + unit - 1) / unit * unit;
+}
+
 // Spread with projections computed in registers.  A workgroup owns the 16
 // directions 16 dgroup .. 16 dgroup + 15 and the sources of chunk `chunk`; grids are
 // kFuseDirs x nr int32 cells in LDS (fixed point per slice as in
 // spread_tile) flushed after every slice into per-thread FP32 accumulators.
 // v = <xi_p, x_n / R>; x~ = pscale v with pscale = tau R.  The range check
-// of these points was done when they were split.
+// of these points was done when they were split; w holds the weights in
+// their slices' fixed point (slice_max_tile).
 template <int W, int KB, int ACC>
 __device__ __forceinline__ void spread_fused_body(
     int* cells, const uint16_t* __restrict__ Xt, int64_t N, const uint16_t* __restrict__ At,
@@ -1180,7 +1223,7 @@ __device__ __forceinline__ void spread_fused_body(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
     const int p0 = dgroup * kFuseDirs;
-    const int ncell = kFuseDirs * g.nr;
+    const int ncell = spread_cells(g.nr);
     SplitOp<KB> dop;
     load_split<KB>(dop, At, dgroup, lane);
     float acc[ACC];
@@ -1188,8 +1231,8 @@ __device__ __forceinline__ void spread_fused_body(
     for (int q = 0; q < ACC; ++q) acc[q] = 0.f;
     for (int j = tid; j < ncell; j += kSpreadBlock) cells[j] = 0;
     __syncthreads();
-    int* gcol = cells + c * g.nr;                     // grid of direction p0 + c
     const WinEval<W> ev(g, win, pscale);
+    const int gcol = c * g.nr - ev.off;               // grid of direction p0 + c
     const int64_t i0 = (int64_t)chunk * chunk_len;   // multiple of 16
     const int len = (int)min(N - i0, chunk_len);           // <= 2^20 sources
     // the chunk's tiles and a few beyond (prefetch), within the tile array;
@@ -1201,23 +1244,22 @@ __device__ __forceinline__ void spread_fused_body(
         buffer_rsrc(Xt + t0 * KB * 2 * (kSplitTileBytes / 2), trange * KB * 2 * kSplitTileBytes);
     const __amdgpu_buffer_rsrc_t ws = buffer_rsrc(w + i0, (int64_t)len * 4);
     // projects one batch of 16 sources on the 16 directions and spreads it
-    auto batch = [&](const SplitOp<KB>& xo, const float (&wv)[4], float scale) {
+    auto batch = [&](const SplitOp<KB>& xo, const u32x4& wv) {
         // C[point][dir]: lane holds points 4r + i of direction c
         const f32x4 pr = split_mfma<KB>(xo, dop, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-        for (int i = 0; i < 4; ++i) spread_point<W>(pr[i], wv[i] * scale, ev, win, gcol);
+        for (int i = 0; i < 4; ++i)
+            spread_point<W>(pr[i], __uint_as_float(wv[i]), ev, win, cells, gcol);
     };
-    auto load = [&](SplitOp<KB>& xo, float (&wv)[4], int n0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) wv[i] = buffer_load_f32(ws, (n0 + 4 * r + i) * 4);
+    auto load = [&](SplitOp<KB>& xo, u32x4& wv, int n0) {
+        wv = __builtin_amdgcn_raw_buffer_load_b128(ws, (n0 + 4 * r) * 4, 0, 0);
         load_split<KB>(xo, xs, n0 / 16, lane);
     };
     // the chunk's pieces inside fixed-point slices, [s0, s1) relative to i0
     // (chunks need not start on a slice; every piece starts on a batch of 16)
     for (int s0 = 0; s0 < len;) {
         const int64_t slice = (i0 + s0) / kSlice;
-        const int k = slice_exponent(slice_max[slice]);
-        const float scale = ldexpf(1.f, k);
+        const float unscale = ldexpf(1.f, -slice_exponent(slice_max[slice]));
         const int s1 = (int)min((int64_t)len, (slice + 1) * kSlice - i0);
         // batches of 16 sources, wave-strided, two in flight: while one is
         // spread the other's operands load.  Each buffer is reloaded only
@@ -1227,23 +1269,33 @@ __device__ __forceinline__ void spread_fused_body(
         constexpr int stride = kSpreadWaves * 16;
         int n0 = s0 + wave * 16;
         SplitOp<KB> xa, xb;
-        float wa[4], wb[4];
+        u32x4 wa, wb;
         load(xa, wa, n0);
         for (; n0 < s1; n0 += 2 * stride) {
             load(xb, wb, n0 + stride);
-            batch(xa, wa, scale);
+            batch(xa, wa);
             load(xa, wa, n0 + 2 * stride);
-            if (n0 + stride < s1) batch(xb, wb, scale);
+            if (n0 + stride < s1) batch(xb, wb);
+            // used on both paths: loads used only inside the branch would be
+            // moved into it, and waited for there
+            asm volatile("" ::"v"(wb));
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) asm volatile("" ::"v"(xb.hi[kb]), "v"(xb.lo[kb]));
         }
         __syncthreads();
-        const float unscale = ldexpf(1.f, -k);
+        // kFlushGroup cells in flight at once: one by one, each waited for
+        // its LDS read
 #pragma unroll
-        for (int q = 0; q < ACC; ++q) {
-            const int j = tid + q * kSpreadBlock;
-            if (j < ncell) {
-                acc[q] = fmaf((float)cells[j], unscale, acc[q]);
-                cells[j] = 0;
-            }
+        for (int q0 = 0; q0 < ACC; q0 += kFlushGroup) {
+            if (q0 * kSpreadBlock >= ncell) break;
+            int v[kFlushGroup];
+#pragma unroll
+            for (int q = 0; q < kFlushGroup; ++q) v[q] = cells[tid + (q0 + q) * kSpreadBlock];
+#pragma unroll
+            for (int q = 0; q < kFlushGroup; ++q) cells[tid + (q0 + q) * kSpreadBlock] = 0;
+#pragma unroll
+            for (int q = 0; q < kFlushGroup; ++q)
+                acc[q0 + q] = fmaf((float)v[q], unscale, acc[q0 + q]);
         }
         __syncthreads();
         s0 = s1;
@@ -1269,19 +1321,96 @@ __global__ __launch_bounds__(kSpreadBlock) void spread_fused_kernel(
                              partial, blockIdx.x, blockIdx.y);
 }
 
-// Copies the grids of directions p0 .. p0+np-1 (contiguous, np * nr floats)
-// into LDS with 16-byte LDS-direct loads, 1 KB per wave instruction.  Lanes
-// past the end re-read the group's first bytes (in bounds) and write into
-// the buffer's padding.  Completion is tracked by vmcnt.
-__device__ __forceinline__ void gather_stage(const float* __restrict__ grid, int p0, int np,
-                                             int nr, float* buf, int wave, int lane) {
-    const int nbytes = np * nr * 4;
-    const char* src = reinterpret_cast<const char*>(grid + (int64_t)p0 * nr);
-    for (int piece = wave; piece * kDmaBytes < nbytes; piece += kGatherWaves) {
-        int off = piece * kDmaBytes + lane * 16;
-        off = off < nbytes ? off : 0;
-        __builtin_amdgcn_global_load_lds(src + off, (lds_void*)(buf + piece * (kDmaBytes / 4)),
-                                         16, 0, 0);
+// Copies the grids of the 16 directions from p0 (contiguous; a plan's last
+// group is padded with zero rows) into LDS with 16-byte LDS-direct loads, 1 KB
+// per wave instruction; lanes past the end load zeros into the buffer's
+// padding.  Completion is tracked by vmcnt.  Buffer loads: the compiler takes
+// the global form for a flat access and then waits for every LDS read in
+// flight wherever it needs one (lgkmcnt(0)), which undoes the pipeline of
+// gather_group.
+__device__ __forceinline__ void gather_stage(const float* __restrict__ grid, int p0, int nr,
+                                             float* buf, int wave, int lane) {
+    const int nbytes = kFuseDirs * nr * 4;
+    const __amdgpu_buffer_rsrc_t gs = buffer_rsrc(grid + (int64_t)p0 * nr, nbytes);
+    for (int piece = wave; piece * kDmaBytes < nbytes; piece += kGatherWaves)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(gs, (lds_void*)(buf + piece * (kDmaBytes / 4)), 16,
+                                                 lane * 16, piece * kDmaBytes, 0, 0);
+}
+
+// Half a batch (16 targets on one group of 16 directions): the cells around
+// two of the lane's four (target, direction) pairs and the offsets in them.
+template <int W>
+struct TapRead {
+    float sp[2];
+    float c[2][W];
+    // issues the LDS reads of pairs i0, i0 + 1 at projections pr (base[i]:
+    // the grid of the lane's direction i in lds, less ev.off)
+    __device__ __forceinline__ void issue(const f32x4& pr, int i0, const float* lds,
+                                          const int (&base)[4], const WinEval<W>& ev) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float* __restrict__ p = lds + (base[i0 + i] + tap0<W>(pr[i0 + i], ev, sp[i]));
+#pragma unroll
+            for (int k = 0; k < W; ++k) c[i][k] = p[k];
+        }
+    }
+    __device__ __forceinline__ float value(int i, const WinEval<W>& ev,
+                                           const WindowArgs& win) const {
+        float wt[W];
+        window_weights<W>(sp[i], win, ev, wt);
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < W; ++k) t = fmaf(c[i][k], wt[k], t);
+        return t;
+    }
+};
+
+// Forms a result before any later LDS read is issued (left alone, the
+// compiler moves all arithmetic behind all reads and spills).
+__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)::"memory"); }
+
+// The batches of one group through a pipeline of half batches: the
+// projections of batch b + 2 on the matrix cores, the LDS reads of the next
+// half batch, the interpolation of this one (its two values to use(b, h,
+// values)).  The reads return while the half before is interpolated: with
+// the reads next to their use a wave waited out the LDS latency twice per
+// batch, and at two waves per SIMD the LDS time added to the VALU time
+// instead of hiding under it.  Half batches, because a wave can count no
+// more than 15 reads in flight.  reload() is called once, after the last use
+// of the direction operand dop.
+template <int W, int KB, int NB, class Use, class Reload>
+__device__ __forceinline__ void gather_group(const float* lds, const int (&base)[4],
+                                             const SplitOp<KB>& dop,
+                                             const SplitOp<KB> (&yop)[NB], const WinEval<W>& ev,
+                                             const WindowArgs& win, Use use, Reload reload) {
+    static_assert(NB >= 2, "the pipeline holds two batches");
+    // C[dir][target]: lane holds directions 4r + i of target c
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+    TapRead<W> tr[2];
+    f32x4 pr = split_mfma<KB>(dop, yop[0], zero), nx = split_mfma<KB>(dop, yop[1], zero);
+    if constexpr (NB == 2) reload();
+    tr[0].issue(pr, 0, lds, base, ev);
+#pragma unroll
+    for (int u = 0; u < 2 * NB; ++u) {
+        const int b = u / 2, h = u & 1;
+        if (h == 0) {
+            tr[1].issue(pr, 2, lds, base, ev);
+        } else if (b + 1 < NB) {
+            pr = nx;
+            tr[0].issue(pr, 0, lds, base, ev);
+        }
+        asm volatile("" ::: "memory");          // the reads stay ahead of the arithmetic
+        if (h == 1 && b + 2 < NB) {
+            nx = split_mfma<KB>(dop, yop[b + 2], zero);
+            if (b + 3 == NB) reload();
+        }
+        float v[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            v[i] = tr[h].value(i, ev, win);
+            pin(v[i]);
+        }
+        use(b, h, v);
     }
 }
 
@@ -1307,7 +1436,7 @@ __device__ __forceinline__ void gather_fused_body(
     const int64_t tw = (mb + wave * (NB * 16)) / 16;   // wave's first target tile
     const int p_begin = range * prange;
     const int p_end = min(P, p_begin + prange);
-    gather_stage(grid, p_begin, min(kFuseDirs, p_end - p_begin), g.nr, gls, wave, lane);
+    gather_stage(grid, p_begin, g.nr, gls, wave, lane);
     // target tiles past the last one read as zero
     const int64_t ntiles = (M + 15) / 16;
     const __amdgpu_buffer_rsrc_t ys =
@@ -1320,93 +1449,31 @@ __device__ __forceinline__ void gather_fused_body(
 #pragma unroll
     for (int b = 0; b < NB; ++b) accd[b] = 0.0;
     const WinEval<W> ev(g, win, pscale);
-    // Projections of all batches on one group, k-block by k-block across
-    // the batches (independent accumulations), then the interpolation.
-    // Branch-free: a direction past np (ragged last group) interpolates
-    // whatever its LDS row holds and the result is masked to zero by bits
-    // (a select here would be turned into a branch around the LDS reads).
-    auto group = [&](int np, const float* gb, const SplitOp<KB>& dop) {
-        f32x4 pr[NB];
+    // Before a group starts, this wave's fetches have landed (vmcnt) and,
+    // after the barrier, every wave's have and no wave still reads the buffer
+    // about to be refilled.
+    SplitOp<KB> dop;
+    load_split<KB>(dop, At, p_begin / kFuseDirs, lane);
+    for (int p0 = p_begin, k = 0; p0 < p_end; p0 += kFuseDirs, k ^= 1) {
+        const int p1 = p0 + kFuseDirs;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (!WIDE && p1 < p_end) gather_stage(grid, p1, g.nr, gls + (k ^ 1) * stage, wave, lane);
+        int base[4];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) pr[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.hi[kb], yop[b].lo[kb], pr[b], 0, 0, 0);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.lo[kb], yop[b].hi[kb], pr[b], 0, 0, 0);
-        }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                // C[dir][target]: lane holds directions 4r + i of target c
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.hi[kb], yop[b].hi[kb], pr[b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float t = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int dir = 4 * r + i;
-                const float v = interp<W>(pr[b][i], gb + dir * g.nr, ev, win);
-                const unsigned keep = 0u - (unsigned)(dir < np);
-                t += __uint_as_float(__float_as_uint(v) & keep);
-            }
-            accd[b] += (double)t;
-        }
-    };
-    // Two groups per iteration, ping-ponging buffers and direction
-    // operands: a group's grids and operand are fetched while the previous
-    // group is interpolated.  Before a group starts, this wave's fetches have
-    // landed (vmcnt) and, after the barrier, every wave's have and no wave
-    // still reads the buffer about to be refilled.
-    SplitOp<KB> da, db;
-    load_split<KB>(da, At, p_begin / kFuseDirs, lane);
-    if constexpr (WIDE) {
-        // one buffer: after a group every wave leaves it before the next
-        // group's grids go in; the next direction operand still loads
-        // during the group
-        for (int p0 = p_begin; p0 < p_end; p0 += 2 * kFuseDirs) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        for (int i = 0; i < 4; ++i) base[i] = (WIDE ? 0 : k * stage) + (4 * r + i) * g.nr - ev.off;
+        float t = 0.f;
+        gather_group<W, KB, NB>(
+            gls, base, dop, yop, ev, win,
+            [&](int b, int h, const float (&v)[2]) {
+                t = h ? t + v[0] : v[0];
+                t += v[1];
+                if (h) accd[b] += (double)t;
+            },
+            [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); });
+        if (WIDE && p1 < p_end) {
             __syncthreads();
-            const int p1 = p0 + kFuseDirs;
-            if (p1 < p_end) load_split<KB>(db, At, p1 / kFuseDirs, lane);
-            group(min(kFuseDirs, p_end - p0), gls, da);
-            if (p1 >= p_end) break;
-            __syncthreads();
-            gather_stage(grid, p1, min(kFuseDirs, p_end - p1), g.nr, gls, wave, lane);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p2 = p1 + kFuseDirs;
-            if (p2 < p_end) load_split<KB>(da, At, p2 / kFuseDirs, lane);
-            group(min(kFuseDirs, p_end - p1), gls, db);
-            if (p2 >= p_end) break;
-            __syncthreads();
-            gather_stage(grid, p2, min(kFuseDirs, p_end - p2), g.nr, gls, wave, lane);
-        }
-    } else {
-        float* buf0 = gls;
-        float* buf1 = gls + stage;
-        for (int p0 = p_begin; p0 < p_end; p0 += 2 * kFuseDirs) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p1 = p0 + kFuseDirs;
-            if (p1 < p_end) {
-                gather_stage(grid, p1, min(kFuseDirs, p_end - p1), g.nr, buf1, wave, lane);
-                load_split<KB>(db, At, p1 / kFuseDirs, lane);
-            }
-            group(min(kFuseDirs, p_end - p0), buf0, da);
-            if (p1 >= p_end) break;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p2 = p1 + kFuseDirs;
-            if (p2 < p_end) {
-                gather_stage(grid, p2, min(kFuseDirs, p_end - p2), g.nr, buf0, wave, lane);
-                load_split<KB>(da, At, p2 / kFuseDirs, lane);
-            }
-            group(min(kFuseDirs, p_end - p1), buf1, db);
+            gather_stage(grid, p1, g.nr, gls, wave, lane);
         }
     }
     // sum the four lane groups r holding the same targets
@@ -1460,7 +1527,7 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
     const int64_t tw = (mb + wave * (kGradNB * 16)) / 16;     // wave's first target tile
     const int p_begin = blockIdx.y * prange;
     const int p_end = min(P, p_begin + prange);
-    gather_stage(grid_d, p_begin, min(kFuseDirs, p_end - p_begin), g.nr, gls, wave, lane);
+    gather_stage(grid_d, p_begin, g.nr, gls, wave, lane);
     const int64_t ntiles = (M + 15) / 16;
     const __amdgpu_buffer_rsrc_t ys =
         buffer_rsrc(Yt + tw * KB * 2 * (kSplitTileBytes / 2),
@@ -1474,94 +1541,40 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
 #pragma unroll
         for (int q = 0; q < kGradMaxDC; ++q) gacc[b][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const WinEval<W> ev(g, win, pscale);
-    auto group = [&](int np, const float* gb, const SplitOp<KB>& dop, int grp) {
-        f32x4 pr[kGradNB];
-#pragma unroll
-        for (int b = 0; b < kGradNB; ++b) pr[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-#pragma unroll
-            for (int b = 0; b < kGradNB; ++b)
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.hi[kb], yop[b].lo[kb], pr[b], 0, 0, 0);
-#pragma unroll
-            for (int b = 0; b < kGradNB; ++b)
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.lo[kb], yop[b].hi[kb], pr[b], 0, 0, 0);
-        }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int b = 0; b < kGradNB; ++b)
-                pr[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dop.hi[kb], yop[b].hi[kb], pr[b], 0, 0, 0);
+    SplitOp<KB> dop;
+    load_split<KB>(dop, At, p_begin / kFuseDirs, lane);
+    // buffers and waits as in gather_fused_body
+    for (int p0 = p_begin, k = 0; p0 < p_end; p0 += kFuseDirs, k ^= 1) {
+        const int p1 = p0 + kFuseDirs;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
         // this lane's back-projection operands of the group
-        const float* __restrict__ ag = Ab + (int64_t)grp * 4 * DC * 64 + lane;
+        const float* __restrict__ ag = Ab + (int64_t)(p0 / kFuseDirs) * 4 * DC * 64 + lane;
         float abv[kGradMaxDC][4];
 #pragma unroll
         for (int q = 0; q < kGradMaxDC; ++q)
 #pragma unroll
             for (int i = 0; i < 4; ++i) abv[q][i] = q < DC ? ag[(i * DC + q) * 64] : 0.f;
+        if (!WIDE && p1 < p_end) gather_stage(grid_d, p1, g.nr, gls + (k ^ 1) * stage, wave, lane);
+        int base[4];
 #pragma unroll
-        for (int b = 0; b < kGradNB; ++b) {
-            float tv[4];
+        for (int i = 0; i < 4; ++i) base[i] = (WIDE ? 0 : k * stage) + (4 * r + i) * g.nr - ev.off;
+        gather_group<W, KB, kGradNB>(
+            gls, base, dop, yop, ev, win,
+            [&](int b, int h, const float (&v)[2]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int dir = 4 * r + i;
-                const float v = interp<W>(pr[b][i], gb + dir * g.nr, ev, win);
-                const unsigned keep = 0u - (unsigned)(dir < np);
-                tv[i] = __uint_as_float(__float_as_uint(v) & keep);
-            }
+                for (int q = 0; q < kGradMaxDC; ++q) {
+                    if (q >= DC) break;
 #pragma unroll
-            for (int q = 0; q < kGradMaxDC; ++q) {
-                if (q >= DC) break;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(abv[q][i], tv[i], gacc[b][q],
-                                                                      0, 0, 0);
-            }
-        }
-    };
-    SplitOp<KB> da, db;
-    load_split<KB>(da, At, p_begin / kFuseDirs, lane);
-    float* buf0 = gls;
-    if constexpr (WIDE) {
-        // one buffer, refilled after each group (see gather_fused_body)
-        for (int p0 = p_begin; p0 < p_end; p0 += 2 * kFuseDirs) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    for (int i = 0; i < 2; ++i)
+                        gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(abv[q][2 * h + i], v[i],
+                                                                          gacc[b][q], 0, 0, 0);
+                }
+            },
+            [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); });
+        if (WIDE && p1 < p_end) {
             __syncthreads();
-            const int p1 = p0 + kFuseDirs;
-            if (p1 < p_end) load_split<KB>(db, At, p1 / kFuseDirs, lane);
-            group(min(kFuseDirs, p_end - p0), buf0, da, p0 / kFuseDirs);
-            if (p1 >= p_end) break;
-            __syncthreads();
-            gather_stage(grid_d, p1, min(kFuseDirs, p_end - p1), g.nr, buf0, wave, lane);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p2 = p1 + kFuseDirs;
-            if (p2 < p_end) load_split<KB>(da, At, p2 / kFuseDirs, lane);
-            group(min(kFuseDirs, p_end - p1), buf0, db, p1 / kFuseDirs);
-            if (p2 >= p_end) break;
-            __syncthreads();
-            gather_stage(grid_d, p2, min(kFuseDirs, p_end - p2), g.nr, buf0, wave, lane);
-        }
-    } else {
-        float* buf1 = gls + stage;
-        for (int p0 = p_begin; p0 < p_end; p0 += 2 * kFuseDirs) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p1 = p0 + kFuseDirs;
-            if (p1 < p_end) {
-                gather_stage(grid_d, p1, min(kFuseDirs, p_end - p1), g.nr, buf1, wave, lane);
-                load_split<KB>(db, At, p1 / kFuseDirs, lane);
-            }
-            group(min(kFuseDirs, p_end - p0), buf0, da, p0 / kFuseDirs);
-            if (p1 >= p_end) break;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            const int p2 = p1 + kFuseDirs;
-            if (p2 < p_end) {
-                gather_stage(grid_d, p2, min(kFuseDirs, p_end - p2), g.nr, buf0, wave, lane);
-                load_split<KB>(da, At, p2 / kFuseDirs, lane);
-            }
-            group(min(kFuseDirs, p_end - p1), buf1, db, p1 / kFuseDirs);
+            gather_stage(grid_d, p1, g.nr, gls, wave, lane);
         }
     }
     // lane (c, r) holds coordinates 16 q + 4 r + j of target c
@@ -1653,14 +1666,18 @@ hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const 
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
                        const float*, int, int, const GridGeom&, float, const float*, int, int,
                        const WindowArgs&, float*, int64_t);
-    static const L t[2][3][2] = {
-        {{launch_gather_grad_t<4, 1, false>, launch_gather_grad_t<4, 2, false>},
+    static const L t[2][5][2] = {
+        {{launch_gather_grad_t<3, 1, false>, launch_gather_grad_t<3, 2, false>},
+         {launch_gather_grad_t<4, 1, false>, launch_gather_grad_t<4, 2, false>},
+         {launch_gather_grad_t<5, 1, false>, launch_gather_grad_t<5, 2, false>},
          {launch_gather_grad_t<6, 1, false>, launch_gather_grad_t<6, 2, false>},
          {launch_gather_grad_t<8, 1, false>, launch_gather_grad_t<8, 2, false>}},
-        {{launch_gather_grad_t<4, 1, true>, launch_gather_grad_t<4, 2, true>},
+        {{launch_gather_grad_t<3, 1, true>, launch_gather_grad_t<3, 2, true>},
+         {launch_gather_grad_t<4, 1, true>, launch_gather_grad_t<4, 2, true>},
+         {launch_gather_grad_t<5, 1, true>, launch_gather_grad_t<5, 2, true>},
          {launch_gather_grad_t<6, 1, true>, launch_gather_grad_t<6, 2, true>},
          {launch_gather_grad_t<8, 1, true>, launch_gather_grad_t<8, 2, true>}}};
-    const int wi = W == 4 ? 0 : W == 6 ? 1 : W == 8 ? 2 : -1;
+    const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     const int DC = (d + 15) / 16;
     const int stage = (kFuseDirs * g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
@@ -1703,29 +1720,31 @@ hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, ui
     return hipGetLastError();
 }
 
-void fused_occupancy(int W, int d, int nr, int* spread_blocks, int* gather_blocks) {
+void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gather_blocks) {
     *spread_blocks = 1;
     *gather_blocks = 1;
     if (!fused_supported(d, nr)) return;
     const bool wide = fused_wide(nr);
-    const void* sk = nullptr;
-    const void* gk = nullptr;
     // occupancy is set by LDS and registers; the larger operand shape
     // stands for both
-    switch (W) {
-        case 4:
-            sk = wide ? (const void*)&spread_fused_kernel<4, 2, kFuseAccWide> : (const void*)&spread_fused_kernel<4, 2, kFuseAcc>;
-            gk = wide ? (const void*)&gather_fused_kernel<4, 2, true> : (const void*)&gather_fused_kernel<4, 2, false>;
-            break;
-        case 6:
-            sk = wide ? (const void*)&spread_fused_kernel<6, 2, kFuseAccWide> : (const void*)&spread_fused_kernel<6, 2, kFuseAcc>;
-            gk = wide ? (const void*)&gather_fused_kernel<6, 2, true> : (const void*)&gather_fused_kernel<6, 2, false>;
-            break;
-        default:
-            sk = wide ? (const void*)&spread_fused_kernel<8, 2, kFuseAccWide> : (const void*)&spread_fused_kernel<8, 2, kFuseAcc>;
-            gk = wide ? (const void*)&gather_fused_kernel<8, 2, true> : (const void*)&gather_fused_kernel<8, 2, false>;
-            break;
-    }
+    const void* sks[2][5] = {
+        {(const void*)&spread_fused_kernel<3, 2, kFuseAcc>, (const void*)&spread_fused_kernel<4, 2, kFuseAcc>,
+         (const void*)&spread_fused_kernel<5, 2, kFuseAcc>, (const void*)&spread_fused_kernel<6, 2, kFuseAcc>,
+         (const void*)&spread_fused_kernel<8, 2, kFuseAcc>},
+        {(const void*)&spread_fused_kernel<3, 2, kFuseAccWide>, (const void*)&spread_fused_kernel<4, 2, kFuseAccWide>,
+         (const void*)&spread_fused_kernel<5, 2, kFuseAccWide>, (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
+         (const void*)&spread_fused_kernel<8, 2, kFuseAccWide>}};
+    const void* gks[2][5] = {
+        {(const void*)&gather_fused_kernel<3, 2, false>, (const void*)&gather_fused_kernel<4, 2, false>,
+         (const void*)&gather_fused_kernel<5, 2, false>, (const void*)&gather_fused_kernel<6, 2, false>,
+         (const void*)&gather_fused_kernel<8, 2, false>},
+        {(const void*)&gather_fused_kernel<3, 2, true>, (const void*)&gather_fused_kernel<4, 2, true>,
+         (const void*)&gather_fused_kernel<5, 2, true>, (const void*)&gather_fused_kernel<6, 2, true>,
+         (const void*)&gather_fused_kernel<8, 2, true>}};
+    const int si = width_index(Ws), gi = width_index(Wg);
+    if (si < 0 || gi < 0) return;
+    const void* sk = sks[wide][si];
+    const void* gk = gks[wide][gi];
     const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
     (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize,
                               kFuseMaxCellsWide * (int)sizeof(int));
@@ -1733,7 +1752,7 @@ void fused_occupancy(int W, int d, int nr, int* spread_blocks, int* gather_block
                               2 * kFuseMaxCells * (int)sizeof(float));
     int b = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, sk, kSpreadBlock,
-                                                     (size_t)kFuseDirs * nr * sizeof(int)) == hipSuccess && b > 0)
+                                                     fused_spread_lds(nr)) == hipSuccess && b > 0)
         *spread_blocks = b;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, gk, kGatherBlock,
                                                      (size_t)(wide ? 1 : 2) * stage * sizeof(float)) == hipSuccess && b > 0)
@@ -1742,27 +1761,31 @@ void fused_occupancy(int W, int d, int nr, int* spread_blocks, int* gather_block
 
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
                                const float* w, int P, GridGeom g, float pscale, int nchunk,
-                               int64_t chunk_len, float* slice_max, const WindowArgs& win,
-                               float* partial, hipStream_t stream) {
+                               int64_t chunk_len, float* slice_max, float* wscaled,
+                               const WindowArgs& win, float* partial, hipStream_t stream) {
     if (!fused_supported(d, g.nr) || chunk_len % 16 != 0 || chunk_len <= 0)
         return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
                        const float*, int, const GridGeom&, float, int64_t, const float*,
                        const WindowArgs&, float*);
-    static const L t[2][3][2] = {
-        {{launch_spread_fused_t<4, 1, kFuseAcc>, launch_spread_fused_t<4, 2, kFuseAcc>},
+    static const L t[2][5][2] = {
+        {{launch_spread_fused_t<3, 1, kFuseAcc>, launch_spread_fused_t<3, 2, kFuseAcc>},
+         {launch_spread_fused_t<4, 1, kFuseAcc>, launch_spread_fused_t<4, 2, kFuseAcc>},
+         {launch_spread_fused_t<5, 1, kFuseAcc>, launch_spread_fused_t<5, 2, kFuseAcc>},
          {launch_spread_fused_t<6, 1, kFuseAcc>, launch_spread_fused_t<6, 2, kFuseAcc>},
          {launch_spread_fused_t<8, 1, kFuseAcc>, launch_spread_fused_t<8, 2, kFuseAcc>}},
-        {{launch_spread_fused_t<4, 1, kFuseAccWide>, launch_spread_fused_t<4, 2, kFuseAccWide>},
+        {{launch_spread_fused_t<3, 1, kFuseAccWide>, launch_spread_fused_t<3, 2, kFuseAccWide>},
+         {launch_spread_fused_t<4, 1, kFuseAccWide>, launch_spread_fused_t<4, 2, kFuseAccWide>},
+         {launch_spread_fused_t<5, 1, kFuseAccWide>, launch_spread_fused_t<5, 2, kFuseAccWide>},
          {launch_spread_fused_t<6, 1, kFuseAccWide>, launch_spread_fused_t<6, 2, kFuseAccWide>},
          {launch_spread_fused_t<8, 1, kFuseAccWide>, launch_spread_fused_t<8, 2, kFuseAccWide>}}};
-    const int wi = W == 4 ? 0 : W == 6 ? 1 : W == 8 ? 2 : -1;
+    const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max);
+                       0, stream, w, N, slice_max, wscaled);
     dim3 grid((unsigned)((P + kFuseDirs - 1) / kFuseDirs), (unsigned)nchunk);
-    t[fused_wide(g.nr)][wi][split_kblocks(d) - 1](grid, (size_t)kFuseDirs * g.nr * sizeof(int),
-                                                  stream, Xt, N, At, w, P, g, pscale, chunk_len,
+    t[fused_wide(g.nr)][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
+                                                  Xt, N, At, wscaled, P, g, pscale, chunk_len,
                                                   slice_max, win, partial);
     return hipGetLastError();
 }
@@ -1775,14 +1798,18 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*, int,
                        const GridGeom&, float, const float*, int, int, const WindowArgs&, double*,
                        int64_t);
-    static const L t[2][3][2] = {
-        {{launch_gather_fused_t<4, 1, false>, launch_gather_fused_t<4, 2, false>},
+    static const L t[2][5][2] = {
+        {{launch_gather_fused_t<3, 1, false>, launch_gather_fused_t<3, 2, false>},
+         {launch_gather_fused_t<4, 1, false>, launch_gather_fused_t<4, 2, false>},
+         {launch_gather_fused_t<5, 1, false>, launch_gather_fused_t<5, 2, false>},
          {launch_gather_fused_t<6, 1, false>, launch_gather_fused_t<6, 2, false>},
          {launch_gather_fused_t<8, 1, false>, launch_gather_fused_t<8, 2, false>}},
-        {{launch_gather_fused_t<4, 1, true>, launch_gather_fused_t<4, 2, true>},
+        {{launch_gather_fused_t<3, 1, true>, launch_gather_fused_t<3, 2, true>},
+         {launch_gather_fused_t<4, 1, true>, launch_gather_fused_t<4, 2, true>},
+         {launch_gather_fused_t<5, 1, true>, launch_gather_fused_t<5, 2, true>},
          {launch_gather_fused_t<6, 1, true>, launch_gather_fused_t<6, 2, true>},
          {launch_gather_fused_t<8, 1, true>, launch_gather_fused_t<8, 2, true>}}};
-    const int wi = W == 4 ? 0 : W == 6 ? 1 : W == 8 ? 2 : -1;
+    const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     // one staging buffer: the group's grids rounded up to whole 1 KB pieces
     const int stage = (kFuseDirs * g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
@@ -1835,18 +1862,19 @@ __global__ __launch_bounds__(kBlock) void batch_scale_kernel(
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
-        slice_max_tile(red, pr.w, pr.N, tk.a, pr.slice_max);
+        slice_max_tile(red, pr.w, pr.N, tk.a, pr.slice_max, pr.wscaled);
     }
 }
 
 template <int W>
 __global__ __launch_bounds__(kBlock) void batch_spread_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
-    int P, WindowArgs win) {
+    int P) {
     extern __shared__ int lds_bspread[];
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
+        const WindowArgs win = pr.swin;
         spread_tile<W>(lds_bspread, pr.xproj, pr.ldx, pr.w, pr.N, P, pr.g, pr.chunk_len,
                        pr.slice_max, win, pr.partial, tk.a, tk.b);
     }
@@ -1867,11 +1895,12 @@ __global__ __launch_bounds__(kBlock) void batch_fftconv_kernel(
 template <int W>
 __global__ __launch_bounds__(kBlock) void batch_gather_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
-    int P, int pstage, WindowArgs win) {
+    int P, int pstage) {
     extern __shared__ float lds[];
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
+        const WindowArgs win = pr.gwin;
         const float* yp = pr.same_xy ? pr.xproj : pr.yproj;
         const int64_t ldy = pr.same_xy ? pr.ldx : pr.ldy;
         gather_tile<W, false>(lds, yp, ldy, pr.M, P, pr.g, pr.grid, pr.pg, pstage, win,
@@ -1920,16 +1949,17 @@ template <int W>
 __global__ __launch_bounds__(kSpreadBlock) __attribute__((amdgpu_waves_per_eu(4))) void
 batch_spread_fused_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
-    int P, WindowArgs win) {
+    int P) {
     extern __shared__ int bcells[];
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
+        const WindowArgs win = pr.swin;
         if (pr.kb == 1)
-            spread_fused_body<W, 1, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.w, P, pr.g, pr.pscale,
+            spread_fused_body<W, 1, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         else
-            spread_fused_body<W, 2, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.w, P, pr.g, pr.pscale,
+            spread_fused_body<W, 2, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         __syncthreads();
     }
@@ -1938,13 +1968,14 @@ batch_spread_fused_kernel(
 template <int W>
 __global__ __launch_bounds__(kGatherBlock) void batch_gather_fused_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
-    int P, WindowArgs win) {
+    int P) {
     extern __shared__ float bgls[];
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
         const int stage = (kFuseDirs * pr.g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
         const uint16_t* yt = pr.same_xy ? pr.xt : pr.yt;
+        const WindowArgs win = pr.gwin;
         // no wave may still read the staging buffers of the previous task
         __syncthreads();
         if (pr.kb == 1)
@@ -1956,7 +1987,7 @@ __global__ __launch_bounds__(kGatherBlock) void batch_gather_fused_kernel(
     }
 }
 
-size_t fused_spread_lds(int nr) { return (size_t)kFuseDirs * nr * sizeof(int); }
+size_t fused_spread_lds(int nr) { return (size_t)spread_cells(nr) * sizeof(int); }
 
 size_t stored_spread_lds(int nr) { return (size_t)nr * sizeof(int); }
 
@@ -1967,7 +1998,7 @@ size_t fused_gather_lds(int nr) {
 
 template <int W>
 void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const BatchTask* tasks,
-                          int ntasks, int P, const WindowArgs& win, size_t lds,
+                          int ntasks, int P, size_t lds,
                           hipStream_t stream) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
@@ -1981,15 +2012,15 @@ void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const
     }
     if (phase == kBatchSpread)
         hipLaunchKernelGGL((batch_spread_fused_kernel<W>), grid, dim3(kSpreadBlock), lds, stream,
-                           probs, tasks, ntasks, P, win);
+                           probs, tasks, ntasks, P);
     else
         hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(kGatherBlock), lds, stream,
-                           probs, tasks, ntasks, P, win);
+                           probs, tasks, ntasks, P);
 }
 
 hipError_t launch_batch_phase_fused(int phase, int W, const BatchProblem* probs,
                                     const BatchTask* tasks, int ntasks, int P,
-                                    const WindowArgs& win, int* flag, int grid_blocks,
+                                    int* flag, int grid_blocks,
                                     size_t lds_bytes, hipStream_t stream) {
     if (ntasks <= 0) return hipSuccess;
     if (phase == kBatchProject) {
@@ -1998,13 +2029,15 @@ hipError_t launch_batch_phase_fused(int phase, int W, const BatchProblem* probs,
         return hipGetLastError();
     }
     if (phase != kBatchSpread && phase != kBatchGather)
-        return launch_batch_phase(phase, W, probs, tasks, ntasks, P, 8, win, flag, grid_blocks,
+        return launch_batch_phase(phase, W, probs, tasks, ntasks, P, 8, flag, grid_blocks,
                                   lds_bytes, stream);
     const dim3 grid((unsigned)ntasks);
     switch (W) {
-        case 4: launch_batch_fused_t<4>(phase, grid, probs, tasks, ntasks, P, win, lds_bytes, stream); break;
-        case 6: launch_batch_fused_t<6>(phase, grid, probs, tasks, ntasks, P, win, lds_bytes, stream); break;
-        case 8: launch_batch_fused_t<8>(phase, grid, probs, tasks, ntasks, P, win, lds_bytes, stream); break;
+        case 3: launch_batch_fused_t<3>(phase, grid, probs, tasks, ntasks, P, lds_bytes, stream); break;
+        case 4: launch_batch_fused_t<4>(phase, grid, probs, tasks, ntasks, P, lds_bytes, stream); break;
+        case 5: launch_batch_fused_t<5>(phase, grid, probs, tasks, ntasks, P, lds_bytes, stream); break;
+        case 6: launch_batch_fused_t<6>(phase, grid, probs, tasks, ntasks, P, lds_bytes, stream); break;
+        case 8: launch_batch_fused_t<8>(phase, grid, probs, tasks, ntasks, P, lds_bytes, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2012,7 +2045,7 @@ hipError_t launch_batch_phase_fused(int phase, int W, const BatchProblem* probs,
 
 hipError_t launch_batch_phase(int phase, int W, const BatchProblem* probs,
                               const BatchTask* tasks, int ntasks, int P, int pstage,
-                              const WindowArgs& win, int* flag, int grid_blocks,
+                              int* flag, int grid_blocks,
                               size_t lds_bytes, hipStream_t stream) {
     if (ntasks <= 0) return hipSuccess;
     const dim3 grid((unsigned)(grid_blocks < ntasks ? grid_blocks : ntasks)), block(kBlock);
@@ -2025,9 +2058,11 @@ hipError_t launch_batch_phase(int phase, int W, const BatchProblem* probs,
             break;
         case kBatchSpread:
             switch (W) {
-                case 4: hipLaunchKernelGGL(batch_spread_kernel<4>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, win); break;
-                case 6: hipLaunchKernelGGL(batch_spread_kernel<6>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, win); break;
-                case 8: hipLaunchKernelGGL(batch_spread_kernel<8>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, win); break;
+                case 3: hipLaunchKernelGGL(batch_spread_kernel<3>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P); break;
+        case 4: hipLaunchKernelGGL(batch_spread_kernel<4>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P); break;
+                case 5: hipLaunchKernelGGL(batch_spread_kernel<5>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P); break;
+                case 6: hipLaunchKernelGGL(batch_spread_kernel<6>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P); break;
+                case 8: hipLaunchKernelGGL(batch_spread_kernel<8>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P); break;
                 default: return hipErrorInvalidValue;
             }
             break;
@@ -2036,9 +2071,11 @@ hipError_t launch_batch_phase(int phase, int W, const BatchProblem* probs,
             break;
         case kBatchGather:
             switch (W) {
-                case 4: hipLaunchKernelGGL(batch_gather_kernel<4>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage, win); break;
-                case 6: hipLaunchKernelGGL(batch_gather_kernel<6>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage, win); break;
-                case 8: hipLaunchKernelGGL(batch_gather_kernel<8>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage, win); break;
+                case 3: hipLaunchKernelGGL(batch_gather_kernel<3>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage); break;
+        case 4: hipLaunchKernelGGL(batch_gather_kernel<4>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage); break;
+                case 5: hipLaunchKernelGGL(batch_gather_kernel<5>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage); break;
+                case 6: hipLaunchKernelGGL(batch_gather_kernel<6>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage); break;
+                case 8: hipLaunchKernelGGL(batch_gather_kernel<8>, grid, block, lds_bytes, stream, probs, tasks, ntasks, P, pstage); break;
                 default: return hipErrorInvalidValue;
             }
             break;

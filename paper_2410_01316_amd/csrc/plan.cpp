@@ -193,6 +193,7 @@ fastsum_status resolve_params(const fastsum_params* in, Resolved& r) {
     if (p.n_ft < 16 || p.n_ft > 4096 || (p.n_ft % 2)) return FASTSUM_EINVAL;
     // Laplace keeps a k^-2 spectrum up to N_ft/2, where the width-4 window's
     // aliasing error reaches ~1e-4; width 6 brings it to ~4e-6.
+    r.fitted = p.window_w == 0 && p.oversample == 0;
     if (p.window_w == 0) p.window_w = (p.kernel == FASTSUM_LAPLACE) ? 6 : 4;
     if (p.window_w != 4 && p.window_w != 6 && p.window_w != 8) return FASTSUM_EINVAL;
     if (p.oversample == 0) p.oversample = 2;
@@ -226,7 +227,7 @@ fastsum_status resolve_params(const fastsum_params* in, Resolved& r) {
 GridGeom make_geom(int n, int W, double tauR) {
     GridGeom g;
     g.n = n;
-    const int half = (int)std::ceil(tauR * n) + W / 2 + 1;
+    const int half = (int)std::ceil(tauR * n) + (W + 1) / 2 + 1;
     int lo = std::max(0, n / 2 - half);
     lo &= ~3;
     g.lo = lo;
@@ -238,7 +239,7 @@ WindowArgs pack_window(const WindowPoly& win) {
     WindowArgs a;
     std::memset(&a, 0, sizeof(a));
     const int nc = win.D + 1;
-    for (int t = 0; t < win.W / 2; ++t)
+    for (int t = 0; t < (win.W + 1) / 2; ++t)    // for odd W the last is the centre tap
         for (int k = 0; k < nc; ++k) {
             if (k % 2 == 0) a.even[t][k / 2] = (float)win.coef[t * nc + k];
             else a.odd[t][k / 2] = (float)win.coef[t * nc + k];
@@ -254,30 +255,42 @@ uint16_t f32_to_bf16_host(float f) {
     return (uint16_t)(u >> 16);
 }
 
-void build_tables(int kernel, int d, double scale, double tau, int n_ft, int n,
-                  const WindowPoly& win, std::vector<float2>& mult,
+void build_tables(const Resolved& r, const WindowPlan& wp, std::vector<float2>& mult,
                   std::vector<float2>& mult_d, std::vector<float2>& tw) {
     std::vector<double> c;
-    fourier_coefficients(kernel, d, scale, tau, n_ft, c);
-    std::vector<double> ph;
-    window_transform(win, n, n / 2, ph);
-    const int K = n_ft / 2;
+    fourier_coefficients(r.p.kernel, r.p.d, r.p.scale, r.tau, r.p.n_ft, c);
+    const int K = r.p.n_ft / 2, n = wp.n;
     mult.assign(n, make_float2(0.f, 0.f));
     mult_d.assign(n, make_float2(0.f, 0.f));
     tw.assign(n, make_float2(0.f, 0.f));
-    for (int k = 0; k < n; ++k) {
-        const int ks = (k <= n / 2) ? k : k - n;
-        const int a = std::abs(ks);
-        double m = 0.0;
-        if (a <= K) {
-            const double cp = (a == K) ? 0.5 * c[a] : c[a];
-            const double den = n * ph[a];
-            m = cp / (den * den);
+    for (int k = 0; k <= n / 2; ++k) {
+        // a fitted grid may end below mode K: it holds every mode whose
+        // coefficient is not negligible
+        if (k <= K && k < n / 2) {
+            const double om = 2.0 * kPi * k / n;
+            const double cp = (k == K) ? 0.5 * c[k] : c[k];
+            const double ps = window_transform_at(wp.spread, om);
+            const double m = cp / (ps * window_transform_at(wp.gather, om));
+            const double md = 2.0 * kPi * k * cp / (ps * window_transform_at(wp.deriv, om));
+            mult[k].x = (float)m;
+            mult_d[k].y = (float)md;
+            if (k > 0) {
+                mult[n - k].x = (float)m;
+                mult_d[n - k].y = (float)-md;
+            }
         }
-        mult[k] = make_float2((float)m, 0.f);
-        mult_d[k] = make_float2(0.f, (float)(2.0 * kPi * ks * m));
-        tw[k] = make_float2((float)std::cos(2.0 * kPi * k / n), (float)-std::sin(2.0 * kPi * k / n));
     }
+    for (int k = 0; k < n; ++k)
+        tw[k] = make_float2((float)std::cos(2.0 * kPi * k / n), (float)-std::sin(2.0 * kPi * k / n));
+}
+
+bool resolve_windows(const Resolved& r, bool grad, WindowPlan& out) {
+    if (!build_window(r.p.window_w, out.spread)) return false;
+    out.gather = out.deriv = out.spread;
+    out.n = r.n;
+    // sorted plans have no grids
+    if (r.fitted && !(r.p.flags & FASTSUM_FLAG_SORTED)) (void)window_plan(r, grad, out);
+    return true;
 }
 
 int spread_chunks(int64_t N, int P) {
@@ -435,10 +448,11 @@ fastsum_status status_of(hipError_t e) {
 
 struct fastsum_plan_s {
     Resolved r;
-    WindowPoly win;
-    WindowArgs win_args;
+    WindowPlan win;                // grid size and windows (spread, gather, derivative gather)
+    WindowArgs swin, gwin, dwin;
     GridGeom geom;
-    int d = 0, P = 0, dpad = 0, dpad64 = 0, W = 4;
+    int d = 0, P = 0, dpad = 0, dpad64 = 0;
+    int Ws = 4, Wg = 4, Wd = 4;    // their widths
     int64_t n_max = 0, m_max = 0, ld_x = 0, ld_y = 0, ldm = 0;
     int nchunk_cap = 1, pstage = 8, ngroup_cap = 1;
     bool fused = false;               // projections inside spread / gather
@@ -483,6 +497,7 @@ struct fastsum_plan_s {
     bool norms_dirty = false;      // an exec stopped before its check cleared them
     float norm_lim = 1.f;          // (1 + 1e-5) / max_p |xi_p|
     float* slice_max = nullptr;    // per-slice max |w| (fixed-point scaling)
+    float* wscaled = nullptr;      // weights in their slices' fixed point (fused plans)
     // sorted plans: rows of stride sort_L, sources at 0, targets at sort_yoff
     float* keys = nullptr;
     float* keys_out = nullptr;
@@ -526,7 +541,7 @@ void free_plan(fastsum_plan_s* p) {
     for (auto e : p->pool) (void)hipEventDestroy(e);
     void* bufs[] = {p->A, p->A64, p->at, p->xt, p->yt, p->gdt, p->gpt, p->xproj, p->yproj, p->partial, p->grid, p->grid_d,
                     p->grid_w, p->spart, p->tprime, p->mult, p->mult_d, p->tw, p->flag,
-                    p->slice_max, p->ab, p->gpart, p->grid_wd, p->tout, p->keys,
+                    p->slice_max, p->wscaled, p->ab, p->gpart, p->grid_wd, p->tout, p->keys,
                     p->keys_out, p->vals, p->sort_temp, p->sv, p->sty, p->stx, p->norms,
                     p->xit, p->bp_tiles, p->bp_scratch,
                     p->sti, p->styb, p->styo, p->stxb, p->stxo};
@@ -603,8 +618,8 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
     const int nchunk = chunk_plan(pl, Nsrc, spread_chunks(Nsrc, P), false, chunk_len);
     {
         PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
-        FS_TRY(launch_spread(pl->W, src_proj, ld_src, wts, Nsrc, P, pl->geom, nchunk, chunk_len,
-                             pl->slice_max, pl->win_args, pl->partial, st));
+        FS_TRY(launch_spread(pl->Ws, src_proj, ld_src, wts, Nsrc, P, pl->geom, nchunk, chunk_len,
+                             pl->slice_max, pl->swin, pl->partial, st));
     }
     {
         PhaseTimer t(pl, FASTSUM_PHASE_FFTCONV, st);
@@ -617,8 +632,8 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
     pl->last_ngroup = ng;
     {
         PhaseTimer t(pl, FASTSUM_PHASE_GATHER, st);
-        FS_TRY(launch_gather(pl->W, tgt_proj, ld_tgt, Mtgt, P, pl->geom, grid, pg, pl->pstage,
-                             pl->win_args, pl->spart, pl->ldm, nullptr, 0, st));
+        FS_TRY(launch_gather(pl->Wg, tgt_proj, ld_tgt, Mtgt, P, pl->geom, grid, pg, pl->pstage,
+                             pl->gwin, pl->spart, pl->ldm, nullptr, 0, st));
     }
     PhaseTimer t(pl, FASTSUM_PHASE_REDUCE, st);
     FS_TRY(launch_reduce(pl->spart, ng, pl->ldm, Mtgt, 1.0 / P, out, bc, st));
@@ -642,8 +657,8 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, const float* w,
                                   chunk_len);
     {
         PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
-        FS_TRY(launch_spread_fused(pl->W, xt, N, pl->d, pl->at, w, P, pl->geom, pscale, nchunk,
-                                   chunk_len, pl->slice_max, pl->win_args, pl->partial, st));
+        FS_TRY(launch_spread_fused(pl->Ws, xt, N, pl->d, pl->at, w, P, pl->geom, pscale, nchunk,
+                                   chunk_len, pl->slice_max, pl->wscaled, pl->swin, pl->partial, st));
     }
     {
         PhaseTimer t(pl, FASTSUM_PHASE_FFTCONV, st);
@@ -651,14 +666,14 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, const float* w,
                               grid_d ? pl->mult_d : nullptr, grid, grid_d, st));
     }
     const int prange = pl->tune_dir_range > 0 ? pl->tune_dir_range
-                                              : fused_dir_range(M, P, pl->gather_slots, pl->geom.nr, pl->W);
+                                              : fused_dir_range(M, P, pl->gather_slots, pl->geom.nr, pl->Wg);
     const int nrange = (P + prange - 1) / prange;
     pl->last_nchunk = nchunk;
     pl->last_ngroup = nrange;
     {
         PhaseTimer t(pl, FASTSUM_PHASE_GATHER, st);
-        FS_TRY(launch_gather_fused(pl->W, yt, M, pl->d, pl->at, P, pl->geom, pscale, grid,
-                                   prange, pl->win_args, pl->spart, pl->ldm, st));
+        FS_TRY(launch_gather_fused(pl->Wg, yt, M, pl->d, pl->at, P, pl->geom, pscale, grid,
+                                   prange, pl->gwin, pl->spart, pl->ldm, st));
     }
     PhaseTimer t(pl, FASTSUM_PHASE_REDUCE, st);
     FS_TRY(launch_reduce(pl->spart, nrange, pl->ldm, M, 1.0 / P, out, bc, st));
@@ -728,8 +743,9 @@ fastsum_status backproject(fastsum_plan_s* pl, const float* T, int64_t ld, int64
     return check(launch_backproject(T, ld, M, pl->P, pl->d, pl->A, pl->dpad, coef, v, grad, st));
 }
 
-// Sorted plans (energy kernel): project x and y into the rows of the sort,
-// then per direction sort + FP64 prefix sums give
+// Sorted plans (energy kernel): project x and y into the rows of the sort
+// (targets that are the first M sources share the sources' entries: a third
+// fewer keys to sort and scan at M = N / 2), then per direction sort + FP64 prefix sums give
 // -(c_d / tau) sum_n w_n |x~_n - y~_m| = sum_n w_n f(<xi_p, x_n - y_m>)
 // exactly, and the FP64 mean over the directions finishes s.
 fastsum_status sorted_pass(fastsum_plan_s* pl, const float* x, const float* w, int64_t N,
@@ -852,19 +868,26 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
     pl->r = r;
     pl->d = r.p.d;
     pl->P = r.p.P;
-    pl->W = r.p.window_w;
     pl->dpad = (int)round_up(pl->d, 4);
     pl->dpad64 = (int)round_up(pl->d, 64);
     pl->n_max = n_max;
     pl->m_max = m_max;
-    if (!build_window(pl->W, pl->win)) { delete pl; return FASTSUM_EINVAL; }
-    pl->win_args = pack_window(pl->win);
+    if (!resolve_windows(r, (r.p.flags & FASTSUM_FLAG_GRAD) != 0, pl->win)) {
+        delete pl;
+        return FASTSUM_EINVAL;
+    }
+    pl->Ws = pl->win.spread.W;
+    pl->Wg = pl->win.gather.W;
+    pl->Wd = pl->win.deriv.W;
+    pl->swin = pack_window(pl->win.spread);
+    pl->gwin = pack_window(pl->win.gather);
+    pl->dwin = pack_window(pl->win.deriv);
     const double tauR = r.tau * r.p.R;
-    pl->geom = make_geom(r.n, pl->W, tauR);
+    pl->geom = make_geom(pl->win.n, std::max({pl->Ws, pl->Wg, pl->Wd}), tauR);
     pl->bound = (float)(tauR * (1.0 + 1e-5) + 1e-7);
     if (hipGetDevice(&pl->device) != hipSuccess) { delete pl; return FASTSUM_EDEVICE; }
 
-    const int P = pl->P, n = r.n, nr = pl->geom.nr;
+    const int P = pl->P, n = pl->win.n, nr = pl->geom.nr;
     const int64_t cap = std::max(n_max, m_max);
     pl->ld_x = round_up(n_max, 64);
     pl->ld_y = round_up(m_max, 64);
@@ -882,7 +905,7 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
         int ncu = 0, sb = 1, gb = 1;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess || ncu < 1)
             ncu = 1;
-        fused_occupancy(pl->W, pl->d, nr, &sb, &gb);
+        fused_occupancy(pl->Ws, pl->Wg, pl->d, nr, &sb, &gb);
         pl->spread_slots = (int64_t)ncu * sb;
         pl->gather_slots = (int64_t)ncu * gb;
         // the rule never takes more than kFusedMaxChunks (or N / 2^20) chunks
@@ -908,6 +931,9 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
     // Sorted plans keep the projections in their sort rows and have no grids.
     const int64_t gtiles = (P + kFuseDirs - 1) / kFuseDirs;
     const size_t PL = (size_t)P * pl->sort_L;
+    // whole groups of directions: the fused gathers read the last one's
+    // missing rows as zeros
+    const size_t grid_cells = (size_t)gtiles * kFuseDirs * nr;
     bool ok = pl->sorted
         ? dev_alloc(&pl->A, (size_t)P * pl->dpad) && dev_alloc(&pl->keys, PL) &&
               dev_alloc(&pl->keys_out, PL) && dev_alloc(&pl->vals, PL) &&
@@ -916,13 +942,13 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
               dev_alloc(&pl->spart, (size_t)kSortMaxRanges * pl->ldm) &&
               dev_alloc(&pl->flag, 1) && dev_alloc(&pl->norms, kNormUints)
         : dev_alloc(&pl->A, (size_t)P * pl->dpad) && dev_alloc(&pl->norms, kNormUints) &&
-              (pl->fused ? dev_alloc(&pl->xt, (size_t)split_tiles_bytes(n_max, pl->d) / 2) &&
+              (pl->fused ? dev_alloc(&pl->wscaled, (size_t)cap) && dev_alloc(&pl->xt, (size_t)split_tiles_bytes(n_max, pl->d) / 2) &&
                                dev_alloc(&pl->yt, (size_t)split_tiles_bytes(m_max, pl->d) / 2) &&
                                dev_alloc(&pl->at, (size_t)split_tiles_bytes(gtiles * kFuseDirs, pl->d) / 2)
                          : dev_alloc(&pl->xproj, (size_t)P * pl->ld_x) &&
                                dev_alloc(&pl->yproj, (size_t)P * pl->ld_y)) &&
               dev_alloc(&pl->partial, (size_t)pl->nchunk_cap * P * nr) &&
-              dev_alloc(&pl->grid, (size_t)P * nr) &&
+              dev_alloc(&pl->grid, grid_cells) &&
               dev_alloc(&pl->spart, (size_t)pl->ngroup_cap * pl->ldm) &&
               dev_alloc(&pl->mult, (size_t)n) && dev_alloc(&pl->tw, (size_t)n) &&
               dev_alloc(&pl->flag, 1) && dev_alloc(&pl->slice_max, (size_t)((cap + kSliceLen - 1) / kSliceLen));
@@ -941,8 +967,8 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
              dev_alloc(&pl->styb, (size_t)P * pl->ldm) && dev_alloc(&pl->styo, (size_t)P * pl->ldm) &&
              dev_alloc(&pl->stxb, (size_t)P * pl->ldm) && dev_alloc(&pl->stxo, (size_t)P * pl->ldm);
     if (ok && grad && !pl->sorted)
-        ok = dev_alloc(&pl->grid_d, (size_t)P * nr) && dev_alloc(&pl->grid_w, (size_t)P * nr) &&
-             dev_alloc(&pl->grid_wd, (size_t)P * nr) && dev_alloc(&pl->tout, (size_t)cap) &&
+        ok = dev_alloc(&pl->grid_d, grid_cells) && dev_alloc(&pl->grid_w, grid_cells) &&
+             dev_alloc(&pl->grid_wd, grid_cells) && dev_alloc(&pl->tout, (size_t)cap) &&
              dev_alloc(&pl->mult_d, (size_t)n) &&
              (pl->fused ? dev_alloc(&pl->ab, (size_t)gtiles * 4 * DC * 64) &&
                               dev_alloc(&pl->gpart, (size_t)kGradMaxRanges * pl->ldg * 16 * DC)
@@ -962,9 +988,15 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
         return FASTSUM_EDEVICE;
     }
 
+    for (float* gr : {pl->grid, pl->grid_d, pl->grid_w, pl->grid_wd})
+        if (gr && hipMemset(gr + (size_t)P * nr, 0, (grid_cells - (size_t)P * nr) * sizeof(float)) != hipSuccess) {
+            free_plan(pl);
+            return FASTSUM_EDEVICE;
+        }
+
     // tables
     std::vector<float2> mult, mult_d, tw;
-    build_tables(r.p.kernel, pl->d, r.p.scale, r.tau, r.p.n_ft, n, pl->win, mult, mult_d, tw);
+    build_tables(r, pl->win, mult, mult_d, tw);
     std::vector<float> A((size_t)P * pl->dpad, 0.f);
     for (int p = 0; p < P; ++p)
         for (int i = 0; i < pl->d; ++i) A[(size_t)p * pl->dpad + i] = (float)(r.tau * (double)xi[(size_t)i * P + p]);
@@ -1131,9 +1163,9 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         const float pscale = (float)(pl->r.tau * pl->r.p.R);
         if (grad_y) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
-            FS_TRY(launch_grad_fused(pl->W, yt, M, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
+            FS_TRY(launch_grad_fused(pl->Wd, yt, M, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
                                      pl->grid_d, fused_grad_range(M, P, pl->gather_slots),
-                                     pl->win_args, pl->gpart, pl->ldg, coef, grad_s, grad_y, st));
+                                     pl->dwin, pl->gpart, pl->ldg, coef, grad_s, grad_y, st));
         }
         if (grad_w || grad_x) {
             fastsum_status r = fused_sum(pl, yt, grad_s, M, pl->xt, N, uout, pl->grid_w,
@@ -1142,9 +1174,9 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         }
         if (grad_x) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
-            FS_TRY(launch_grad_fused(pl->W, pl->xt, N, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
+            FS_TRY(launch_grad_fused(pl->Wd, pl->xt, N, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
                                      pl->grid_wd, fused_grad_range(N, P, pl->gather_slots),
-                                     pl->win_args, pl->gpart, pl->ldg, coef, pl->last_w, grad_x,
+                                     pl->dwin, pl->gpart, pl->ldg, coef, pl->last_w, grad_x,
                                      st));
         }
         return FASTSUM_OK;
@@ -1156,8 +1188,8 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         const int pg = gather_group(M, P, pl->pstage);
         {
             PhaseTimer t(pl, FASTSUM_PHASE_GATHER, st);
-            FS_TRY(launch_gather(pl->W, yp, ldy, M, P, pl->geom, pl->grid_d, pg, pl->pstage,
-                                 pl->win_args, nullptr, 0, pl->tprime, pl->ld_y, st));
+            FS_TRY(launch_gather(pl->Wd, yp, ldy, M, P, pl->geom, pl->grid_d, pg, pl->pstage,
+                                 pl->dwin, nullptr, 0, pl->tprime, pl->ld_y, st));
         }
         PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
         fastsum_status r = backproject(pl, pl->tprime, pl->ld_y, M, coef, grad_s, grad_y, st);
@@ -1172,8 +1204,8 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         const int pg = gather_group(N, P, pl->pstage);
         {
             PhaseTimer t(pl, FASTSUM_PHASE_GATHER, st);
-            FS_TRY(launch_gather(pl->W, pl->xproj, pl->ld_x, N, P, pl->geom, pl->grid_wd, pg,
-                                 pl->pstage, pl->win_args, nullptr, 0, pl->tprime, pl->ld_x, st));
+            FS_TRY(launch_gather(pl->Wd, pl->xproj, pl->ld_x, N, P, pl->geom, pl->grid_wd, pg,
+                                 pl->pstage, pl->dwin, nullptr, 0, pl->tprime, pl->ld_x, st));
         }
         PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
         fastsum_status r = backproject(pl, pl->tprime, pl->ld_x, N, coef, pl->last_w, grad_x, st);
@@ -1200,10 +1232,10 @@ fastsum_status fastsum_check(fastsum_plan pl) {
 fastsum_status fastsum_get_info(fastsum_plan pl, fastsum_plan_info* info) {
     if (!pl || !info) return FASTSUM_EINVAL;
     info->tau = pl->r.tau;
-    info->beta = pl->win.beta;
-    info->n_grid = pl->r.n;
-    info->window_w = pl->W;
-    info->poly_degree = pl->win.D;
+    info->beta = pl->win.spread.beta;
+    info->n_grid = pl->win.n;
+    info->window_w = pl->Ws;
+    info->poly_degree = pl->win.spread.D;
     info->n_ft = pl->r.p.n_ft;
     info->n_max = pl->n_max;
     info->m_max = pl->m_max;

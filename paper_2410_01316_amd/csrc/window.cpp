@@ -1,0 +1,323 @@
+// Windows fitted to the spectrum of a plan's one-dimensional kernel.
+//
+// A window with transform phihat turns mode k of a grid of n cells into
+//   e^{2 pi i k t} (1 + sum_{m != 0} rho_m(k) e^{2 pi i m n t}),
+//   rho_m(k) = phihat(k + m n) / phihat(k),
+// once the multipliers have undone phihat(k); the rho are its aliases.  The
+// general window (exponential of semicircle, 4 taps, 6 for Laplace) keeps
+// them near 1e-5 up to |k| = n / 4.  The kernels' own spectra are nothing
+// like flat: Gauss keeps some twenty modes whatever N_ft is, the Matern and
+// Laplace coefficients fall like a power of k.  On such a band a piecewise
+// polynomial with fewer taps does as well, and the spread and the gather pay
+// for fewer taps and, where the band is narrow, fewer cells.
+//
+// Two fits of a symmetric window of W taps and degree D, both a linear
+// least-squares problem in its coefficients:
+//   free grid   minimises sum_k c_k^2 sum_m rho_m(k)^2 on the smallest grid
+//               that will do,
+//   same grid   minimises sum_k c_k^2 sum_m (rho_m(k) - general rho_m(k))^2,
+//               so that results move little from the general window's.
+// A window's error is random from direction to direction, so it reaches the
+// mean over P directions as sqrt(2 / P) of itself (spread and gather).  A fit
+// is taken only where it moves that mean by less than kDrift: results are
+// then the general window's to FP32 working accuracy, also for sums that
+// cancel tenfold.
+#include "host_common.h"
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+namespace fastsum {
+namespace host {
+
+namespace {
+
+constexpr int kAliases = 3;        // m = +-1 .. +-3
+constexpr int kMaxDegree = 7;
+constexpr int kMaxFree = 16;       // free coefficients of a symmetric window
+// a mode below this share of the largest coefficient is left out of the
+// error model, and of grids too coarse to hold it: below FP32 rounding
+constexpr double kNegligible = 1e-9;
+
+// m[p] = integral over [-1/2, 1/2] of s^p cos(w s) (p even) or s^p sin(w s)
+// (p odd), p <= D
+void cell_moments(double w, int D, double* m) {
+    if (std::fabs(w) < 3.0) {
+        for (int p = 0; p <= D; ++p) {
+            // term j: (-1)^j w^e / e! * (1/2)^(p + e) / (p + e + 1), e = 2j (+ 1)
+            double acc = 0.0, f = (p % 2) ? w : 1.0, h = std::ldexp(1.0, -p - (p % 2));
+            for (int j = 0, e = p % 2; j < 16; ++j, e += 2) {
+                acc += f * h / (p + e + 1);
+                f *= -w * w / ((e + 1.0) * (e + 2.0));
+                h *= 0.25;
+            }
+            m[p] = acc;
+        }
+        return;
+    }
+    const double s = std::sin(0.5 * w), c = std::cos(0.5 * w);
+    m[0] = 2.0 * s / w;
+    double h = 1.0;
+    for (int p = 1; p <= D; ++p) {
+        h *= 0.5;
+        m[p] = (p % 2) ? (-2.0 * h * c + p * m[p - 1]) / w : (2.0 * h * s - p * m[p - 1]) / w;
+    }
+}
+
+// Transforms of the free coefficients of a symmetric window of W taps and
+// degree D at angular frequency w per cell: pair t (taps t and W-1-t, all
+// powers) and for odd W the centre tap (even powers).  Returns their number.
+int basis(int W, int D, double w, double* out) {
+    double m[kMaxDegree + 1];
+    cell_moments(w, D, m);
+    int q = 0;
+    for (int t = 0; t < (W + 1) / 2; ++t) {
+        const double a = t + 0.5 - 0.5 * W;
+        const bool centre = (W % 2) && t == W / 2;
+        const double ca = std::cos(w * a), sa = std::sin(w * a);
+        for (int p = 0; p <= D; p += centre ? 2 : 1)
+            out[q++] = (centre ? 1.0 : 2.0) * ((p % 2) ? sa : ca) * m[p];
+    }
+    return q;
+}
+
+// eigenvalues (diagonal of A) and eigenvectors (columns of V) of a symmetric
+// matrix by cyclic Jacobi rotations
+void jacobi(std::vector<double>& A, std::vector<double>& V, int n) {
+    V.assign(n * n, 0.0);
+    for (int i = 0; i < n; ++i) V[i * n + i] = 1.0;
+    for (int sweep = 0; sweep < 40; ++sweep) {
+        double off = 0.0, dia = 0.0;
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j) (i == j ? dia : off) += A[i * n + j] * A[i * n + j];
+        if (off <= 1e-34 * dia) break;
+        for (int p = 0; p < n; ++p)
+            for (int q = p + 1; q < n; ++q) {
+                const double apq = A[p * n + q];
+                if (apq == 0.0) continue;
+                const double th = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
+                const double t = (th >= 0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
+                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+                for (int k = 0; k < n; ++k) {
+                    const double x = A[k * n + p], y = A[k * n + q];
+                    A[k * n + p] = c * x - s * y;
+                    A[k * n + q] = s * x + c * y;
+                }
+                for (int k = 0; k < n; ++k) {
+                    const double x = A[p * n + k], y = A[q * n + k];
+                    A[p * n + k] = c * x - s * y;
+                    A[q * n + k] = s * x + c * y;
+                }
+                for (int k = 0; k < n; ++k) {
+                    const double x = V[k * n + p], y = V[k * n + q];
+                    V[k * n + p] = c * x - s * y;
+                    V[k * n + q] = s * x + c * y;
+                }
+            }
+    }
+}
+
+// Transforms of the free coefficients at every mode k = 0 .. K of a grid of
+// n cells (row 0) and at its aliases k + m n (rows 1 .. 2 kAliases).
+struct Basis {
+    int W, D, n, K, nf = 0;        // K: highest mode
+    std::vector<double> v;         // (2 kAliases + 1) x (K + 1) x kMaxFree
+    Basis(int W_, int D_, int n_, int K_) : W(W_), D(D_), n(n_), K(K_) {
+        v.resize((size_t)(2 * kAliases + 1) * (K + 1) * kMaxFree);
+        for (int r = 0; r <= 2 * kAliases; ++r)
+            for (int k = 0; k <= K; ++k) {
+                const int m = r == 0 ? 0 : (r + 1) / 2 * (r % 2 ? 1 : -1);
+                nf = basis(W, D, 2.0 * kPi * ((double)k / n + m), at(r, k));
+            }
+    }
+    double* at(int r, int k) { return &v[((size_t)r * (K + 1) + k) * kMaxFree]; }
+    double dot(int r, int k, const double* x) {
+        const double* b = at(r, k);
+        double a = 0.0;
+        for (int i = 0; i < nf; ++i) a += b[i] * x[i];
+        return a;
+    }
+};
+
+using Aliases = std::vector<double>;   // rho, 2 kAliases per mode (order of the basis rows)
+
+// free coefficients minimising sum_k wt_k sum_m (rho_m(k) - target)^2; false
+// if the fit fails
+bool fit(Basis& B, const std::vector<double>& wt, const Aliases& target, double* x) {
+    const int nf = B.nf, K = B.K;
+    std::vector<double> ph(K + 1, 1.0), A(nf * nf), V, b(nf), sc(nf);
+    for (int it = 0; it < 4; ++it) {      // rho is relative to the window's own phihat(k)
+        std::fill(A.begin(), A.end(), 0.0);
+        std::fill(b.begin(), b.end(), 0.0);
+        double tot = 0.0;
+        for (int k = 0; k <= K; ++k) {
+            const double w = wt[k] / (ph[k] * ph[k]);
+            if (!(w > 0.0)) continue;
+            tot += w;
+            const double* b0 = B.at(0, k);
+            for (int i = 0; i < nf; ++i) b[i] += w * b0[i];
+            for (int r = 1; r <= 2 * kAliases; ++r) {
+                const double* br = B.at(r, k);
+                const double rho = target[2 * kAliases * k + r - 1];
+                double v[kMaxFree];
+                for (int i = 0; i < nf; ++i) v[i] = br[i] - rho * b0[i];
+                for (int i = 0; i < nf; ++i)
+                    for (int j = 0; j <= i; ++j) A[i * nf + j] += w * v[i] * v[j];
+            }
+        }
+        if (!(tot > 0.0)) return false;
+        for (int i = 0; i < nf; ++i) sc[i] = std::sqrt(std::max(A[i * nf + i], 1e-300));
+        for (int i = 0; i < nf; ++i)
+            for (int j = 0; j <= i; ++j)
+                A[i * nf + j] = A[j * nf + i] = A[i * nf + j] / (sc[i] * sc[j]);
+        jacobi(A, V, nf);
+        double top = 0.0;
+        for (int i = 0; i < nf; ++i) top = std::max(top, A[i * nf + i]);
+        std::fill(x, x + nf, 0.0);
+        for (int e = 0; e < nf; ++e) {
+            double c = 0.0;
+            for (int i = 0; i < nf; ++i) c += V[i * nf + e] * b[i] / sc[i];
+            c /= std::max(A[e * nf + e], 1e-18 * top);
+            for (int i = 0; i < nf; ++i) x[i] += c * V[i * nf + e] / sc[i];
+        }
+        double s = 0.0;
+        for (int i = 0; i < nf; ++i) s += b[i] * x[i];
+        if (!(std::fabs(s) > 0.0) || !std::isfinite(s)) return false;
+        for (int i = 0; i < nf; ++i) x[i] *= tot / s;
+        for (int k = 0; k <= K; ++k) {
+            ph[k] = B.dot(0, k, x);
+            if (wt[k] > 0.0 && !(ph[k] > 1e-3)) return false;
+        }
+    }
+    return true;
+}
+
+// the window of free coefficients x, scaled to a largest tap of 1
+WindowPoly window_of(const Basis& B, const double* x) {
+    WindowPoly w;
+    w.W = B.W;
+    w.D = B.D;
+    const int nc = w.D + 1;
+    w.coef.assign(w.W * nc, 0.0);
+    int q = 0;
+    for (int t = 0; t < (w.W + 1) / 2; ++t) {
+        const bool centre = (w.W % 2) && t == w.W / 2;
+        for (int p = 0; p <= w.D; p += centre ? 2 : 1) {
+            w.coef[t * nc + p] = x[q];
+            if (!centre) w.coef[(w.W - 1 - t) * nc + p] = (p % 2) ? -x[q] : x[q];
+            ++q;
+        }
+    }
+    double mx = 0.0;
+    for (int t = 0; t < w.W; ++t)
+        for (int i = 0; i <= 64; ++i) mx = std::max(mx, std::fabs(w.eval(t, i / 64.0 - 0.5)));
+    for (double& c : w.coef) c /= mx;
+    return w;
+}
+
+// aliases of a window at modes 0 .. K
+Aliases aliases(const WindowPoly& w, int n, int K) {
+    Aliases a(2 * kAliases * (K + 1));
+    for (int k = 0; k <= K; ++k) {
+        const double p0 = window_transform_at(w, 2.0 * kPi * k / n);
+        for (int r = 1; r <= 2 * kAliases; ++r) {
+            const int m = (r + 1) / 2 * (r % 2 ? 1 : -1);
+            a[2 * kAliases * k + r - 1] = window_transform_at(w, 2.0 * kPi * ((double)k / n + m)) / p0;
+        }
+    }
+    return a;
+}
+
+// root of sum_k (c_k k^deriv)^2 sum_m (a - b)^2, relative to the coefficients
+double distance(const Aliases& a, const Aliases& b, const std::vector<double>& c, int deriv) {
+    double num = 0.0, den = 0.0;
+    for (size_t k = 1; k < c.size(); ++k) {
+        const double v = c[k] * (deriv ? (double)k : 1.0);
+        double s = 0.0;
+        for (int r = 0; r < 2 * kAliases; ++r) {
+            const double d = a[2 * kAliases * k + r] - b[2 * kAliases * k + r];
+            s += d * d;
+        }
+        num += v * v * s;
+        den += v * v;
+    }
+    return den > 0.0 ? std::sqrt(num / den) : 0.0;
+}
+
+// Largest accepted change of the mean over the directions against the
+// general window, relative to the coefficients.  The weights k c_k of the
+// derivative also stand for sources whose low modes cancel; plans without
+// gradients allow them ten times as much.
+constexpr double kDrift = 5e-7;
+
+constexpr int degree_of(int W) { return W == 3 ? 3 : 4; }
+
+}  // namespace
+
+double window_transform_at(const WindowPoly& w, double om) {
+    double m[kMaxDegree + 1];
+    cell_moments(om, w.D, m);
+    double acc = 0.0;
+    for (int t = 0; t < w.W; ++t) {
+        const double a = t + 0.5 - 0.5 * w.W;
+        const double ca = std::cos(om * a), sa = std::sin(om * a);
+        for (int p = 0; p <= w.D; ++p)
+            acc += w.coef[t * (w.D + 1) + p] * ((p % 2) ? sa : ca) * m[p];
+    }
+    return acc;
+}
+
+bool window_plan(const Resolved& r, bool grad, WindowPlan& out) {
+    // Energy sums are taken of sets whose weights cancel about a common
+    // centre: the modes that decide them are not the ones c_k names (at
+    // d = 784 a fit that is 25 times better by its coefficients moved the sum
+    // by 7e-5).
+    if (r.p.kernel == FASTSUM_ENERGY) return false;
+    const WindowPoly general = out.spread;
+    const int K = r.p.n_ft / 2;
+    std::vector<double> c;
+    fourier_coefficients(r.p.kernel, r.p.d, r.p.scale, r.tau, r.p.n_ft, c);
+    c[K] *= 0.5;
+    double top = 0.0;
+    for (double v : c) top = std::max(top, std::fabs(v));
+    if (!(top > 0.0) || !std::isfinite(top)) return false;
+    int ke = K;
+    while (ke > 1 && std::fabs(c[ke]) <= kNegligible * top) --ke;
+    c.resize(ke + 1);
+    std::vector<double> w0(ke + 1), w1(ke + 1);
+    for (int k = 0; k <= ke; ++k) {
+        w0[k] = c[k] * c[k];
+        w1[k] = w0[k] * k * k;
+    }
+    const Aliases zero(2 * kAliases * (ke + 1), 0.0), same = aliases(general, r.n, ke);
+    const double tauR = r.tau * r.p.R;
+    const double tol0 = kDrift / std::sqrt(2.0 / r.p.P), tol1 = (grad ? 1.0 : 10.0) * tol0;
+
+    // a window of W taps on n cells whose aliases are within t0 (t1 with the
+    // derivative's weights) of `target`
+    auto attempt = [&](int W, int n, const Aliases& target, double t0, double t1) {
+        if (n <= 2 * ke || !(tauR <= 0.5 - (W / 2 + 3.0) / n)) return false;
+        Basis B(W, degree_of(W), n, ke);
+        double x[kMaxFree];
+        if (!fit(B, grad ? w1 : w0, target, x)) return false;
+        WindowPlan p;
+        p.n = n;
+        p.spread = p.gather = p.deriv = window_of(B, x);
+        const Aliases a = aliases(p.spread, n, ke);
+        if (distance(a, target, c, 0) > t0 || distance(a, target, c, 1) > t1) return false;
+        out = p;
+        return true;
+    };
+    const double g0 = distance(same, zero, c, 0), g1 = distance(same, zero, c, 1);
+    if (g0 <= tol0 && g1 <= tol1)
+        for (int W = 3; W < general.W; ++W)
+            for (int n = 64; n <= 2048; n *= 2)
+                if (attempt(W, n, zero, 0.5 * g0, 0.5 * g1)) return true;
+    for (int W = 3; W < general.W; ++W)
+        if (attempt(W, r.n, same, tol0, tol1)) return true;
+    return false;
+}
+
+}  // namespace host
+}  // namespace fastsum
