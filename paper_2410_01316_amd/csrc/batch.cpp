@@ -206,8 +206,8 @@ fastsum_status build_tasks(fastsum_batch_s* b, const fastsum_problem_io* io) {
         d.N = q.N;
         d.M = q.M;
         d.same_xy = (q.x == q.y) ? 1 : 0;
+        d.wscaled = reinterpret_cast<float*>(b->arena + pp.off_wscaled);
         if (b->fused) {
-            d.wscaled = reinterpret_cast<float*>(b->arena + pp.off_wscaled);
             d.at = reinterpret_cast<const uint16_t*>(b->arena + pp.off_A);
             d.xt = reinterpret_cast<uint16_t*>(b->arena + pp.off_xproj);
             d.yt = reinterpret_cast<uint16_t*>(b->arena + pp.off_yproj);
@@ -442,8 +442,9 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
         pp.nchunk_cap = nc;
         pp.ngroup_cap = ng;
         const int nr = pp.geom.nr, n = pp.win.n;
+        pp.off_wscaled = off;
+        off = align256(off + sizeof(float) * (size_t)round_up(pp.n_max, kSliceLen));
         if (b->fused) {
-            pp.off_wscaled = off; off = align256(off + sizeof(float) * (size_t)pp.n_max);
             pp.off_A = off; off = align256(off + Ats[i].size() * sizeof(uint16_t));
             pp.off_xproj = off; off = align256(off + (size_t)split_tiles_bytes(pp.n_max, pp.r.p.d));
             pp.off_yproj = off; off = align256(off + (size_t)split_tiles_bytes(pp.m_max, pp.r.p.d));

@@ -126,12 +126,13 @@ hipError_t launch_project_tiles(const float* X, int64_t N, int d, bool bf16, con
 // partial[(c*P + p)*nr + j - lo] = sum over sources i of chunk c of
 //   w[i] * window(cell j - u(proj[p*ld + i]))
 // chunk_len must be a multiple of kSliceLen; slice_max is scratch for
-// ceil(N / kSliceLen) floats.
+// ceil(N / kSliceLen) floats, wscaled for round_up(N, kSliceLen) (the weights
+// in their slices' fixed point).
 constexpr int kSliceLen = 4096;
 hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
                          int64_t N, int P, GridGeom g, int nchunk,
-                         int64_t chunk_len, float* slice_max, const WindowArgs& win,
-                         float* partial, hipStream_t stream);
+                         int64_t chunk_len, float* slice_max, float* wscaled,
+                         const WindowArgs& win, float* partial, hipStream_t stream);
 
 // Per pair of directions: sum the chunk partials, complex FFT of size n,
 // multiply by mult (and separately by mult_d when grid_d != nullptr),
@@ -200,8 +201,8 @@ hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, ui
 
 // As launch_spread, with the projections computed in the kernel from the
 // split tiles of the sources (Xt, scale 1/R) and of the directions (At):
-// x~ = pscale * <xi, x / R>, pscale = tau R.  wscaled: scratch for N floats
-// (the weights in their slices' fixed point).
+// x~ = pscale * <xi, x / R>, pscale = tau R.  slice_max and wscaled as in
+// launch_spread.
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
                                const float* w, int P, GridGeom g, float pscale, int nchunk,
                                int64_t chunk_len, float* slice_max, float* wscaled,
@@ -298,7 +299,7 @@ struct BatchProblem {
     float* grid;           // P x nr
     double* spart;         // ngroup x ldm
     float* slice_max;      // ceil(N / kSliceLen)
-    float* wscaled;        // N weights in their slices' fixed point (fused; else nullptr)
+    float* wscaled;        // round_up(N, kSliceLen) weights in their slices' fixed point
     const float2* mult;    // n coefficient multipliers
     const float2* tw;      // n twiddles
     int64_t ldx, ldy, ldm;

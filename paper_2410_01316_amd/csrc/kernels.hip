@@ -423,8 +423,8 @@ __device__ __forceinline__ int slice_exponent(float mx) {
     return ok ? 18 - e : 0;
 }
 
-// slice_max[s] = max |w_i| over the sources i of slice s, and (wscaled, if
-// given) their weights in the slice's fixed point, w_i 2^k
+// slice_max[s] = max |w_i| over the sources i of slice s, and the weights in
+// the slice's fixed point, wscaled_i = w_i 2^k (zero from N to the slice's end)
 __device__ __forceinline__ void slice_max_tile(float* red, const float* __restrict__ w,
                                                int64_t N, int s, float* __restrict__ slice_max,
                                                float* __restrict__ wscaled) {
@@ -446,14 +446,10 @@ __device__ __forceinline__ void slice_max_tile(float* red, const float* __restri
         __syncthreads();
     }
     if (threadIdx.x == 0) slice_max[s] = red[0];
-    if (wscaled != nullptr) {
-        const float scale = ldexpf(1.f, slice_exponent(red[0]));
+    const float scale = ldexpf(1.f, slice_exponent(red[0]));
 #pragma unroll
-        for (int q = 0; q < kSlice / kBlock; ++q) {
-            const int64_t i = i0 + threadIdx.x + (int64_t)q * kBlock;
-            if (i < N) wscaled[i] = v[q] * scale;
-        }
-    }
+    for (int q = 0; q < kSlice / kBlock; ++q)
+        wscaled[i0 + threadIdx.x + (int64_t)q * kBlock] = v[q] * scale;
 }
 
 __global__ __launch_bounds__(kBlock) void slice_max_kernel(
@@ -468,23 +464,33 @@ __global__ __launch_bounds__(kBlock) void slice_max_kernel(
 // a few fraction bits at the top of the fixed-point range, so exact halves
 // are common and rounding them up would add a bias that grows with the
 // number of sources.
-template <int W>
+// Cell j of the grid lies at lds32[base + (j << LOGR)].
+template <int W, int LOGR = 0>
 __device__ __forceinline__ void spread_point(float xt, float ws, const WinEval<W>& ev,
                                              const WindowArgs& win, int* lds32, int base) {
     float sp;
-    int* __restrict__ c = lds32 + (base + tap0<W>(xt, ev, sp));
+    int* __restrict__ c = lds32 + (base + (tap0<W>(xt, ev, sp) << LOGR));
     const float q = sp * sp, spw = sp * ws;
 #pragma unroll
     for (int t = 0; t < W / 2; ++t) {
         float e, o;
         window_pair<W>(q, t, win, ev, e, o);
         e *= ws;
-        atomicAdd(c + t, __float2int_rn(fmaf(o, spw, e)));
-        atomicAdd(c + W - 1 - t, __float2int_rn(fmaf(-o, spw, e)));
+        atomicAdd(c + (t << LOGR), __float2int_rn(fmaf(o, spw, e)));
+        atomicAdd(c + ((W - 1 - t) << LOGR), __float2int_rn(fmaf(-o, spw, e)));
     }
     if constexpr (W % 2)
-        atomicAdd(c + W / 2, __float2int_rn(window_even<W>(q, W / 2, win, ev) * ws));
+        atomicAdd(c + ((W / 2) << LOGR), __float2int_rn(window_even<W>(q, W / 2, win, ev) * ws));
 }
+
+// Spread of stored projections: each cell is kept in 2^kSpreadLogR copies,
+// lane l adding to copy l mod 2^kSpreadLogR, and the copies are added as
+// integers when the slice is flushed (exact in any order).  All 64 lanes of
+// a wave work on one direction's grid, and image-like points project onto a
+// few tens of cells: with one copy the atomics of a wave queue on the same
+// addresses (a spread of +-20 cells ran at 773 cycles per 256 pairs against
+// 515 for +-100; the window arithmetic alone takes 354).
+constexpr int kSpreadLogR = 2;
 
 template <int W>
 __device__ __forceinline__ void spread_tile(
@@ -492,45 +498,51 @@ __device__ __forceinline__ void spread_tile(
     const float* __restrict__ w, int64_t N, int P, const GridGeom& g, int64_t chunk_len,
     const float* __restrict__ slice_max, const WindowArgs& win, float* __restrict__ partial,
     int p, int c) {
-    int* lds32 = reinterpret_cast<int*>(lds_raw);             // nr ints
+    static_assert(kSpreadLogR == 2, "a flush reads a cell's copies as one int4");
+    int* lds32 = reinterpret_cast<int*>(lds_raw);             // nr cells x 4 copies
+    int4* cells4 = reinterpret_cast<int4*>(lds_raw);
     const WinEval<W> ev(g, win);
+    const int base = (int)(threadIdx.x & 3) - 4 * ev.off;
     float acc[kSpreadAcc];
 #pragma unroll
     for (int q = 0; q < kSpreadAcc; ++q) acc[q] = 0.f;
-    __syncthreads();               // LDS may still be read by a previous tile
-    for (int j = threadIdx.x; j < g.nr; j += kBlock) lds32[j] = 0;
-    __syncthreads();
     const int64_t i0 = (int64_t)c * chunk_len;          // multiple of kSlice
     const int64_t i1 = min(N, i0 + chunk_len);
     const float* __restrict__ row = proj + (int64_t)p * ld;
-    for (int64_t s0 = i0; s0 < i1; s0 += kSlice) {
-        const int k = slice_exponent(slice_max[s0 / kSlice]);
-        const float scale = ldexpf(1.f, k);
-        // issue all loads of the slice first; rows are padded to 64 floats
-        float4 xv[kSliceSteps];
-        float wv[kSliceSteps][4];
+    // a slice's projections and weights, loaded while the slice before is
+    // spread; rows are padded to 64 floats, weights to whole slices
+    float4 xv[kSliceSteps], wv[kSliceSteps];
+    auto load = [&](int64_t s0) {
 #pragma unroll
         for (int q = 0; q < kSliceSteps; ++q) {
             const int64_t i = s0 + 4 * threadIdx.x + (int64_t)q * 4 * kBlock;
-            xv[q] = (i < i1) ? *reinterpret_cast<const float4*>(row + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) wv[q][r] = (i + r < i1) ? w[i + r] : 0.f;
+            const bool in = i < i1;
+            xv[q] = in ? *reinterpret_cast<const float4*>(row + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+            wv[q] = in ? *reinterpret_cast<const float4*>(w + i) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
+    };
+    load(i0);
+    __syncthreads();               // LDS may still be read by a previous tile
+    for (int j = threadIdx.x; j < g.nr; j += kBlock) cells4[j] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    for (int64_t s0 = i0; s0 < i1; s0 += kSlice) {
 #pragma unroll
         for (int q = 0; q < kSliceSteps; ++q) {
-            spread_point<W>(xv[q].x, wv[q][0] * scale, ev, win, lds32, -ev.off);
-            spread_point<W>(xv[q].y, wv[q][1] * scale, ev, win, lds32, -ev.off);
-            spread_point<W>(xv[q].z, wv[q][2] * scale, ev, win, lds32, -ev.off);
-            spread_point<W>(xv[q].w, wv[q][3] * scale, ev, win, lds32, -ev.off);
+            spread_point<W, kSpreadLogR>(xv[q].x, wv[q].x, ev, win, lds32, base);
+            spread_point<W, kSpreadLogR>(xv[q].y, wv[q].y, ev, win, lds32, base);
+            spread_point<W, kSpreadLogR>(xv[q].z, wv[q].z, ev, win, lds32, base);
+            spread_point<W, kSpreadLogR>(xv[q].w, wv[q].w, ev, win, lds32, base);
         }
+        const float unscale = ldexpf(1.f, -slice_exponent(slice_max[s0 / kSlice]));
+        if (s0 + kSlice < i1) load(s0 + kSlice);
         __syncthreads();
-        const float unscale = ldexpf(1.f, -k);
 #pragma unroll
         for (int q = 0; q < kSpreadAcc; ++q) {
             const int j = threadIdx.x + q * kBlock;
             if (j < g.nr) {
-                acc[q] = fmaf((float)lds32[j], unscale, acc[q]);
-                lds32[j] = 0;
+                const int4 v = cells4[j];
+                acc[q] = fmaf((float)(v.x + v.y + v.z + v.w), unscale, acc[q]);
+                cells4[j] = make_int4(0, 0, 0, 0);
             }
         }
         __syncthreads();
@@ -555,18 +567,18 @@ __global__ __launch_bounds__(kBlock) void spread_kernel(
 
 hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
                          int64_t N, int P, GridGeom g, int nchunk,
-                         int64_t chunk_len, float* slice_max, const WindowArgs& win,
-                         float* partial, hipStream_t stream) {
+                         int64_t chunk_len, float* slice_max, float* wscaled,
+                         const WindowArgs& win, float* partial, hipStream_t stream) {
     hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max, nullptr);
+                       0, stream, w, N, slice_max, wscaled);
     dim3 grid((unsigned)P, (unsigned)nchunk);
     const size_t lds = stored_spread_lds(g.nr);
     switch (W) {
-        case 3: hipLaunchKernelGGL(spread_kernel<3>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
-        case 4: hipLaunchKernelGGL(spread_kernel<4>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
-        case 5: hipLaunchKernelGGL(spread_kernel<5>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
-        case 6: hipLaunchKernelGGL(spread_kernel<6>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
-        case 8: hipLaunchKernelGGL(spread_kernel<8>, grid, dim3(kBlock), lds, stream, proj, ld, w, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 3: hipLaunchKernelGGL(spread_kernel<3>, grid, dim3(kBlock), lds, stream, proj, ld, wscaled, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 4: hipLaunchKernelGGL(spread_kernel<4>, grid, dim3(kBlock), lds, stream, proj, ld, wscaled, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 5: hipLaunchKernelGGL(spread_kernel<5>, grid, dim3(kBlock), lds, stream, proj, ld, wscaled, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 6: hipLaunchKernelGGL(spread_kernel<6>, grid, dim3(kBlock), lds, stream, proj, ld, wscaled, N, P, g, chunk_len, slice_max, win, partial); break;
+        case 8: hipLaunchKernelGGL(spread_kernel<8>, grid, dim3(kBlock), lds, stream, proj, ld, wscaled, N, P, g, chunk_len, slice_max, win, partial); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -803,18 +815,43 @@ hipError_t launch_fftconv(const float* partial, int nchunk, int P, GridGeom g,
 
 constexpr int kGatherTPT = 4;   // consecutive targets per thread (one float4)
 
+// Cells around two points of a thread and the offsets in them: the LDS reads
+// (issue) apart from the interpolation (value), so that the reads of the next
+// two points return while these are interpolated.
 template <int W>
-__device__ __forceinline__ float interp(float xt, const float* gl, int base, const WinEval<W>& ev,
-                                        const WindowArgs& win) {
-    float sp;
-    const float* __restrict__ c = gl + (base + tap0<W>(xt, ev, sp));
-    float wt[W];
-    window_weights<W>(sp, win, ev, wt);
-    float t = 0.f;
+struct TapRead {
+    float sp[2];
+    float c[2][W];
+    // points at projections x0, x1; their grids start at lds[base0 + ev.off],
+    // lds[base1 + ev.off]
+    __device__ __forceinline__ void issue(float x0, float x1, const float* lds, int base0, int base1,
+                                          const WinEval<W>& ev) {
 #pragma unroll
-    for (int k = 0; k < W; ++k) t = fmaf(c[k], wt[k], t);
-    return t;
-}
+        for (int i = 0; i < 2; ++i) {
+            const float* __restrict__ p =
+                lds + ((i ? base1 : base0) + tap0<W>(i ? x1 : x0, ev, sp[i]));
+#pragma unroll
+            for (int k = 0; k < W; ++k) c[i][k] = p[k];
+        }
+    }
+    __device__ __forceinline__ float value(int i, const WinEval<W>& ev,
+                                           const WindowArgs& win) const {
+        float wt[W];
+        window_weights<W>(sp[i], win, ev, wt);
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < W; ++k) t = fmaf(c[i][k], wt[k], t);
+        return t;
+    }
+};
+
+// LDS reads written before stay before it.
+__device__ __forceinline__ void reads_ahead() { asm volatile("" ::: "memory"); }
+// Forms a result before any later LDS read is issued (left alone, the
+// compiler moves all arithmetic behind all reads and spills).
+__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)::"memory"); }
+
+constexpr int kGatherStageMax = 8;   // grids staged at once, at most
 
 template <int W, bool WRITE_T>
 __device__ __forceinline__ void gather_tile(
@@ -829,6 +866,18 @@ __device__ __forceinline__ void gather_tile(
     const int p_end = min(P, p_begin + pg);
     const WinEval<W> ev(g, win);
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    // the projections of a stage's directions, loaded a stage ahead: a load
+    // per direction just before its use waited out the memory's latency.
+    // Rows are padded to a multiple of 64 floats: the float4 at m is in bounds.
+    float4 xv[kGatherStageMax];
+    auto load = [&](int ps) {
+#pragma unroll
+        for (int pp = 0; pp < kGatherStageMax; ++pp)
+            if (pp < pstage && ps + pp < p_end)          // uniform
+                xv[pp] = active ? *reinterpret_cast<const float4*>(proj + (int64_t)(ps + pp) * ld + m)
+                                : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    load(p_begin);
     for (int ps = p_begin; ps < p_end; ps += pstage) {
         const int np = min(pstage, p_end - ps);
         __syncthreads();
@@ -847,29 +896,42 @@ __device__ __forceinline__ void gather_tile(
             }
             for (; j < n4; j += kBlock) dst4[j] = src4[j];
         }
+        float4 cur[kGatherStageMax];
+#pragma unroll
+        for (int pp = 0; pp < kGatherStageMax; ++pp) cur[pp] = xv[pp];
+        if (ps + pstage < p_end) load(ps + pstage);
         __syncthreads();
-        if (active) {
-            // rows are padded to a multiple of 64 floats: the float4 at m is in bounds
-            const float* __restrict__ rowp = proj + (int64_t)ps * ld + m;
-            float4 cur = *reinterpret_cast<const float4*>(rowp);
-            for (int pp = 0; pp < np; ++pp) {
-                float4 nxt = cur;
-                if (pp + 1 < np) nxt = *reinterpret_cast<const float4*>(rowp + (int64_t)(pp + 1) * ld);
-                const int base = pp * g.nr - ev.off;
-                const float t0 = interp<W>(cur.x, lds, base, ev, win);
-                const float t1 = interp<W>(cur.y, lds, base, ev, win);
-                const float t2 = interp<W>(cur.z, lds, base, ev, win);
-                const float t3 = interp<W>(cur.w, lds, base, ev, win);
-                if (WRITE_T) {
+        // two points at a time, their reads one step ahead
+        TapRead<W> lo, hi;
+        int base = -ev.off;
+        lo.issue(cur[0].x, cur[0].y, lds, base, base, ev);
+#pragma unroll
+        for (int pp = 0; pp < kGatherStageMax; ++pp) {
+            if (pp >= np) break;
+            hi.issue(cur[pp].z, cur[pp].w, lds, base, base, ev);
+            reads_ahead();
+            float t0 = lo.value(0, ev, win), t1 = lo.value(1, ev, win);
+            pin(t0);
+            pin(t1);
+            base += g.nr;
+            // past the last direction: read again, unused, in bounds
+            const int nx = pp + 1 < kGatherStageMax ? pp + 1 : pp;
+            const bool more = pp + 1 < np;
+            lo.issue(more ? cur[nx].x : cur[pp].x, more ? cur[nx].y : cur[pp].y, lds,
+                     more ? base : -ev.off, more ? base : -ev.off, ev);
+            reads_ahead();
+            float t2 = hi.value(0, ev, win), t3 = hi.value(1, ev, win);
+            pin(t2);
+            pin(t3);
+            if (WRITE_T) {
+                if (active)
                     *reinterpret_cast<float4*>(tout + (int64_t)(ps + pp) * ld_t + m) =
                         make_float4(t0, t1, t2, t3);
-                } else {
-                    a0 += (double)t0;
-                    a1 += (double)t1;
-                    a2 += (double)t2;
-                    a3 += (double)t3;
-                }
-                cur = nxt;
+            } else {
+                a0 += (double)t0;
+                a1 += (double)t1;
+                a2 += (double)t2;
+                a3 += (double)t3;
             }
         }
     }
@@ -1337,38 +1399,6 @@ __device__ __forceinline__ void gather_stage(const float* __restrict__ grid, int
                                                  lane * 16, piece * kDmaBytes, 0, 0);
 }
 
-// Half a batch (16 targets on one group of 16 directions): the cells around
-// two of the lane's four (target, direction) pairs and the offsets in them.
-template <int W>
-struct TapRead {
-    float sp[2];
-    float c[2][W];
-    // issues the LDS reads of pairs i0, i0 + 1 at projections pr (base[i]:
-    // the grid of the lane's direction i in lds, less ev.off)
-    __device__ __forceinline__ void issue(const f32x4& pr, int i0, const float* lds,
-                                          const int (&base)[4], const WinEval<W>& ev) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const float* __restrict__ p = lds + (base[i0 + i] + tap0<W>(pr[i0 + i], ev, sp[i]));
-#pragma unroll
-            for (int k = 0; k < W; ++k) c[i][k] = p[k];
-        }
-    }
-    __device__ __forceinline__ float value(int i, const WinEval<W>& ev,
-                                           const WindowArgs& win) const {
-        float wt[W];
-        window_weights<W>(sp[i], win, ev, wt);
-        float t = 0.f;
-#pragma unroll
-        for (int k = 0; k < W; ++k) t = fmaf(c[i][k], wt[k], t);
-        return t;
-    }
-};
-
-// Forms a result before any later LDS read is issued (left alone, the
-// compiler moves all arithmetic behind all reads and spills).
-__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)::"memory"); }
-
 // The batches of one group through a pipeline of half batches: the
 // projections of batch b + 2 on the matrix cores, the LDS reads of the next
 // half batch, the interpolation of this one (its two values to use(b, h,
@@ -1389,17 +1419,17 @@ __device__ __forceinline__ void gather_group(const float* lds, const int (&base)
     TapRead<W> tr[2];
     f32x4 pr = split_mfma<KB>(dop, yop[0], zero), nx = split_mfma<KB>(dop, yop[1], zero);
     if constexpr (NB == 2) reload();
-    tr[0].issue(pr, 0, lds, base, ev);
+    tr[0].issue(pr[0], pr[1], lds, base[0], base[1], ev);
 #pragma unroll
     for (int u = 0; u < 2 * NB; ++u) {
         const int b = u / 2, h = u & 1;
         if (h == 0) {
-            tr[1].issue(pr, 2, lds, base, ev);
+            tr[1].issue(pr[2], pr[3], lds, base[2], base[3], ev);
         } else if (b + 1 < NB) {
             pr = nx;
-            tr[0].issue(pr, 0, lds, base, ev);
+            tr[0].issue(pr[0], pr[1], lds, base[0], base[1], ev);
         }
-        asm volatile("" ::: "memory");          // the reads stay ahead of the arithmetic
+        reads_ahead();
         if (h == 1 && b + 2 < NB) {
             nx = split_mfma<KB>(dop, yop[b + 2], zero);
             if (b + 3 == NB) reload();
@@ -1875,7 +1905,7 @@ __global__ __launch_bounds__(kBlock) void batch_spread_kernel(
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
         const WindowArgs win = pr.swin;
-        spread_tile<W>(lds_bspread, pr.xproj, pr.ldx, pr.w, pr.N, P, pr.g, pr.chunk_len,
+        spread_tile<W>(lds_bspread, pr.xproj, pr.ldx, pr.wscaled, pr.N, P, pr.g, pr.chunk_len,
                        pr.slice_max, win, pr.partial, tk.a, tk.b);
     }
 }
@@ -1989,7 +2019,7 @@ __global__ __launch_bounds__(kGatherBlock) void batch_gather_fused_kernel(
 
 size_t fused_spread_lds(int nr) { return (size_t)spread_cells(nr) * sizeof(int); }
 
-size_t stored_spread_lds(int nr) { return (size_t)nr * sizeof(int); }
+size_t stored_spread_lds(int nr) { return ((size_t)nr << kSpreadLogR) * sizeof(int); }
 
 size_t fused_gather_lds(int nr) {
     const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);

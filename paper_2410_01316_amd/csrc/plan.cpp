@@ -497,7 +497,7 @@ struct fastsum_plan_s {
     bool norms_dirty = false;      // an exec stopped before its check cleared them
     float norm_lim = 1.f;          // (1 + 1e-5) / max_p |xi_p|
     float* slice_max = nullptr;    // per-slice max |w| (fixed-point scaling)
-    float* wscaled = nullptr;      // weights in their slices' fixed point (fused plans)
+    float* wscaled = nullptr;      // weights in their slices' fixed point
     // sorted plans: rows of stride sort_L, sources at 0, targets at sort_yoff
     float* keys = nullptr;
     float* keys_out = nullptr;
@@ -619,7 +619,7 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
     {
         PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
         FS_TRY(launch_spread(pl->Ws, src_proj, ld_src, wts, Nsrc, P, pl->geom, nchunk, chunk_len,
-                             pl->slice_max, pl->swin, pl->partial, st));
+                             pl->slice_max, pl->wscaled, pl->swin, pl->partial, st));
     }
     {
         PhaseTimer t(pl, FASTSUM_PHASE_FFTCONV, st);
@@ -942,7 +942,8 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
               dev_alloc(&pl->spart, (size_t)kSortMaxRanges * pl->ldm) &&
               dev_alloc(&pl->flag, 1) && dev_alloc(&pl->norms, kNormUints)
         : dev_alloc(&pl->A, (size_t)P * pl->dpad) && dev_alloc(&pl->norms, kNormUints) &&
-              (pl->fused ? dev_alloc(&pl->wscaled, (size_t)cap) && dev_alloc(&pl->xt, (size_t)split_tiles_bytes(n_max, pl->d) / 2) &&
+              dev_alloc(&pl->wscaled, (size_t)round_up(cap, kSliceLen)) &&
+              (pl->fused ? dev_alloc(&pl->xt, (size_t)split_tiles_bytes(n_max, pl->d) / 2) &&
                                dev_alloc(&pl->yt, (size_t)split_tiles_bytes(m_max, pl->d) / 2) &&
                                dev_alloc(&pl->at, (size_t)split_tiles_bytes(gtiles * kFuseDirs, pl->d) / 2)
                          : dev_alloc(&pl->xproj, (size_t)P * pl->ld_x) &&
