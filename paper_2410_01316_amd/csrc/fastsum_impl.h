@@ -62,6 +62,23 @@ __device__ inline void record_norm2(unsigned* role, float n2) {
     if ((threadIdx.x & 63) == 0) atomicMax(role + (blockIdx.x % kNormSlots) * kNormStride, u);
 }
 
+// Where a kernel that reads points records the largest |z / R|^2 of its rows:
+// the slots of a role (nullptr: nowhere), and for sources whose first
+// `prefix` rows are the targets, those rows' largest also into the targets'
+// slots, which follow.
+struct NormSink {
+    unsigned* role = nullptr;
+    int64_t prefix = 0;
+};
+
+// One wave (every lane active): n2 of row `row`, first_row the wave's first.
+__device__ inline void record_rows(const NormSink& sink, float n2, int64_t row, int64_t first_row) {
+    if (sink.role == nullptr) return;
+    record_norm2(sink.role, n2);
+    if (first_row < sink.prefix)
+        record_norm2(sink.role + kNormRoleUints, row < sink.prefix ? n2 : 0.f);
+}
+
 __device__ inline unsigned wave_max_u32(unsigned u) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) u = max(u, (unsigned)__shfl_xor((int)u, o));
@@ -94,13 +111,12 @@ hipError_t launch_point_norms(const float* X, int64_t N, int d, float scale, uns
                               hipStream_t stream);
 
 // out[p*ld + j] = sum_i A[p*dpad + i] * X[j*d + i] for p < P, j < N, with
-// A = tau * Xi^T.  Sets *flag if |out| > bound.  norm_slot (nullable):
-// largest |x_n * inv_r|^2, see BoundCheck.
+// A = tau * Xi^T.  Sets *flag if |out| > bound.  sink: |x_n * inv_r|^2 (NormSink).
 // FP32 MFMA, d <= 64: A64 is A zero-padded to round_up(P, 64) x 64.
 constexpr int kA64Cols = 64;
 hipError_t launch_project_f32(const float* X, int64_t N, int d, const float* A64, int P,
                               float* out, int64_t ld, float bound, int* flag,
-                              unsigned* norm_slot, float inv_r, hipStream_t stream);
+                              const NormSink& sink, float inv_r, hipStream_t stream);
 // Tile GEMM, any d: X is first written as operand tiles into xtiles (the
 // tile layout of the fused path below; bf16: one BF16 part per k-block,
 // else f16 hi + lo of x * inv_r), then multiplied with the direction tiles
@@ -120,7 +136,7 @@ hipError_t launch_backproject_tiles(const float* T, int64_t ld, int64_t M, int P
                                     hipStream_t stream);
 hipError_t launch_project_tiles(const float* X, int64_t N, int d, bool bf16, const uint16_t* At,
                                 int P, float inv_r, float pscale, uint16_t* xtiles, float* out,
-                                int64_t ld, float bound, int* flag, unsigned* norm_slot,
+                                int64_t ld, float bound, int* flag, const NormSink& sink,
                                 hipStream_t stream);
 
 // partial[(c*P + p)*nr + j - lo] = sum over sources i of chunk c of
@@ -193,19 +209,30 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
 int64_t split_tiles_bytes(int64_t rows, int d);
 
 // tiles of Z * scale (Z: N x d row-major); sets *flag if a row has
-// |Z_row * scale|^2 > norm2_max (or is not finite); records the largest
-// |Z_row * scale|^2 in *norm_slot (nullable, see BoundCheck)
+// |Z_row * scale|^2 > norm2_max (or is not finite); records
+// |Z_row * scale|^2 in sink
 hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, uint16_t* tiles,
-                               float norm2_max, int* flag, unsigned* norm_slot,
+                               float norm2_max, int* flag, const NormSink& sink,
                                hipStream_t stream);
+// Everything a fused exec reads its inputs for, in one launch: the tiles of
+// x (N rows, into xt) and, unless y is null, of y (M rows, into yt), and the
+// fixed-point weights of x (slice_max, wscaled: launch_spread).  norms: the
+// bound check's slots of both roles; prefix: as in NormSink.
+hipError_t launch_prepare_fused(const float* x, int64_t N, const float* y, int64_t M, int d,
+                                float scale, uint16_t* xt, uint16_t* yt, float norm2_max, int* flag,
+                                unsigned* norms, int64_t prefix, const float* w, float* slice_max,
+                                float* wscaled, hipStream_t stream);
+// slice_max and wscaled of the weights w (N)
+hipError_t launch_slice_max(const float* w, int64_t N, float* slice_max, float* wscaled,
+                            hipStream_t stream);
 
 // As launch_spread, with the projections computed in the kernel from the
 // split tiles of the sources (Xt, scale 1/R) and of the directions (At):
-// x~ = pscale * <xi, x / R>, pscale = tau R.  slice_max and wscaled as in
-// launch_spread.
+// x~ = pscale * <xi, x / R>, pscale = tau R.  slice_max and wscaled: filled
+// before by launch_prepare_fused or launch_slice_max.
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
-                               const float* w, int P, GridGeom g, float pscale, int nchunk,
-                               int64_t chunk_len, float* slice_max, float* wscaled,
+                               int P, GridGeom g, float pscale, int nchunk,
+                               int64_t chunk_len, const float* slice_max, const float* wscaled,
                                const WindowArgs& win, float* partial, hipStream_t stream);
 
 // spart[b*ldm + m] = sum over directions p of range b (prange per range, a

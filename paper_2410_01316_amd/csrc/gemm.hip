@@ -246,10 +246,10 @@ void project_tiles_kernel(const uint16_t* __restrict__ Xt, int64_t N,
 }
 
 // BF16 point tiles (one part per k-block): bf16(Z) in the tile layout; the
-// largest |Z_row * inv_r|^2 into *norm_slot (nullable, see BoundCheck)
+// rows' |z * inv_r|^2 into sink
 __global__ __launch_bounds__(kBlock) void bf16_points_kernel(
     const float* __restrict__ Z, int64_t N, int d, int KB, int64_t ntiles, u32x4* __restrict__ tiles,
-    float inv_r, unsigned* __restrict__ norm_slot) {
+    float inv_r, NormSink sink) {
     const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (id >= ntiles * 64) return;                    // whole waves
     const int lane = (int)(id & 63);
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kBlock) void bf16_points_kernel(
     }
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
-    if (norm_slot != nullptr) record_norm2(norm_slot, ss);
+    record_rows(sink, ss, r0 + (lane & 15), r0);
 }
 
 template <int PARTS>
@@ -384,7 +384,7 @@ size_t project_tiles_bytes(int64_t rows, int d, bool bf16) {
 
 hipError_t launch_project_tiles(const float* X, int64_t N, int d, bool bf16, const uint16_t* At,
                                 int P, float inv_r, float pscale, uint16_t* xtiles, float* out,
-                                int64_t ld, float bound, int* flag, unsigned* norm_slot,
+                                int64_t ld, float bound, int* flag, const NormSink& sink,
                                 hipStream_t stream) {
     const int KB = split_kblocks(d);
     const int64_t ntiles = (N + 15) / 16;
@@ -392,10 +392,10 @@ hipError_t launch_project_tiles(const float* X, int64_t N, int d, bool bf16, con
     if (bf16) {
         const unsigned sb = (unsigned)((ntiles * 64 + kBlock - 1) / kBlock);
         hipLaunchKernelGGL(bf16_points_kernel, dim3(sb), dim3(kBlock), 0, stream, X, N, d, KB,
-                           ntiles, reinterpret_cast<u32x4*>(xtiles), inv_r, norm_slot);
+                           ntiles, reinterpret_cast<u32x4*>(xtiles), inv_r, sink);
         e = hipGetLastError();
     } else {   // no per-point range check here: the projections are checked when stored
-        e = launch_split_points(X, N, d, inv_r, xtiles, __builtin_inff(), flag, norm_slot, stream);
+        e = launch_split_points(X, N, d, inv_r, xtiles, __builtin_inff(), flag, sink, stream);
     }
     if (e != hipSuccess) return e;
     const int64_t ncols = (N + 15) / 16 * 16;          // the padded rows are stored too

@@ -301,8 +301,7 @@ template <int KS>
 __device__ __forceinline__ void project_tile_f32_xres(
     ProjSmemXres& sm, const float* __restrict__ X, int64_t N, int d,
     const float* __restrict__ A64, int P, float* __restrict__ out, int64_t ld, float bound,
-    int* __restrict__ flag, int p_begin, int p_end, int64_t n0, unsigned* __restrict__ norm_slot,
-    float inv_r) {
+    int* __restrict__ flag, int p_begin, int p_end, int64_t n0, const NormSink& sink, float inv_r) {
     const int tid = threadIdx.x;
     float4 va[kXresQ4];
     xres_load_a(va, A64, p_begin);
@@ -312,7 +311,7 @@ __device__ __forceinline__ void project_tile_f32_xres(
         const int r = e / kXresLd, k = e % kXresLd;
         sm.Xs[r][k] = (k < d && n0 + r < N) ? X[(n0 + r) * d + k] : 0.f;
     }
-    if (norm_slot != nullptr) {                     // uniform: the bound check's row norms
+    if (sink.role != nullptr) {                     // uniform: the bound check's row norms
         __syncthreads();
         const int row = tid >> 1;                   // two threads per row (kBlock = 2 kProjBN)
         float ss = 0.f;
@@ -321,7 +320,7 @@ __device__ __forceinline__ void project_tile_f32_xres(
             ss = fmaf(v, v, ss);
         }
         ss += __shfl_xor(ss, 1);
-        record_norm2(norm_slot, ss);
+        record_rows(sink, ss, n0 + row, n0 + ((tid >> 6) << 5));
     }
     // steady state: whole 64 x 128 tiles, straight-line code so the wait
     // for the prefetched A tile does not include this tile's stores
@@ -357,20 +356,20 @@ template <int KS>
 __global__ __launch_bounds__(kBlock) void project_f32_xres_kernel(
     const float* __restrict__ X, int64_t N, int d, const float* __restrict__ A64,
     int P, float* __restrict__ out, int64_t ld, float bound, int* __restrict__ flag,
-    int prange, unsigned* __restrict__ norm_slot, float inv_r) {
+    int prange, NormSink sink, float inv_r) {
     __shared__ ProjSmemXres sm;
     const int p_begin = blockIdx.y * prange;
     project_tile_f32_xres<KS>(sm, X, N, d, A64, P, out, ld, bound, flag, p_begin,
                               min(P, p_begin + prange), (int64_t)blockIdx.x * kProjBN,
-                              blockIdx.y == 0 ? norm_slot : nullptr, inv_r);
+                              blockIdx.y == 0 ? sink : NormSink{}, inv_r);
 }
 
 template <int KS>
 void launch_xres(dim3 grid, hipStream_t stream, const float* X, int64_t N, int d,
                  const float* A64, int P, float* out, int64_t ld, float bound, int* flag,
-                 int prange, unsigned* norm_slot, float inv_r) {
+                 int prange, const NormSink& sink, float inv_r) {
     hipLaunchKernelGGL(project_f32_xres_kernel<KS>, grid, dim3(kBlock), 0, stream, X, N, d, A64,
-                       P, out, ld, bound, flag, prange, norm_slot, inv_r);
+                       P, out, ld, bound, flag, prange, sink, inv_r);
 }
 
 int project_xres_range(int64_t N, int P) {
@@ -382,19 +381,19 @@ int project_xres_range(int64_t N, int P) {
 
 hipError_t launch_project_f32(const float* X, int64_t N, int d, const float* A64, int P,
                               float* out, int64_t ld, float bound, int* flag,
-                              unsigned* norm_slot, float inv_r, hipStream_t stream) {
+                              const NormSink& sink, float inv_r, hipStream_t stream) {
     if (d > kXresMaxD || A64 == nullptr) return hipErrorInvalidValue;
     const int prange = project_xres_range(N, P);
     dim3 grid((unsigned)((N + kProjBN - 1) / kProjBN), (unsigned)((P + prange - 1) / prange));
     using L = void (*)(dim3, hipStream_t, const float*, int64_t, int, const float*, int,
-                       float*, int64_t, float, int*, int, unsigned*, float);
+                       float*, int64_t, float, int*, int, const NormSink&, float);
     static const L table[16] = {
         launch_xres<1>, launch_xres<2>, launch_xres<3>, launch_xres<4>,
         launch_xres<5>, launch_xres<6>, launch_xres<7>, launch_xres<8>,
         launch_xres<9>, launch_xres<10>, launch_xres<11>, launch_xres<12>,
         launch_xres<13>, launch_xres<14>, launch_xres<15>, launch_xres<16>};
     table[(d + 3) / 4 - 1](grid, stream, X, N, d, A64, P, out, ld, bound, flag, prange,
-                           norm_slot, inv_r);
+                           sink, inv_r);
     return hipGetLastError();
 }
 
@@ -569,8 +568,8 @@ hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
                          int64_t N, int P, GridGeom g, int nchunk,
                          int64_t chunk_len, float* slice_max, float* wscaled,
                          const WindowArgs& win, float* partial, hipStream_t stream) {
-    hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max, wscaled);
+    const hipError_t e = launch_slice_max(w, N, slice_max, wscaled, stream);
+    if (e != hipSuccess) return e;
     dim3 grid((unsigned)P, (unsigned)nchunk);
     const size_t lds = stored_spread_lds(g.nr);
     switch (W) {
@@ -1127,13 +1126,13 @@ constexpr int kDmaBytes = 64 * 16;                         // one wave's 16-byte
 // and columns >= d are zero.  Also the range check of the fused path: a
 // row with |z * scale|^2 > norm2_max sets *flag (z * scale is x / R, and
 // |<xi, x / R>| <= max|xi| |x| / R bounds every projection of the row), and
-// the row norms of the bound check (BoundCheck) when norm_slot is given.
+// the row norms of the bound check (NormSink).
 // Called by whole waves (one tile per wave).
 __device__ __forceinline__ void split_points_lane(const float* __restrict__ Z, int64_t N, int d,
                                                   float scale, int KB, int64_t t, int lane,
                                                   u32x4* __restrict__ tiles, float norm2_max,
                                                   int* __restrict__ flag,
-                                                  unsigned* __restrict__ norm_slot) {
+                                                  const NormSink& sink) {
     // The tile's rows as a buffer: a lane reads its eight columns with two
     // 16-byte loads; rows past N read as zero and columns >= d (the next
     // row's values) are masked.
@@ -1165,17 +1164,39 @@ __device__ __forceinline__ void split_points_lane(const float* __restrict__ Z, i
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
     if (!(ss <= norm2_max) && lane < 16) atomicOr(flag, 1);   // NaN also flags
-    if (norm_slot != nullptr) record_norm2(norm_slot, ss);
+    record_rows(sink, ss, r0 + (lane & 15), r0);
 }
 
 __global__ __launch_bounds__(kBlock) void split_points_kernel(
     const float* __restrict__ Z, int64_t N, int d, float scale, int KB, int64_t ntiles,
-    u32x4* __restrict__ tiles, float norm2_max, int* __restrict__ flag,
-    unsigned* __restrict__ norm_slot) {
+    u32x4* __restrict__ tiles, float norm2_max, int* __restrict__ flag, NormSink sink) {
     const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (id >= ntiles * 64) return;                    // whole waves
-    split_points_lane(Z, N, d, scale, KB, id >> 6, (int)(id & 63), tiles, norm2_max, flag,
-                      norm_slot);
+    split_points_lane(Z, N, d, scale, KB, id >> 6, (int)(id & 63), tiles, norm2_max, flag, sink);
+}
+
+constexpr int kPrepTiles = kBlock / 64;               // tiles per workgroup
+
+// Workgroups [0, bx) split the sources, [bx, bx + by) the targets, the rest
+// take one slice of weights each.  Three launches in one: at a few thousand
+// points each costs its launch, not its work.
+__global__ __launch_bounds__(kBlock) void prepare_fused_kernel(
+    const float* __restrict__ x, int64_t N, const float* __restrict__ y, int64_t M, int d,
+    float scale, int KB, int bx, int by, u32x4* __restrict__ xt, u32x4* __restrict__ yt,
+    float norm2_max, int* __restrict__ flag, NormSink xsink, NormSink ysink,
+    const float* __restrict__ w, float* __restrict__ slice_max, float* __restrict__ wscaled) {
+    __shared__ float red[kBlock];
+    const int b = blockIdx.x;
+    if (b >= bx + by) {
+        slice_max_tile(red, w, N, b - bx - by, slice_max, wscaled);
+        return;
+    }
+    const bool src = b < bx;
+    const int64_t n = src ? N : M;
+    const int64_t t = (int64_t)(src ? b : b - bx) * kPrepTiles + (threadIdx.x >> 6);
+    if (16 * t >= n) return;                          // whole waves
+    split_points_lane(src ? x : y, n, d, scale, KB, t, threadIdx.x & 63, src ? xt : yt, norm2_max,
+                      flag, src ? xsink : ysink);
 }
 
 // One wave per row of X: the largest |x_n * scale|^2 into *slot (bound
@@ -1739,14 +1760,34 @@ int64_t split_tiles_bytes(int64_t rows, int d) {
 }
 
 hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, uint16_t* tiles,
-                               float norm2_max, int* flag, unsigned* norm_slot,
+                               float norm2_max, int* flag, const NormSink& sink,
                                hipStream_t stream) {
     const int KB = split_kblocks(d);
     const int64_t ntiles = (N + 15) / 16;
     const int64_t threads = ntiles * 64;
     hipLaunchKernelGGL(split_points_kernel, dim3((unsigned)((threads + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, stream, Z, N, d, scale, KB, ntiles,
-                       reinterpret_cast<u32x4*>(tiles), norm2_max, flag, norm_slot);
+                       reinterpret_cast<u32x4*>(tiles), norm2_max, flag, sink);
+    return hipGetLastError();
+}
+
+hipError_t launch_prepare_fused(const float* x, int64_t N, const float* y, int64_t M, int d,
+                                float scale, uint16_t* xt, uint16_t* yt, float norm2_max, int* flag,
+                                unsigned* norms, int64_t prefix, const float* w, float* slice_max,
+                                float* wscaled, hipStream_t stream) {
+    auto blocks = [](int64_t n) { return (int)((n + 16 * kPrepTiles - 1) / (16 * kPrepTiles)); };
+    const int bx = blocks(N), by = y ? blocks(M) : 0, bs = (int)((N + kSlice - 1) / kSlice);
+    hipLaunchKernelGGL(prepare_fused_kernel, dim3((unsigned)(bx + by + bs)), dim3(kBlock), 0, stream,
+                       x, N, y, M, d, scale, split_kblocks(d), bx, by, reinterpret_cast<u32x4*>(xt),
+                       reinterpret_cast<u32x4*>(yt), norm2_max, flag, NormSink{norms, prefix},
+                       NormSink{norms + kNormRoleUints, 0}, w, slice_max, wscaled);
+    return hipGetLastError();
+}
+
+hipError_t launch_slice_max(const float* w, int64_t N, float* slice_max, float* wscaled,
+                            hipStream_t stream) {
+    hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
+                       0, stream, w, N, slice_max, wscaled);
     return hipGetLastError();
 }
 
@@ -1790,8 +1831,8 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
 }
 
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
-                               const float* w, int P, GridGeom g, float pscale, int nchunk,
-                               int64_t chunk_len, float* slice_max, float* wscaled,
+                               int P, GridGeom g, float pscale, int nchunk,
+                               int64_t chunk_len, const float* slice_max, const float* wscaled,
                                const WindowArgs& win, float* partial, hipStream_t stream) {
     if (!fused_supported(d, g.nr) || chunk_len % 16 != 0 || chunk_len <= 0)
         return hipErrorInvalidValue;
@@ -1811,8 +1852,6 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
          {launch_spread_fused_t<8, 1, kFuseAccWide>, launch_spread_fused_t<8, 2, kFuseAccWide>}}};
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max, wscaled);
     dim3 grid((unsigned)((P + kFuseDirs - 1) / kFuseDirs), (unsigned)nchunk);
     t[fused_wide(g.nr)][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
                                                   Xt, N, At, wscaled, P, g, pscale, chunk_len,
@@ -1970,7 +2009,7 @@ __global__ __launch_bounds__(kBlock) void batch_split_kernel(
         for (int64_t id = t0 * 64 + threadIdx.x; id < t1 * 64; id += kBlock)
             split_points_lane(is_y ? pr.y : pr.x, n, pr.d, pr.inv_r, pr.kb, id >> 6,
                               (int)(id & 63), dst, pr.norm2_max, flag,
-                              pr.norms + (is_y ? kNormRoleUints : 0));
+                              NormSink{pr.norms + (is_y ? kNormRoleUints : 0), 0});
     }
 }
 

@@ -643,12 +643,17 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
 // Fused path (d <= 64): the points are split into f16 operand tiles
 // (scaled by 1/R), then the projections tau R <xi, x / R> are computed inside
 // the spreading and gathering kernels.
-//   split(x), split(y) -> spread(x, w) -> fftconv -> gather(y) -> reduce
-// Spread (sources xt, weights w), FFT convolution (and the derivative grids
+//   prepare(x, y, w) -> spread(x, w) -> fftconv -> gather(y) -> reduce
+// Rows of the sources that are also the targets, when those are a proper
+// prefix of the sources (0 otherwise): their norms are checked as targets'.
+int64_t prefix_rows(const float* x, int64_t N, const float* y, int64_t M) {
+    return x == y && M < N ? M : 0;
+}
+
+// Spread (sources xt, weights w in pl->wscaled), FFT convolution (and the derivative grids
 // when grid_d is given), gather at the targets yt and reduction into out:
 // one sliced Fourier sum on split operand tiles.
-fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, const float* w, int64_t N,
-                         const uint16_t* yt, int64_t M, float* out, float* grid, float* grid_d,
+fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, const uint16_t* yt, int64_t M, float* out, float* grid, float* grid_d,
                          const BoundCheck& bc, hipStream_t st) {
     const int P = pl->P;
     const float pscale = (float)(pl->r.tau * pl->r.p.R);
@@ -657,7 +662,7 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, const float* w,
                                   chunk_len);
     {
         PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
-        FS_TRY(launch_spread_fused(pl->Ws, xt, N, pl->d, pl->at, w, P, pl->geom, pscale, nchunk,
+        FS_TRY(launch_spread_fused(pl->Ws, xt, N, pl->d, pl->at, P, pl->geom, pscale, nchunk,
                                    chunk_len, pl->slice_max, pl->wscaled, pl->swin, pl->partial, st));
     }
     {
@@ -688,18 +693,14 @@ fastsum_status fused_pass(fastsum_plan_s* pl, const float* x, const float* w, in
     // the stored path's check of each projection)
     const double lim = (1.0 + 1e-5) / pl->xi_norm_max;
     const float norm2_max = (float)(lim * lim);
-    const uint16_t* yt = pl->xt;
+    const uint16_t* yt = y != x ? pl->yt : pl->xt;
     {
         PhaseTimer t(pl, FASTSUM_PHASE_PROJECT, st);
-        FS_TRY(launch_split_points(x, N, pl->d, inv_r, pl->xt, norm2_max, pl->flag, pl->norms,
-                                   st));
-        if (y != x) {
-            FS_TRY(launch_split_points(y, M, pl->d, inv_r, pl->yt, norm2_max, pl->flag,
-                                       pl->norms + kNormRoleUints, st));
-            yt = pl->yt;
-        }
+        FS_TRY(launch_prepare_fused(x, N, y != x ? y : nullptr, M, pl->d, inv_r, pl->xt, pl->yt,
+                                    norm2_max, pl->flag, pl->norms, prefix_rows(x, N, y, M), w,
+                                    pl->slice_max, pl->wscaled, st));
     }
-    return fused_sum(pl, pl->xt, w, N, yt, M, out, pl->grid,
+    return fused_sum(pl, pl->xt, N, yt, M, out, pl->grid,
                      (pl->r.p.flags & FASTSUM_FLAG_GRAD) ? pl->grid_d : nullptr, bc, st);
 }
 
@@ -715,10 +716,10 @@ int fused_grad_range(int64_t M, int P, int64_t slots) {
     return (int)round_up((P + ranges - 1) / ranges, kFuseDirs);
 }
 
-// Stored projections of X into out (row stride ld); norm_slot (nullable)
-// receives the rows' largest |x / R|^2 for the bound check.
+// Stored projections of X into out (row stride ld); sink: the bound check's
+// row norms.
 fastsum_status project(fastsum_plan_s* pl, const float* X, int64_t N, float* out, int64_t ld,
-                       unsigned* norm_slot, hipStream_t st) {
+                       const NormSink& sink, hipStream_t st) {
     PhaseTimer t(pl, FASTSUM_PHASE_PROJECT, st);
     const float inv_r = (float)(1.0 / pl->r.p.R);
     if (pl->tile_gemm) {
@@ -727,10 +728,10 @@ fastsum_status project(fastsum_plan_s* pl, const float* X, int64_t N, float* out
         const bool bf16 = pl->r.p.proj == FASTSUM_PROJ_BF16;
         return check(launch_project_tiles(X, N, pl->d, bf16, pl->gdt, pl->P, inv_r,
                                           bf16 ? 1.f : (float)(pl->r.tau * pl->r.p.R), pl->gpt,
-                                          out, ld, pl->bound, pl->flag, norm_slot, st));
+                                          out, ld, pl->bound, pl->flag, sink, st));
     }
     return check(launch_project_f32(X, N, pl->d, pl->A64, pl->P, out, ld, pl->bound, pl->flag,
-                                    norm_slot, inv_r, st));
+                                    sink, inv_r, st));
 }
 
 // grad[m * d + i] = coef v[m] sum_p T[p * ld + m] tau xi_p[i]: on the tile
@@ -752,10 +753,10 @@ fastsum_status sorted_pass(fastsum_plan_s* pl, const float* x, const float* w, i
                            const float* y, int64_t M, float* out, bool same,
                            const BoundCheck& bc, hipStream_t st) {
     const int64_t L = pl->sort_L, yoff = pl->sort_yoff;
-    fastsum_status r = project(pl, x, N, pl->keys, L, pl->norms, st);
+    fastsum_status r = project(pl, x, N, pl->keys, L, NormSink{pl->norms, prefix_rows(x, N, y, M)}, st);
     if (r != FASTSUM_OK) return r;
     if (!same) {
-        r = project(pl, y, M, pl->keys + yoff, L, pl->norms + kNormRoleUints, st);
+        r = project(pl, y, M, pl->keys + yoff, L, NormSink{pl->norms + kNormRoleUints, 0}, st);
         if (r != FASTSUM_OK) return r;
     }
     const double coef = -energy_cd(pl->d) / pl->r.tau;
@@ -1111,20 +1112,17 @@ fastsum_status fastsum_exec(fastsum_plan pl, const float* x, int64_t N, const fl
     if (pl->norms_dirty) FS_TRY(launch_clear_norms(pl->norms, st));
     pl->norms_dirty = true;
     const BoundCheck bc{pl->norms, pl->flag, pl->norm_lim, (same && !prefix) ? 1 : 0};
-    if (prefix)
-        FS_TRY(launch_point_norms(y, M, pl->d, (float)(1.0 / pl->r.p.R),
-                                  pl->norms + kNormRoleUints, st));
     fastsum_status r = FASTSUM_OK;
     if (pl->sorted) {
         r = sorted_pass(pl, x, w, N, y, M, s, same, bc, st);
     } else if (pl->fused) {
         r = fused_pass(pl, x, w, N, y, M, s, bc, st);
     } else {
-        r = project(pl, x, N, pl->xproj, pl->ld_x, pl->norms, st);
+        r = project(pl, x, N, pl->xproj, pl->ld_x, NormSink{pl->norms, prefix_rows(x, N, y, M)}, st);
         const float* yp = pl->xproj;
         int64_t ldy = pl->ld_x;
         if (r == FASTSUM_OK && !same) {
-            r = project(pl, y, M, pl->yproj, pl->ld_y, pl->norms + kNormRoleUints, st);
+            r = project(pl, y, M, pl->yproj, pl->ld_y, NormSink{pl->norms + kNormRoleUints, 0}, st);
             yp = pl->yproj;
             ldy = pl->ld_y;
         }
@@ -1169,7 +1167,11 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
                                      pl->dwin, pl->gpart, pl->ldg, coef, grad_s, grad_y, st));
         }
         if (grad_w || grad_x) {
-            fastsum_status r = fused_sum(pl, yt, grad_s, M, pl->xt, N, uout, pl->grid_w,
+            {
+                PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
+                FS_TRY(launch_slice_max(grad_s, M, pl->slice_max, pl->wscaled, st));
+            }
+            fastsum_status r = fused_sum(pl, yt, M, pl->xt, N, uout, pl->grid_w,
                                          grad_x ? pl->grid_wd : nullptr, BoundCheck{}, st);
             if (r != FASTSUM_OK) return r;
         }
