@@ -167,7 +167,7 @@ void fused_tasks(int i, const BatchProblem& d, const fastsum_problem_io& q, int 
             cost[kBatchSpread].push_back(len * std::min(kFuseDirs, P - g * kFuseDirs));
         }
     }
-    for (int a = 0; a < (P + 1) / 2; ++a) ph[kBatchFftconv].push_back({i, a, 0, 0});
+    for (int a = 0; a < (P + 1) / 2; a += fftconv_pairs(d.g.n)) ph[kBatchFftconv].push_back({i, a, 0, 0});
     const int64_t tile = fused_gather_tile(0, 4);    // batched plans: narrow grids
     const int gtiles = (int)((q.M + tile - 1) / tile);
     for (int r = 0; r < d.ngroup; ++r)
@@ -260,7 +260,7 @@ fastsum_status build_tasks(fastsum_batch_s* b, const fastsum_problem_io* io) {
             ph[kBatchScale].push_back({i, c, 0, 0});
         for (int c = 0; c < d.nchunk; ++c)
             for (int p = 0; p < P; ++p) ph[kBatchSpread].push_back({i, p, c, 0});
-        for (int a = 0; a < (P + 1) / 2; ++a) ph[kBatchFftconv].push_back({i, a, 0, 0});
+        for (int a = 0; a < (P + 1) / 2; a += fftconv_pairs(d.g.n)) ph[kBatchFftconv].push_back({i, a, 0, 0});
         const int gtiles = (int)((q.M + kGatherTile - 1) / kGatherTile);
         for (int g = 0; g < d.ngroup; ++g)
             for (int t = 0; t < gtiles; ++t) ph[kBatchGather].push_back({i, t, g, 0});
@@ -358,7 +358,7 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
 
     // per-problem FP64 precompute and arena layout
     size_t off = 0;
-    int max_nr = 8, max_n = 8;
+    int max_nr = 8;
     std::vector<std::vector<float2>> mults(n_problems), tws(n_problems);
     std::vector<std::vector<float>> As(n_problems);
     std::vector<std::vector<uint16_t>> Ats(n_problems);
@@ -399,7 +399,6 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
         pp.ldy = round_up(pd.m_max, 64);
         pp.ldm = round_up(std::max(pd.n_max, pd.m_max), 64);
         max_nr = std::max(max_nr, pp.geom.nr);
-        max_n = std::max(max_n, n);
         std::vector<float2> mult_d;
         build_tables(pp.r, pp.win, mults[i], mult_d, tws[i]);
         As[i].assign((size_t)b->P * pp.dpad, 0.f);
@@ -472,9 +471,16 @@ fastsum_status fastsum_batch_create(const fastsum_params* common, const fastsum_
     }
     b->arena_bytes = off;
     b->task_cap = tasks;
-    b->lds_spread = b->fused ? fused_spread_lds(max_nr) : stored_spread_lds(max_nr);
-    b->lds_fft = fftconv_lds_bytes(max_n, false);
-    b->lds_gather = b->fused ? fused_gather_lds(max_nr) : (size_t)b->pstage * max_nr * sizeof(float);
+    b->lds_spread = stored_spread_lds(max_nr);
+    if (b->fused) {
+        b->lds_spread = 0;    // a narrow grid with copies may need more than a wider one
+        for (const ProblemPlan& pp : b->plans)
+            b->lds_spread = std::max(b->lds_spread, fused_spread_lds(pp.geom.nr));
+    }
+    b->lds_fft = 0;          // several pairs share a workgroup on small grids
+    for (const ProblemPlan& pp : b->plans)
+        b->lds_fft = std::max(b->lds_fft, fftconv_lds_bytes(pp.win.n, false));
+    b->lds_gather = b->fused ? fused_gather_lds(max_nr) : stored_gather_lds(b->pstage, max_nr);
 
     hipError_t e = hipGetDevice(&b->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&b->num_cu, hipDeviceAttributeMultiprocessorCount, b->device);

@@ -152,13 +152,17 @@ hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
 
 // Per pair of directions: sum the chunk partials, complex FFT of size n,
 // multiply by mult (and separately by mult_d when grid_d != nullptr),
-// inverse FFT, store the cells [lo, lo+nr) of the real grids.
-// LDS bytes of one FFT-convolution workgroup (grid size n, derivative grids)
+// inverse FFT, store the cells [lo, lo+nr) of the real grids.  dmax
+// (nullable, zeroed before): the largest |grid_d| into abs_slots_uints() slots.
+size_t abs_slots_uints();
+// direction pairs of one FFT-convolution workgroup (grid size n), and its LDS
+// bytes (grad: with derivative grids)
+int fftconv_pairs(int n);
 size_t fftconv_lds_bytes(int n, bool grad);
 hipError_t launch_fftconv(const float* partial, int nchunk, int P, GridGeom g,
                           const float2* tw, const float2* mult,
                           const float2* mult_d, float* grid, float* grid_d,
-                          hipStream_t stream);
+                          unsigned* dmax, hipStream_t stream);
 
 // spart[b*ldm + m] = sum over the directions p of group b (pg per group) of
 //   sum_taps grid[p*nr + cell - lo] * window(cell - u(proj[p*ld + m]))
@@ -221,10 +225,11 @@ hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, ui
 hipError_t launch_prepare_fused(const float* x, int64_t N, const float* y, int64_t M, int d,
                                 float scale, uint16_t* xt, uint16_t* yt, float norm2_max, int* flag,
                                 unsigned* norms, int64_t prefix, const float* w, float* slice_max,
-                                float* wscaled, hipStream_t stream);
-// slice_max and wscaled of the weights w (N)
+                                float* wscaled, unsigned* clear, hipStream_t stream);
+// slice_max and wscaled of the weights w (N).  clear (nullable, here and
+// above): the slots of a derivative maximum (launch_fftconv's dmax) to zero
 hipError_t launch_slice_max(const float* w, int64_t N, float* slice_max, float* wscaled,
-                            hipStream_t stream);
+                            unsigned* clear, hipStream_t stream);
 
 // As launch_spread, with the projections computed in the kernel from the
 // split tiles of the sources (Xt, scale 1/R) and of the directions (At):
@@ -243,17 +248,18 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
                                hipStream_t stream);
 
 // Adjoint in the targets on the fused path:
-//   grad_y[m*d + i] = coef * v[m] * sum_p t'_{m,p} (tau xi_p)_i
+//   grad_y[m*d + i] = coef * v[m] * sum_p t'_{m,p} (xi_p)_i
 // with t' the derivative grid interpolated at the in-kernel projections and
 // the sum over p back-projected on the matrix cores.  Ab: per 16-direction
-// group g, MFMA i (0..3) and 16-coordinate chunk q (DC = ceil(d/16)), 64
-// floats: entry k*16 + m = tau xi_{16g + 4k + i}[16q + m] (zero past P, d).
+// group g, 16-coordinate chunk q (DC = ceil(d/16)) and part (f16 hi, lo),
+// lane m + 16 k: 4 halves (xi_{16g + 4k + i})_{16q + m}, i < 4 (zero past P,
+// d).  dmax: the slots launch_fftconv filled with grid_d.
 // gpart: ceil(P / prange) x ldg x 16 DC floats of partial sums (ldg >= M).
 int64_t fused_grad_tile();    // targets per workgroup
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
-                             const float* Ab, int P, GridGeom g, float pscale,
-                             const float* grid_d, int prange, const WindowArgs& win,
-                             float* gpart, int64_t ldg, float coef, const float* v,
+                             const uint16_t* Ab, int P, GridGeom g, float pscale,
+                             const float* grid_d, const unsigned* dmax, int prange,
+                             const WindowArgs& win, float* gpart, int64_t ldg, float coef, const float* v,
                              float* grad_y, hipStream_t stream);
 
 // ---- exact sliced sums for the energy kernel by sorting (sorted.hip) ----
@@ -365,7 +371,7 @@ enum BatchPhase {
                          // (fused: b = block of kSplitTaskTiles split tiles)
     kBatchScale = 1,     // a = slice of kSliceLen sources
     kBatchSpread = 2,    // a = direction, b = chunk (fused: a = 16-direction group)
-    kBatchFftconv = 3,   // a = direction pair
+    kBatchFftconv = 3,   // a = first of fftconv_pairs direction pairs
     kBatchGather = 4,    // a = target tile, b = direction group (fused: range)
     kBatchReduce = 5,    // a = block of kBlock targets
     kBatchPhases = 6
@@ -393,5 +399,7 @@ size_t fused_spread_lds(int nr);
 // LDS bytes of the stored-projection spread (one direction's int32 cells)
 size_t stored_spread_lds(int nr);
 size_t fused_gather_lds(int nr);
+// LDS bytes of the stored-projection gather (pstage grids)
+size_t stored_gather_lds(int pstage, int nr);
 
 }  // namespace fastsum

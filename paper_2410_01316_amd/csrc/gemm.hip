@@ -308,11 +308,8 @@ hipError_t launch_gemm(const uint16_t* Xt, int64_t N, const uint16_t* At, int P,
 // plan); the GEMM's epilogue applies coef v[m] tau 2^e.
 // ---------------------------------------------------------------------------
 
-constexpr int kAbsSlots = 64;
-constexpr int kAbsStride = 16;                     // one 64-byte line per slot
-
 __global__ __launch_bounds__(kBlock) void clear_slots_kernel(unsigned* __restrict__ slots) {
-    for (int j = threadIdx.x; j < kAbsSlots * kAbsStride; j += kBlock) slots[j] = 0u;
+    for (int j = threadIdx.x; j < kAbsUints; j += kBlock) slots[j] = 0u;
 }
 
 // largest |T[p][m]| (p < P, m < M) as float bits into the slots (a
@@ -329,20 +326,7 @@ __global__ __launch_bounds__(kBlock) void abs_max_kernel(const float* __restrict
             mx = (a <= 3.4e38f) ? fmaxf(mx, a) : __builtin_inff();
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    const int b = blockIdx.x + gridDim.x * blockIdx.y;
-    if ((threadIdx.x & 63) == 0) atomicMax(slots + (b % kAbsSlots) * kAbsStride, __float_as_uint(mx));
-}
-
-// e with max 2^-e < 1 from the slots (0 for an all-zero or non-finite T)
-__device__ __forceinline__ int slots_exponent(const unsigned* __restrict__ slots, int lane) {
-    float mx = __uint_as_float(slots[lane * kAbsStride]);      // 64 lanes, 64 slots
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    int e = 0;
-    if (mx > 0.f && mx <= 3.4e38f) (void)frexpf(mx, &e);     // mx < 2^e
-    return e;
+    record_abs(slots, mx, blockIdx.x + gridDim.x * blockIdx.y);
 }
 
 // Split tiles of T^T: tile t (rows m = 16 t + c), k-block kb (columns
@@ -407,7 +391,7 @@ hipError_t launch_project_tiles(const float* X, int64_t N, int d, bool bf16, con
 
 size_t backproject_tiles_bytes(int64_t rows, int P) { return (size_t)split_tiles_bytes(rows, P); }
 
-size_t backproject_scratch_bytes() { return (size_t)kAbsSlots * kAbsStride * 4 + 256; }
+size_t backproject_scratch_bytes() { return (size_t)kAbsUints * 4 + 256; }
 
 hipError_t launch_backproject_tiles(const float* T, int64_t ld, int64_t M, int P, int d,
                                     const uint16_t* xit, float tau, float coef, const float* v,
@@ -415,7 +399,7 @@ hipError_t launch_backproject_tiles(const float* T, int64_t ld, int64_t M, int P
                                     hipStream_t stream) {
     if (M < 1 || P < 1 || d < 1) return hipErrorInvalidValue;
     unsigned* slots = static_cast<unsigned*>(scratch);
-    float* gscale = reinterpret_cast<float*>(slots + kAbsSlots * kAbsStride);
+    float* gscale = reinterpret_cast<float*>(slots + kAbsUints);
     hipLaunchKernelGGL(clear_slots_kernel, dim3(1), dim3(kBlock), 0, stream, slots);
     const dim3 mg((unsigned)std::min<int64_t>(64, (M + kBlock - 1) / kBlock),
                   (unsigned)std::min(P, 32));

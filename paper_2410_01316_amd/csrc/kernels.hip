@@ -423,7 +423,8 @@ __device__ __forceinline__ int slice_exponent(float mx) {
 }
 
 // slice_max[s] = max |w_i| over the sources i of slice s, and the weights in
-// the slice's fixed point, wscaled_i = w_i 2^k (zero from N to the slice's end)
+// the slice's fixed point, wscaled_i = w_i 2^k (zero for NaN, and from N to
+// the slice's end)
 __device__ __forceinline__ void slice_max_tile(float* red, const float* __restrict__ w,
                                                int64_t N, int s, float* __restrict__ slice_max,
                                                float* __restrict__ wscaled) {
@@ -448,13 +449,21 @@ __device__ __forceinline__ void slice_max_tile(float* red, const float* __restri
     const float scale = ldexpf(1.f, slice_exponent(red[0]));
 #pragma unroll
     for (int q = 0; q < kSlice / kBlock; ++q)
-        wscaled[i0 + threadIdx.x + (int64_t)q * kBlock] = v[q] * scale;
+        wscaled[i0 + threadIdx.x + (int64_t)q * kBlock] = v[q] == v[q] ? v[q] * scale : 0.f;
+}
+
+// clear: kAbsUints maxima to be zeroed for the FFT convolution that follows
+// (nullptr: none)
+__device__ __forceinline__ void clear_abs(unsigned* __restrict__ clear) {
+    if (clear != nullptr)
+        for (int j = threadIdx.x; j < kAbsUints; j += kBlock) clear[j] = 0u;
 }
 
 __global__ __launch_bounds__(kBlock) void slice_max_kernel(
     const float* __restrict__ w, int64_t N, float* __restrict__ slice_max,
-    float* __restrict__ wscaled) {
+    float* __restrict__ wscaled, unsigned* __restrict__ clear) {
     __shared__ float red[kBlock];
+    if (blockIdx.x == 0) clear_abs(clear);
     slice_max_tile(red, w, N, blockIdx.x, slice_max, wscaled);
 }
 
@@ -568,7 +577,7 @@ hipError_t launch_spread(int W, const float* proj, int64_t ld, const float* w,
                          int64_t N, int P, GridGeom g, int nchunk,
                          int64_t chunk_len, float* slice_max, float* wscaled,
                          const WindowArgs& win, float* partial, hipStream_t stream) {
-    const hipError_t e = launch_slice_max(w, N, slice_max, wscaled, stream);
+    const hipError_t e = launch_slice_max(w, N, slice_max, wscaled, nullptr, stream);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)P, (unsigned)nchunk);
     const size_t lds = stored_spread_lds(g.nr);
@@ -631,12 +640,13 @@ __device__ __forceinline__ void dft8(float2 (&a)[8], float sgn) {
     }
 }
 
+// t0, nt: this thread of the nt that share the transform
 template <int R>
 __device__ __forceinline__ void fft_pass(const float2* a, float2* b, int n, int L,
-                                         const float2* tw, float sgn) {
+                                         const float2* tw, float sgn, int t0, int nt) {
     const int nb = n / R;
     const int tstep = n / (R * L);
-    for (int t = threadIdx.x; t < nb; t += kBlock) {
+    for (int t = t0; t < nb; t += nt) {
         const int k = t & (L - 1);
         float2 v[R];
 #pragma unroll
@@ -665,19 +675,20 @@ __device__ __forceinline__ void fft_pass(const float2* a, float2* b, int n, int 
 }
 
 // returns the buffer (a or b) that holds the transform
-__device__ float2* fft_lds(float2* a, float2* b, int n, const float2* tw, bool inverse) {
+__device__ float2* fft_lds(float2* a, float2* b, int n, const float2* tw, bool inverse, int t0,
+                           int nt) {
     const float sgn = inverse ? -1.f : 1.f;
     for (int L = 1; L < n;) {
         const int rest = n / L;
         int R;
         if (rest >= 8) {
-            fft_pass<8>(a, b, n, L, tw, sgn);
+            fft_pass<8>(a, b, n, L, tw, sgn, t0, nt);
             R = 8;
         } else if (rest == 4) {
-            fft_pass<4>(a, b, n, L, tw, sgn);
+            fft_pass<4>(a, b, n, L, tw, sgn, t0, nt);
             R = 4;
         } else {
-            fft_pass<2>(a, b, n, L, tw, sgn);
+            fft_pass<2>(a, b, n, L, tw, sgn, t0, nt);
             R = 2;
         }
         __syncthreads();
@@ -689,33 +700,46 @@ __device__ float2* fft_lds(float2* a, float2* b, int n, const float2* tw, bool i
     return a;
 }
 
-// LDS of one fftconv tile: the twiddle table and two (three with the
-// derivative grids) buffers of n complex values
-size_t fftconv_lds_bytes(int n, bool grad) { return (size_t)(grad ? 4 : 3) * n * sizeof(float2); }
+// A workgroup transforms fftconv_pairs(n) direction pairs, kBlock /
+// fftconv_pairs threads each: one radix-8 butterfly per thread and pass (at
+// n = 512 a workgroup per pair left three of its four waves idle, and
+// registers allow three workgroups per CU).
+__host__ __device__ constexpr int fftconv_threads(int n) { return n >= 2048 ? 256 : n >= 1024 ? 128 : 64; }
+int fftconv_pairs(int n) { return kBlock / fftconv_threads(n); }
 
+// LDS of one fftconv workgroup: the twiddle table and two (three with the
+// derivative grids) buffers of n complex values per pair
+size_t fftconv_lds_bytes(int n, bool grad) {
+    return (size_t)(1 + (grad ? 3 : 2) * fftconv_pairs(n)) * n * sizeof(float2);
+}
+
+// nt: threads per pair (fftconv_threads(g.n)); the workgroup's pairs are
+// pair0 .. pair0 + kBlock / nt - 1.  dmax (nullptr: none): the largest
+// |grid_d| into its slots (record_abs)
 __device__ __forceinline__ void fftconv_tile(
     float2* cbuf, const float* __restrict__ partial, int nchunk, int P, const GridGeom& g,
     const float2* __restrict__ tw, const float2* __restrict__ mult,
     const float2* __restrict__ mult_d, float* __restrict__ grid, float* __restrict__ grid_d,
-    int pair) {
-    constexpr int kPer = 2048 / kBlock;   // table entries per thread (n <= 2048)
+    unsigned* __restrict__ dmax, int nt, int pair0) {
+    constexpr int kPer = 8;               // table entries per thread (n <= 8 nt)
     constexpr int kInFlight = 8;          // chunk partials per direction loaded at once
     const int n = g.n;
-    const int tid = threadIdx.x;
+    const int sub = threadIdx.x / nt, tid = threadIdx.x - sub * nt;
     float2* twl = cbuf;
-    float2* b0 = cbuf + n;
-    float2* b1 = cbuf + 2 * n;
-    float2* b2 = cbuf + 3 * n;            // only with derivative grids
-    const int pa = 2 * pair, pb = pa + 1;
+    float2* b0 = cbuf + n + sub * (grid_d ? 3 : 2) * n;
+    float2* b1 = b0 + n;
+    float2* b2 = b1 + n;                  // only with derivative grids
+    const bool valid = 2 * (pair0 + sub) < P;     // a pair past the last transforms the last again
+    const int pa = valid ? 2 * (pair0 + sub) : (P - 1) / 2 * 2, pb = pa + 1;
     const bool has_b = pb < P;
     // the twiddles and multipliers (tables shared by every pair) are loaded
     // into registers first, so their latency overlaps the partials'
     float2 twv[kPer], mv[kPer], mdv[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-        const int j = tid + q * kBlock;
+        const int j = tid + q * nt;
         if (j < n) {
-            twv[q] = tw[j];
+            if (sub == 0) twv[q] = tw[j];
             mv[q] = mult[j];
             if (grid_d != nullptr) mdv[q] = mult_d[j];
         }
@@ -727,7 +751,7 @@ __device__ __forceinline__ void fftconv_tile(
     const float4* __restrict__ pa4 = reinterpret_cast<const float4*>(partial + (int64_t)pa * g.nr);
     const float4* __restrict__ pb4 = reinterpret_cast<const float4*>(partial + (int64_t)(has_b ? pb : pa) * g.nr);
     const int64_t cstride4 = (int64_t)P * g.nr / 4;
-    for (int r4 = tid; r4 < g.nr / 4; r4 += kBlock) {
+    for (int r4 = tid; r4 < g.nr / 4; r4 += nt) {
         float4 sa = make_float4(0.f, 0.f, 0.f, 0.f), sb = sa;
         for (int c0 = 0; c0 < nchunk; c0 += kInFlight) {
             float4 va[kInFlight], vb[kInFlight];
@@ -756,14 +780,14 @@ __device__ __forceinline__ void fftconv_tile(
     // cells outside [lo, lo + nr) are zero
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-        const int j = tid + q * kBlock;
+        const int j = tid + q * nt;
         if (j < n) {
-            twl[j] = twv[q];
+            if (sub == 0) twl[j] = twv[q];
             if (j < g.lo || j >= g.lo + g.nr) b0[j] = make_float2(0.f, 0.f);
         }
     }
     __syncthreads();
-    float2* spec = fft_lds(b0, b1, n, twl, false);
+    float2* spec = fft_lds(b0, b1, n, twl, false, tid, nt);
     float2* other = (spec == b0) ? b1 : b0;
     const int passes = grid_d ? 2 : 1;
     for (int pass = 0; pass < passes; ++pass) {
@@ -774,16 +798,22 @@ __device__ __forceinline__ void fftconv_tile(
         float2* wb = (passes == 1) ? other : b2;
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-            const int j = tid + q * kBlock;
+            const int j = tid + q * nt;
             if (j < n) wa[j] = cmul(spec[j], pass ? mdv[q] : mv[q]);
         }
         __syncthreads();
-        const float2* res = fft_lds(wa, wb, n, twl, true);
-        for (int r = tid; r < g.nr; r += kBlock) {
-            const float2 v = res[g.lo + r];
-            out[(int64_t)pa * g.nr + r] = v.x;
-            if (has_b) out[(int64_t)pb * g.nr + r] = v.y;
+        const float2* res = fft_lds(wa, wb, n, twl, true, tid, nt);
+        float mx = 0.f;
+        if (valid) {
+            for (int r = tid; r < g.nr; r += nt) {
+                const float2 v = res[g.lo + r];
+                out[(int64_t)pa * g.nr + r] = v.x;
+                if (has_b) out[(int64_t)pb * g.nr + r] = v.y;
+                const float a = fmaxf(fabsf(v.x), fabsf(v.y));
+                mx = (fabsf(v.x) <= 3.4e38f && fabsf(v.y) <= 3.4e38f) ? fmaxf(mx, a) : __builtin_inff();
+            }
         }
+        if (pass && dmax != nullptr) record_abs(dmax, mx, blockIdx.x);
         __syncthreads();
     }
 }
@@ -792,19 +822,21 @@ __global__ __launch_bounds__(kBlock) void fftconv_kernel(
     const float* __restrict__ partial, int nchunk, int P, GridGeom g,
     const float2* __restrict__ tw, const float2* __restrict__ mult,
     const float2* __restrict__ mult_d, float* __restrict__ grid,
-    float* __restrict__ grid_d) {
+    float* __restrict__ grid_d, unsigned* __restrict__ dmax, int nt) {
     extern __shared__ float2 cbuf[];
-    fftconv_tile(cbuf, partial, nchunk, P, g, tw, mult, mult_d, grid, grid_d, blockIdx.x);
+    fftconv_tile(cbuf, partial, nchunk, P, g, tw, mult, mult_d, grid, grid_d, dmax, nt,
+                 blockIdx.x * (kBlock / nt));
 }
 
 hipError_t launch_fftconv(const float* partial, int nchunk, int P, GridGeom g,
                           const float2* tw, const float2* mult,
                           const float2* mult_d, float* grid, float* grid_d,
-                          hipStream_t stream) {
-    dim3 grid_dim((unsigned)((P + 1) / 2));
+                          unsigned* dmax, hipStream_t stream) {
+    const int pairs = (P + 1) / 2, per = fftconv_pairs(g.n);
     const size_t lds = fftconv_lds_bytes(g.n, grid_d != nullptr);
-    hipLaunchKernelGGL(fftconv_kernel, grid_dim, dim3(kBlock), lds, stream, partial,
-                       nchunk, P, g, tw, mult, mult_d, grid, grid_d);
+    hipLaunchKernelGGL(fftconv_kernel, dim3((unsigned)((pairs + per - 1) / per)), dim3(kBlock), lds,
+                       stream, partial, nchunk, P, g, tw, mult, mult_d, grid, grid_d, dmax,
+                       fftconv_threads(g.n));
     return hipGetLastError();
 }
 
@@ -812,6 +844,7 @@ hipError_t launch_fftconv(const float* partial, int nchunk, int P, GridGeom g,
 // gather: one tile = 1024 targets x a group of directions
 // ---------------------------------------------------------------------------
 
+constexpr int kDmaBytes = 64 * 16;   // one wave's 16-byte LDS-direct loads
 constexpr int kGatherTPT = 4;   // consecutive targets per thread (one float4)
 
 // Cells around two points of a thread and the offsets in them: the LDS reads
@@ -880,24 +913,18 @@ __device__ __forceinline__ void gather_tile(
     for (int ps = p_begin; ps < p_end; ps += pstage) {
         const int np = min(pstage, p_end - ps);
         __syncthreads();
-        {   // stage np grids (np * nr floats, nr a multiple of 4)
-            const float4* __restrict__ src4 = reinterpret_cast<const float4*>(grid + (int64_t)ps * g.nr);
-            float4* dst4 = reinterpret_cast<float4*>(lds);
-            const int n4 = np * g.nr / 4;
-            int j = tid;
-            for (; j + 3 * kBlock < n4; j += 4 * kBlock) {
-                const float4 v0 = src4[j], v1 = src4[j + kBlock], v2 = src4[j + 2 * kBlock],
-                             v3 = src4[j + 3 * kBlock];
-                dst4[j] = v0;
-                dst4[j + kBlock] = v1;
-                dst4[j + 2 * kBlock] = v2;
-                dst4[j + 3 * kBlock] = v3;
-            }
-            for (; j < n4; j += kBlock) dst4[j] = src4[j];
+        // stage np grids (np * nr floats, nr a multiple of 4), 1 KB per wave
+        // instruction; lanes past the end write zeros into the padding
+        {
+            const __amdgpu_buffer_rsrc_t gs = buffer_rsrc(grid + (int64_t)ps * g.nr, (int64_t)np * g.nr * 4);
+            for (int off = (tid >> 6) * kDmaBytes; off < np * g.nr * 4; off += (kBlock / 64) * kDmaBytes)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(gs, (lds_void*)(lds + off / 4), 16,
+                                                         (tid & 63) * 16, off, 0, 0);
         }
         float4 cur[kGatherStageMax];
 #pragma unroll
         for (int pp = 0; pp < kGatherStageMax; ++pp) cur[pp] = xv[pp];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // grids and cur have landed
         if (ps + pstage < p_end) load(ps + pstage);
         __syncthreads();
         // two points at a time, their reads one step ahead
@@ -954,6 +981,10 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(
                             ld_t, blockIdx.x, blockIdx.y);
 }
 
+size_t stored_gather_lds(int pstage, int nr) {
+    return ((size_t)pstage * nr * sizeof(float) + kDmaBytes - 1) / kDmaBytes * kDmaBytes;
+}
+
 hipError_t launch_gather(int W, const float* proj, int64_t ld, int64_t M,
                          int P, GridGeom g, const float* grid, int pg,
                          int pstage, const WindowArgs& win, double* spart,
@@ -961,7 +992,7 @@ hipError_t launch_gather(int W, const float* proj, int64_t ld, int64_t M,
                          hipStream_t stream) {
     dim3 grid_dim((unsigned)((M + kBlock * kGatherTPT - 1) / (kBlock * kGatherTPT)),
                   (unsigned)((P + pg - 1) / pg));
-    const size_t lds = (size_t)pstage * g.nr * sizeof(float);
+    const size_t lds = stored_gather_lds(pstage, g.nr);
 #define FS_GATHER(WW, WT)                                                                     \
     hipLaunchKernelGGL((gather_kernel<WW, WT>), grid_dim, dim3(kBlock), lds, stream, proj, ld, \
                        M, P, g, grid, pg, pstage, win, spart, ldm, tout, ld_t)
@@ -986,8 +1017,23 @@ __device__ __forceinline__ void reduce_tile(const double* __restrict__ spart, in
                                             int64_t ldm, int64_t M, double scale,
                                             float* __restrict__ s, int64_t m) {
     if (m >= M) return;
+    // kReduceFlight partial sums in flight (loaded one by one, each waited
+    // for the one before), added in order
+    constexpr int kReduceFlight = 16;
     double acc = 0.0;
-    for (int b = 0; b < nb; ++b) acc += spart[(int64_t)b * ldm + m];
+    int b = 0;
+    for (; b + kReduceFlight <= nb; b += kReduceFlight) {
+        double v[kReduceFlight];
+#pragma unroll
+        for (int q = 0; q < kReduceFlight; ++q) v[q] = spart[(int64_t)(b + q) * ldm + m];
+#pragma unroll
+        for (int q = 0; q < kReduceFlight; ++q) acc += v[q];
+    }
+    double v[kReduceFlight];
+#pragma unroll
+    for (int q = 0; q < kReduceFlight; ++q) v[q] = b + q < nb ? spart[(int64_t)(b + q) * ldm + m] : 0.0;
+#pragma unroll
+    for (int q = 0; q < kReduceFlight; ++q) acc += v[q];
     s[m] = (float)(acc * scale);
 }
 
@@ -1120,7 +1166,6 @@ constexpr int kGatherNB = 8;                               // 16-target batches 
 constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : (W >= 8 ? 3 : 4); }
 // row of the dispatch tables of window width W (-1: none)
 constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
-constexpr int kDmaBytes = 64 * 16;                         // one wave's 16-byte LDS-direct loads
 
 // split_points_kernel: one thread per (tile, lane), all k-blocks; rows >= N
 // and columns >= d are zero.  Also the range check of the fused path: a
@@ -1184,10 +1229,12 @@ __global__ __launch_bounds__(kBlock) void prepare_fused_kernel(
     const float* __restrict__ x, int64_t N, const float* __restrict__ y, int64_t M, int d,
     float scale, int KB, int bx, int by, u32x4* __restrict__ xt, u32x4* __restrict__ yt,
     float norm2_max, int* __restrict__ flag, NormSink xsink, NormSink ysink,
-    const float* __restrict__ w, float* __restrict__ slice_max, float* __restrict__ wscaled) {
+    const float* __restrict__ w, float* __restrict__ slice_max, float* __restrict__ wscaled,
+    unsigned* __restrict__ clear) {
     __shared__ float red[kBlock];
     const int b = blockIdx.x;
     if (b >= bx + by) {
+        if (b == bx + by) clear_abs(clear);
         slice_max_tile(red, w, N, b - bx - by, slice_max, wscaled);
         return;
     }
@@ -1552,15 +1599,19 @@ __global__ __launch_bounds__(kGatherBlock) void gather_fused_kernel(
 // Adjoint in the targets, fused: t'_{m,p}, the derivative grid of direction
 // p interpolated at tau <xi_p, y_m>, is formed in registers exactly as the
 // gather forms t_{m,p}, and back-projected at once on the matrix cores:
-//   G[i][m] += sum over the 16 directions p of a group of (tau xi_p)_i t'_{m,p}
-// as four v_mfma_f32_16x16x4f32 per 16 coordinates.  Lane (c, r) holds t'
-// of directions 4r + i of target c, which is the B operand of MFMA i
-// (k = r, column c) when its A operand holds (tau xi)_{4k + i} (Ab: per
-// group, MFMA i and 16-coordinate chunk dc, lane m + 16k holds
-// tau xi_{16 group + 4k + i}[16 dc + m], zero past P and d).  Workgroup
-// (x, y): kGradTargets targets of tile x, direction range y; writes
-// gpart[(y * ldg + m) * 16 DC + i] (FP32, summed over the ranges by
-// grad_reduce_kernel).
+//   G[i][m] += sum over the 16 directions p of a group of (xi_p)_i t'_{m,p} 2^-e
+// on f16 hi + lo operands, three v_mfma_f32_16x16x16_f16 per 16 coordinates
+// (the cross terms first).  2^e is above the largest derivative cell (dmax),
+// so the scaled t' stay below 4 and their two parts keep all but 2^-25 of it,
+// less than the FFT's own rounding of the grids; the parts of xi are the
+// projection's.  FP32 operands took four v_mfma_f32_16x16x4f32 instead, 128
+// cycles per batch and 16 coordinates against 48: at d = 50 more than the
+// interpolation.  Lane (c, r) holds t' of directions 4r + i of target c, the B
+// operand (column c, k = 4r + i); Ab holds per group, 16-coordinate chunk q
+// and part the A operand, lane m + 16k: (xi_{16 group + 4k + i})_{16 q + m},
+// i < 4 (zero past P and d).  Workgroup (x, y): kGradTargets targets of tile
+// x, direction range y; writes gpart[(y * ldg + m) * 16 DC + i] (FP32, summed
+// over the ranges by grad_reduce_kernel).
 constexpr int kGradNB = 4;                                   // 16-target batches per wave
 constexpr int kGradTargets = kGatherWaves * kGradNB * 16;
 constexpr int kGradMaxDC = kSplitMaxD / 16;
@@ -1568,9 +1619,9 @@ constexpr int kGradMaxDC = kSplitMaxD / 16;
 template <int W, int KB, bool WIDE>
 __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
-    const float* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
-    const float* __restrict__ grid_d, int prange, int stage, WindowArgs win,
-    float* __restrict__ gpart, int64_t ldg) {
+    const uint16_t* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
+    const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, int prange, int stage,
+    WindowArgs win, float* __restrict__ gpart, int64_t ldg) {
     extern __shared__ float gls[];                    // 2 x stage floats
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
@@ -1591,6 +1642,7 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
     for (int b = 0; b < kGradNB; ++b)
 #pragma unroll
         for (int q = 0; q < kGradMaxDC; ++q) gacc[b][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float tscale = ldexpf(1.f, -slots_exponent(dmax, lane));
     const WinEval<W> ev(g, win, pscale);
     SplitOp<KB> dop;
     load_split<KB>(dop, At, p_begin / kFuseDirs, lane);
@@ -1600,26 +1652,37 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // this lane's back-projection operands of the group
-        const float* __restrict__ ag = Ab + (int64_t)(p0 / kFuseDirs) * 4 * DC * 64 + lane;
-        float abv[kGradMaxDC][4];
+        const h4* __restrict__ ag = reinterpret_cast<const h4*>(Ab) + (int64_t)(p0 / kFuseDirs) * DC * 128 + lane;
+        h4 abv[kGradMaxDC][2];
 #pragma unroll
         for (int q = 0; q < kGradMaxDC; ++q)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) abv[q][i] = q < DC ? ag[(i * DC + q) * 64] : 0.f;
+            if (q < DC) {
+                abv[q][0] = ag[q * 128];
+                abv[q][1] = ag[q * 128 + 64];
+            }
         if (!WIDE && p1 < p_end) gather_stage(grid_d, p1, g.nr, gls + (k ^ 1) * stage, wave, lane);
         int base[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) base[i] = (WIDE ? 0 : k * stage) + (4 * r + i) * g.nr - ev.off;
+        h4 thi, tlo;
         gather_group<W, KB, kGradNB>(
             gls, base, dop, yop, ev, win,
             [&](int b, int h, const float (&v)[2]) {
 #pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float x = v[i] * tscale;
+                    const _Float16 hi = (_Float16)x;
+                    thi[2 * h + i] = hi;
+                    tlo[2 * h + i] = (_Float16)(x - (float)hi);
+                }
+                if (h == 0) return;
+#pragma unroll
                 for (int q = 0; q < kGradMaxDC; ++q) {
                     if (q >= DC) break;
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(abv[q][2 * h + i], v[i],
-                                                                          gacc[b][q], 0, 0, 0);
+                    f32x4 a = gacc[b][q];
+                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], tlo, a, 0, 0, 0);
+                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][1], thi, a, 0, 0, 0);
+                    gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], thi, a, 0, 0, 0);
                 }
             },
             [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); });
@@ -1644,10 +1707,12 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
     }
 }
 
-// grad_y[m * d + i] = coef * v[m] * sum over ranges of gpart[(r * ldg + m) * 16 DC + i]
+// grad_y[m * d + i] = coef 2^e * v[m] * sum over ranges of gpart[(r * ldg + m) * 16 DC + i]
 __global__ __launch_bounds__(kBlock) void grad_reduce_kernel(
     const float* __restrict__ gpart, int nrange, int64_t ldg, int DC, int64_t M, int d,
-    float coef, const float* __restrict__ v, float* __restrict__ grad_y) {
+    float coef, const unsigned* __restrict__ dmax, const float* __restrict__ v,
+    float* __restrict__ grad_y) {
+    coef = ldexpf(coef, slots_exponent(dmax, threadIdx.x & 63));
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (e >= M * d) return;
     const int64_t m = e / d;
@@ -1692,9 +1757,10 @@ void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
 
 template <int W, int KB, bool WIDE>
 void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Yt,
-                          int64_t M, const uint16_t* At, const float* Ab, int DC, int P,
-                          const GridGeom& g, float pscale, const float* grid_d, int prange,
-                          int stage, const WindowArgs& win, float* gpart, int64_t ldg) {
+                          int64_t M, const uint16_t* At, const uint16_t* Ab, int DC, int P,
+                          const GridGeom& g, float pscale, const float* grid_d,
+                          const unsigned* dmax, int prange, int stage, const WindowArgs& win,
+                          float* gpart, int64_t ldg) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_grad_fused_kernel<W, KB, WIDE>),
@@ -1703,20 +1769,22 @@ void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint1
         attr_set = true;
     }
     hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, WIDE>), grid, dim3(kGatherBlock), lds, stream,
-                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, prange, stage, win, gpart, ldg);
+                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win, gpart, ldg);
 }
 
 int64_t fused_grad_tile() { return kGradTargets; }
 
+size_t abs_slots_uints() { return kAbsUints; }
+
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
-                             const float* Ab, int P, GridGeom g, float pscale,
-                             const float* grid_d, int prange, const WindowArgs& win,
-                             float* gpart, int64_t ldg, float coef, const float* v,
+                             const uint16_t* Ab, int P, GridGeom g, float pscale,
+                             const float* grid_d, const unsigned* dmax, int prange,
+                             const WindowArgs& win, float* gpart, int64_t ldg, float coef, const float* v,
                              float* grad_y, hipStream_t stream) {
     if (!fused_supported(d, g.nr) || prange % kFuseDirs != 0 || M > ldg) return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
-                       const float*, int, int, const GridGeom&, float, const float*, int, int,
-                       const WindowArgs&, float*, int64_t);
+                       const uint16_t*, int, int, const GridGeom&, float, const float*,
+                       const unsigned*, int, int, const WindowArgs&, float*, int64_t);
     static const L t[2][5][2] = {
         {{launch_gather_grad_t<3, 1, false>, launch_gather_grad_t<3, 2, false>},
          {launch_gather_grad_t<4, 1, false>, launch_gather_grad_t<4, 2, false>},
@@ -1736,12 +1804,13 @@ hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const 
     dim3 gd((unsigned)((M + kGradTargets - 1) / kGradTargets), (unsigned)nrange);
     const bool wide = fused_wide(g.nr);
     t[wide][wi][split_kblocks(d) - 1](gd, (size_t)(wide ? 1 : 2) * stage * sizeof(float), stream,
-                                      Yt, M, At, Ab, DC, P, g, pscale, grid_d, prange, stage, win,
+                                      Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win,
                                       gpart, ldg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((M * d + kBlock - 1) / kBlock)),
-                       dim3(kBlock), 0, stream, gpart, nrange, ldg, DC, M, d, coef, v, grad_y);
+                       dim3(kBlock), 0, stream, gpart, nrange, ldg, DC, M, d, coef, dmax, v,
+                       grad_y);
     return hipGetLastError();
 }
 
@@ -1774,20 +1843,20 @@ hipError_t launch_split_points(const float* Z, int64_t N, int d, float scale, ui
 hipError_t launch_prepare_fused(const float* x, int64_t N, const float* y, int64_t M, int d,
                                 float scale, uint16_t* xt, uint16_t* yt, float norm2_max, int* flag,
                                 unsigned* norms, int64_t prefix, const float* w, float* slice_max,
-                                float* wscaled, hipStream_t stream) {
+                                float* wscaled, unsigned* clear, hipStream_t stream) {
     auto blocks = [](int64_t n) { return (int)((n + 16 * kPrepTiles - 1) / (16 * kPrepTiles)); };
     const int bx = blocks(N), by = y ? blocks(M) : 0, bs = (int)((N + kSlice - 1) / kSlice);
     hipLaunchKernelGGL(prepare_fused_kernel, dim3((unsigned)(bx + by + bs)), dim3(kBlock), 0, stream,
                        x, N, y, M, d, scale, split_kblocks(d), bx, by, reinterpret_cast<u32x4*>(xt),
                        reinterpret_cast<u32x4*>(yt), norm2_max, flag, NormSink{norms, prefix},
-                       NormSink{norms + kNormRoleUints, 0}, w, slice_max, wscaled);
+                       NormSink{norms + kNormRoleUints, 0}, w, slice_max, wscaled, clear);
     return hipGetLastError();
 }
 
 hipError_t launch_slice_max(const float* w, int64_t N, float* slice_max, float* wscaled,
-                            hipStream_t stream) {
+                            unsigned* clear, hipStream_t stream) {
     hipLaunchKernelGGL(slice_max_kernel, dim3((unsigned)((N + kSlice - 1) / kSlice)), dim3(kBlock),
-                       0, stream, w, N, slice_max, wscaled);
+                       0, stream, w, N, slice_max, wscaled, clear);
     return hipGetLastError();
 }
 
@@ -1957,7 +2026,7 @@ __global__ __launch_bounds__(kBlock) void batch_fftconv_kernel(
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
         fftconv_tile(cbuf, pr.partial, pr.nchunk, P, pr.g, pr.tw, pr.mult, nullptr, pr.grid,
-                     nullptr, tk.a);
+                     nullptr, nullptr, fftconv_threads(pr.g.n), tk.a);
     }
 }
 

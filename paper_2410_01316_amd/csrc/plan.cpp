@@ -470,7 +470,8 @@ struct fastsum_plan_s {
     uint16_t* xt = nullptr;        // split-f16 tiles of the sources / targets (fused plans)
     uint16_t* yt = nullptr;
     double xi_norm_max = 1.0;      // max_p |xi_p| (range check of the fused path)
-    float* ab = nullptr;           // back-projection operands of the fused adjoint
+    uint16_t* ab = nullptr;        // back-projection operands of the fused adjoint
+    unsigned* dmax = nullptr;      // largest |grid_d|, |grid_wd| (two sets of slots)
     float* gpart = nullptr;        // its per-range partial sums, kGradMaxRanges x ldg x 16 DC
     int64_t ldg = 0;
     // stored projections by the tile GEMM (BF16, or FP32 with d > 64):
@@ -541,7 +542,7 @@ void free_plan(fastsum_plan_s* p) {
     for (auto e : p->pool) (void)hipEventDestroy(e);
     void* bufs[] = {p->A, p->A64, p->at, p->xt, p->yt, p->gdt, p->gpt, p->xproj, p->yproj, p->partial, p->grid, p->grid_d,
                     p->grid_w, p->spart, p->tprime, p->mult, p->mult_d, p->tw, p->flag,
-                    p->slice_max, p->wscaled, p->ab, p->gpart, p->grid_wd, p->tout, p->keys,
+                    p->slice_max, p->wscaled, p->ab, p->dmax, p->gpart, p->grid_wd, p->tout, p->keys,
                     p->keys_out, p->vals, p->sort_temp, p->sv, p->sty, p->stx, p->norms,
                     p->xit, p->bp_tiles, p->bp_scratch,
                     p->sti, p->styb, p->styo, p->stxb, p->stxo};
@@ -624,7 +625,7 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
     {
         PhaseTimer t(pl, FASTSUM_PHASE_FFTCONV, st);
         FS_TRY(launch_fftconv(pl->partial, nchunk, P, pl->geom, pl->tw, pl->mult, pl->mult_d,
-                              grid, grid_d, st));
+                              grid, grid_d, nullptr, st));
     }
     const int pg = gather_group(Mtgt, P, pl->pstage);
     const int ng = (P + pg - 1) / pg;
@@ -653,8 +654,9 @@ int64_t prefix_rows(const float* x, int64_t N, const float* y, int64_t M) {
 // Spread (sources xt, weights w in pl->wscaled), FFT convolution (and the derivative grids
 // when grid_d is given), gather at the targets yt and reduction into out:
 // one sliced Fourier sum on split operand tiles.
-fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, const uint16_t* yt, int64_t M, float* out, float* grid, float* grid_d,
-                         const BoundCheck& bc, hipStream_t st) {
+fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, const uint16_t* yt,
+                         int64_t M, float* out, float* grid, float* grid_d,
+                         unsigned* dmax, const BoundCheck& bc, hipStream_t st) {
     const int P = pl->P;
     const float pscale = (float)(pl->r.tau * pl->r.p.R);
     int64_t chunk_len = 0;
@@ -668,7 +670,8 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, cons
     {
         PhaseTimer t(pl, FASTSUM_PHASE_FFTCONV, st);
         FS_TRY(launch_fftconv(pl->partial, nchunk, P, pl->geom, pl->tw, pl->mult,
-                              grid_d ? pl->mult_d : nullptr, grid, grid_d, st));
+                              grid_d ? pl->mult_d : nullptr, grid, grid_d, grid_d ? dmax : nullptr,
+                              st));
     }
     const int prange = pl->tune_dir_range > 0 ? pl->tune_dir_range
                                               : fused_dir_range(M, P, pl->gather_slots, pl->geom.nr, pl->Wg);
@@ -698,10 +701,10 @@ fastsum_status fused_pass(fastsum_plan_s* pl, const float* x, const float* w, in
         PhaseTimer t(pl, FASTSUM_PHASE_PROJECT, st);
         FS_TRY(launch_prepare_fused(x, N, y != x ? y : nullptr, M, pl->d, inv_r, pl->xt, pl->yt,
                                     norm2_max, pl->flag, pl->norms, prefix_rows(x, N, y, M), w,
-                                    pl->slice_max, pl->wscaled, st));
+                                    pl->slice_max, pl->wscaled, pl->dmax, st));
     }
     return fused_sum(pl, pl->xt, N, yt, M, out, pl->grid,
-                     (pl->r.p.flags & FASTSUM_FLAG_GRAD) ? pl->grid_d : nullptr, bc, st);
+                     (pl->r.p.flags & FASTSUM_FLAG_GRAD) ? pl->grid_d : nullptr, pl->dmax, bc, st);
 }
 
 // direction ranges of the fused adjoint gather: at least three rounds of
@@ -972,7 +975,8 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
         ok = dev_alloc(&pl->grid_d, grid_cells) && dev_alloc(&pl->grid_w, grid_cells) &&
              dev_alloc(&pl->grid_wd, grid_cells) && dev_alloc(&pl->tout, (size_t)cap) &&
              dev_alloc(&pl->mult_d, (size_t)n) &&
-             (pl->fused ? dev_alloc(&pl->ab, (size_t)gtiles * 4 * DC * 64) &&
+             (pl->fused ? dev_alloc(&pl->ab, (size_t)gtiles * DC * 512) &&
+                              dev_alloc(&pl->dmax, 2 * abs_slots_uints()) &&
                               dev_alloc(&pl->gpart, (size_t)kGradMaxRanges * pl->ldg * 16 * DC)
                         : dev_alloc(&pl->tprime, (size_t)P * std::max(pl->ld_x, pl->ld_y)));
     if (ok && grad && pl->d > kSplitMaxD) {
@@ -1015,20 +1019,24 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
         if (r.p.proj == FASTSUM_PROJ_BF16) bf16_dirs_host(A, pl->dpad, pl->d, P, gdt);
         else split_dirs_host(xi, pl->d, P, gdt);
     }
-    // back-projection operands: group g, MFMA i, chunk q, lane k*16 + m
-    std::vector<float> ab;
+    // back-projection operands: group g, chunk q, part, lane k*16 + m, i
+    std::vector<uint16_t> ab;
     if (pl->ab) {
-        ab.assign((size_t)gtiles * 4 * DC * 64, 0.f);
+        ab.assign((size_t)gtiles * DC * 512, 0);
         for (int64_t g = 0; g < gtiles; ++g)
-            for (int i = 0; i < 4; ++i)
-                for (int q = 0; q < DC; ++q)
-                    for (int k = 0; k < 4; ++k)
-                        for (int m = 0; m < 16; ++m) {
+            for (int q = 0; q < DC; ++q)
+                for (int k = 0; k < 4; ++k)
+                    for (int m = 0; m < 16; ++m)
+                        for (int i = 0; i < 4; ++i) {
                             const int64_t p = 16 * g + 4 * k + i;
                             const int col = 16 * q + m;
-                            if (p < P && col < pl->d)
-                                ab[(((size_t)g * 4 + i) * DC + q) * 64 + k * 16 + m] =
-                                    A[(size_t)p * pl->dpad + col];
+                            if (p >= P || col >= pl->d) continue;
+                            const float v = xi[(size_t)col * P + p];
+                            const _Float16 hi = (_Float16)v;
+                            const _Float16 lo = (_Float16)(v - (float)hi);
+                            const size_t at = ((size_t)g * DC + q) * 512 + 4 * (k * 16 + m) + i;
+                            std::memcpy(&ab[at], &hi, 2);
+                            std::memcpy(&ab[at + 256], &lo, 2);
                         }
     }
     pl->xi_norm_max = 0.0;
@@ -1044,7 +1052,7 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
     if (e == hipSuccess && pl->at)
         e = hipMemcpyAsync(pl->at, at.data(), at.size() * sizeof(uint16_t), hipMemcpyHostToDevice, hs);
     if (e == hipSuccess && pl->ab)
-        e = hipMemcpyAsync(pl->ab, ab.data(), ab.size() * sizeof(float), hipMemcpyHostToDevice, hs);
+        e = hipMemcpyAsync(pl->ab, ab.data(), ab.size() * sizeof(uint16_t), hipMemcpyHostToDevice, hs);
     if (e == hipSuccess && pl->gdt)
         e = hipMemcpyAsync(pl->gdt, gdt.data(), gdt.size() * 2, hipMemcpyHostToDevice, hs);
     if (e == hipSuccess && pl->xit)
@@ -1160,26 +1168,29 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
     if (pl->fused) {
         const uint16_t* yt = pl->last_same ? pl->xt : pl->yt;
         const float pscale = (float)(pl->r.tau * pl->r.p.R);
+        const float fcoef = (float)(pl->r.tau / P);
         if (grad_y) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, yt, M, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
-                                     pl->grid_d, fused_grad_range(M, P, pl->gather_slots),
-                                     pl->dwin, pl->gpart, pl->ldg, coef, grad_s, grad_y, st));
+                                     pl->grid_d, pl->dmax, fused_grad_range(M, P, pl->gather_slots),
+                                     pl->dwin, pl->gpart, pl->ldg, fcoef, grad_s, grad_y, st));
         }
         if (grad_w || grad_x) {
             {
                 PhaseTimer t(pl, FASTSUM_PHASE_SPREAD, st);
-                FS_TRY(launch_slice_max(grad_s, M, pl->slice_max, pl->wscaled, st));
+                FS_TRY(launch_slice_max(grad_s, M, pl->slice_max, pl->wscaled,
+                                        grad_x ? pl->dmax + abs_slots_uints() : nullptr, st));
             }
             fastsum_status r = fused_sum(pl, yt, M, pl->xt, N, uout, pl->grid_w,
-                                         grad_x ? pl->grid_wd : nullptr, BoundCheck{}, st);
+                                         grad_x ? pl->grid_wd : nullptr,
+                                         pl->dmax + abs_slots_uints(), BoundCheck{}, st);
             if (r != FASTSUM_OK) return r;
         }
         if (grad_x) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, pl->xt, N, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
-                                     pl->grid_wd, fused_grad_range(N, P, pl->gather_slots),
-                                     pl->dwin, pl->gpart, pl->ldg, coef, pl->last_w, grad_x,
+                                     pl->grid_wd, pl->dmax + abs_slots_uints(), fused_grad_range(N, P, pl->gather_slots),
+                                     pl->dwin, pl->gpart, pl->ldg, fcoef, pl->last_w, grad_x,
                                      st));
         }
         return FASTSUM_OK;
