@@ -40,16 +40,19 @@ template <> struct WinShape<8> { static constexpr int NE = 4, NO = 4; };  // deg
 template <int W>
 struct WinEval {
     float n, half_n;
-    int off, top;                 // floor(u) of the points whose first tap is cell 0, cell nr - W
+    int off;                      // floor(u) of the points whose first tap is cell 0
+    int first, last;              // floor(u) is clamped to this range (tap0)
     float e_lead[(W + 1) / 2], o_lead[W / 2];
-    // pscale: the kernel's projection values are x~ / pscale
+    // pscale: the kernel's projection values are x~ / pscale; spare: spare
+    // cells on each side of the stored ones that points may address
     __device__ __forceinline__ WinEval(const GridGeom& g, const WindowArgs& win,
-                                       float pscale = 1.f) {
+                                       float pscale = 1.f, int spare = 0) {
         constexpr int NE = WinShape<W>::NE, NO = WinShape<W>::NO;
         n = (float)g.n * pscale;
         half_n = 0.5f * (float)g.n + ((W % 2) ? 0.5f : 0.f);
         off = (W - 1) / 2 + g.lo;
-        top = off + g.nr - W;
+        first = off - spare;
+        last = off + g.nr - W + spare;
 #pragma unroll
         for (int t = 0; t < (W + 1) / 2; ++t) {
             e_lead[t] = win.even[t][NE - 1];
@@ -101,8 +104,9 @@ __device__ __forceinline__ void window_weights(float sp, const WindowArgs& win,
 // 1/2): returns floor(u), which is the first tap plus ev.off (callers take
 // ev.off from the grid's base, where it costs nothing per point), clamped so
 // that no point (outside the bound, infinite or NaN) addresses a cell outside
-// the stored range, and sets sp = frac(u) - 1/2.  Points inside the bound are
-// never clamped (the stored range has a margin of a cell on each side).
+// the stored range and its spare cells, and sets sp = frac(u) - 1/2.  Points
+// inside the bound are never clamped (the stored range has a margin of a cell
+// on each side).
 template <int W>
 __device__ __forceinline__ int tap0(float xt, const WinEval<W>& ev, float& sp) {
     const float u = fmaf(xt, ev.n, ev.half_n);
@@ -110,7 +114,7 @@ __device__ __forceinline__ int tap0(float xt, const WinEval<W>& ev, float& sp) {
     int j;
     asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(j) : "v"(u));
     int b;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(b) : "v"(j), "v"(ev.off), "v"(ev.top));
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(b) : "v"(j), "v"(ev.first), "v"(ev.last));
     return b;
 }
 
@@ -467,29 +471,50 @@ __global__ __launch_bounds__(kBlock) void slice_max_kernel(
     slice_max_tile(red, w, N, blockIdx.x, slice_max, wscaled);
 }
 
-// Adds ws * weight_t, rounded to the nearest integer (ties to even), to the
-// W cells of a point.  The rounding must be unbiased: ws * weight_t has only
-// a few fraction bits at the top of the fixed-point range, so exact halves
-// are common and rounding them up would add a bias that grows with the
-// number of sources.
-// Cell j of the grid lies at lds32[base + (j << LOGR)].
-template <int W, int LOGR = 0>
+// floor(x + 1/2) in one instruction (rounding to even takes two); a NaN gives
+// +-2^31, so the spread keeps NaN weights out (slice_max_tile) and lets
+// points that are not finite fall into spare cells (kSpareCells)
+__device__ __forceinline__ int round_half_up(float x) {
+    int i;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+    return i;
+}
+
+// Adds ws * weight_t, rounded to the nearest integer, to the W cells of a
+// point.  The rounding must be unbiased: ws * weight_t has only a few
+// fraction bits at the top of the fixed-point range, so exact halves are
+// common and rounding them all up would add a bias that grows with the number
+// of sources.  Halves go up for one half of the points and down for the
+// other (NEG: the negated contribution is rounded and subtracted; callers
+// alternate), which leaves no bias over the points.  Cell j of the grid lies
+// at lds32[base + (j << LOGR)].
+template <int W, bool NEG, int LOGR = 0>
 __device__ __forceinline__ void spread_point(float xt, float ws, const WinEval<W>& ev,
                                              const WindowArgs& win, int* lds32, int base) {
     float sp;
     int* __restrict__ c = lds32 + (base + (tap0<W>(xt, ev, sp) << LOGR));
+    if (NEG) ws = -ws;
     const float q = sp * sp, spw = sp * ws;
+    auto add = [&](int t, float v) {
+        if (NEG) atomicSub(c + (t << LOGR), round_half_up(v));
+        else atomicAdd(c + (t << LOGR), round_half_up(v));
+    };
 #pragma unroll
     for (int t = 0; t < W / 2; ++t) {
         float e, o;
         window_pair<W>(q, t, win, ev, e, o);
         e *= ws;
-        atomicAdd(c + (t << LOGR), __float2int_rn(fmaf(o, spw, e)));
-        atomicAdd(c + ((W - 1 - t) << LOGR), __float2int_rn(fmaf(-o, spw, e)));
+        add(t, fmaf(o, spw, e));
+        add(W - 1 - t, fmaf(-o, spw, e));
     }
-    if constexpr (W % 2)
-        atomicAdd(c + ((W / 2) << LOGR), __float2int_rn(window_even<W>(q, W / 2, win, ev) * ws));
+    if constexpr (W % 2) add(W / 2, window_even<W>(q, W / 2, win, ev) * ws);
 }
+
+// Grids in LDS have W spare cells on each side that are never read: a point
+// outside the stored range (infinite and NaN ones among them; all are
+// reported by the bound check) adds to those.
+template <int W> constexpr int kSpareCells = W;
+constexpr int kMaxSpareCells = 8;
 
 // Spread of stored projections: each cell is kept in 2^kSpreadLogR copies,
 // lane l adding to copy l mod 2^kSpreadLogR, and the copies are added as
@@ -499,6 +524,7 @@ __device__ __forceinline__ void spread_point(float xt, float ws, const WinEval<W
 // addresses (a spread of +-20 cells ran at 773 cycles per 256 pairs against
 // 515 for +-100; the window arithmetic alone takes 354).
 constexpr int kSpreadLogR = 2;
+constexpr int kHeldSlices = 3;     // 2 copies x 3 slices x 1024 x 2^18 x 1.01 < 2^31
 
 template <int W>
 __device__ __forceinline__ void spread_tile(
@@ -507,9 +533,9 @@ __device__ __forceinline__ void spread_tile(
     const float* __restrict__ slice_max, const WindowArgs& win, float* __restrict__ partial,
     int p, int c) {
     static_assert(kSpreadLogR == 2, "a flush reads a cell's copies as one int4");
-    int* lds32 = reinterpret_cast<int*>(lds_raw);             // nr cells x 4 copies
-    int4* cells4 = reinterpret_cast<int4*>(lds_raw);
-    const WinEval<W> ev(g, win);
+    int4* cells4 = reinterpret_cast<int4*>(lds_raw) + kSpareCells<W>;   // nr cells x 4 copies
+    int* lds32 = reinterpret_cast<int*>(cells4);
+    const WinEval<W> ev(g, win, 1.f, kSpareCells<W>);
     const int base = (int)(threadIdx.x & 3) - 4 * ev.off;
     float acc[kSpreadAcc];
 #pragma unroll
@@ -533,23 +559,34 @@ __device__ __forceinline__ void spread_tile(
     __syncthreads();               // LDS may still be read by a previous tile
     for (int j = threadIdx.x; j < g.nr; j += kBlock) cells4[j] = make_int4(0, 0, 0, 0);
     __syncthreads();
+    int held = 0;                  // slices in the cells
     for (int64_t s0 = i0; s0 < i1; s0 += kSlice) {
+        const int k = slice_exponent(slice_max[s0 / kSlice]);
 #pragma unroll
         for (int q = 0; q < kSliceSteps; ++q) {
-            spread_point<W, kSpreadLogR>(xv[q].x, wv[q].x, ev, win, lds32, base);
-            spread_point<W, kSpreadLogR>(xv[q].y, wv[q].y, ev, win, lds32, base);
-            spread_point<W, kSpreadLogR>(xv[q].z, wv[q].z, ev, win, lds32, base);
-            spread_point<W, kSpreadLogR>(xv[q].w, wv[q].w, ev, win, lds32, base);
+            spread_point<W, false, kSpreadLogR>(xv[q].x, wv[q].x, ev, win, lds32, base);
+            spread_point<W, true, kSpreadLogR>(xv[q].y, wv[q].y, ev, win, lds32, base);
+            spread_point<W, false, kSpreadLogR>(xv[q].z, wv[q].z, ev, win, lds32, base);
+            spread_point<W, true, kSpreadLogR>(xv[q].w, wv[q].w, ev, win, lds32, base);
         }
-        const float unscale = ldexpf(1.f, -slice_exponent(slice_max[s0 / kSlice]));
-        if (s0 + kSlice < i1) load(s0 + kSlice);
+        const bool last = s0 + kSlice >= i1;
+        if (!last) load(s0 + kSlice);
+        // A copy takes a quarter of each slice, at most 1024 terms below
+        // 2^18 * 1.01, so the four copies of a cell hold kHeldSlices slices of
+        // one scale: flushed when the scale changes or they are full.
+        if (++held < kHeldSlices && !last &&
+            slice_exponent(slice_max[s0 / kSlice + 1]) == k) continue;
+        held = 0;
+        const float unscale = ldexpf(1.f, -k);
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < kSpreadAcc; ++q) {
             const int j = threadIdx.x + q * kBlock;
             if (j < g.nr) {
                 const int4 v = cells4[j];
-                acc[q] = fmaf((float)(v.x + v.y + v.z + v.w), unscale, acc[q]);
+                // pairs of copies fit an integer, all four may not
+                acc[q] = fmaf((float)(v.x + v.y), unscale, acc[q]);
+                acc[q] = fmaf((float)(v.z + v.w), unscale, acc[q]);
                 cells4[j] = make_int4(0, 0, 0, 0);
             }
         }
@@ -1158,11 +1195,18 @@ constexpr int kFuseMaxCells = kFuseAcc * kSpreadBlock;     // kFuseDirs * nr <= 
 // T = 0.45): twice the accumulators, one workgroup per CU, and the gathers
 // stage one group's grids at a time (two would not fit in LDS)
 constexpr int kFuseAccWide = 64;
+// grids with copies (at most kCopyMaxCells cells): fewer accumulators
+constexpr int kFuseAccCopies = 8;
 constexpr int kFuseMaxCellsWide = kFuseAccWide * kSpreadBlock;
+// LDS of the widest spread: its cells and spare cells
+constexpr int kSpreadMaxLds = (kFuseMaxCellsWide + 2 * kMaxSpareCells * 16) * (int)sizeof(int);
 constexpr int kGatherBlock = 512;                          // 8 waves, one workgroup per CU
 constexpr int kGatherWaves = kGatherBlock / 64;
 constexpr int kGatherNB = 8;                               // 16-target batches per wave
-// wide grids: fewer batches (registers; W = 8 takes three)
+// wide grids: fewer batches (registers; W = 8 takes three).  Eight batches
+// fit at up to five taps, but 512-target tiles fill the rounds better: the
+// MMD energy gather (d = 20, M = 2e5, P = 512) took 198 us with eight, 180
+// with four
 constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : (W >= 8 ? 3 : 4); }
 // row of the dispatch tables of window width W (-1: none)
 constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
@@ -1329,22 +1373,32 @@ __device__ __forceinline__ f32x4 split_mfma(const SplitOp<KB>& a, const SplitOp<
     return acc;
 }
 
-// Cells of a fused spread workgroup: whole groups of kFlushGroup per thread,
-// so that a flush needs no bounds checks.
-constexpr int kFlushGroup = 8;
+// Cells of a fused spread workgroup lie cell-major, the 16 directions of a
+// cell side by side: the lanes of a wave that hold different directions never
+// meet in a bank, however the points are concentrated (direction-major, the
+// directions' grids start 64 banks apart at nr = 1856 and lie within 8 banks
+// of each other at nr = 88).  Narrow grids keep four copies of each cell,
+// one per group of 16 lanes: then no two lanes of a wave share a bank or a
+// cell.  A copy takes a quarter of the points, so kHeldSlices slices of one
+// scale are held before a flush (as in spread_tile).
+constexpr int kCopyMaxCells = 160;                 // nr with copies: 48 KB, three workgroups per CU
+constexpr bool spread_copies(int nr) { return nr <= kCopyMaxCells; }
+// accumulators (16 nr / kSpreadBlock) are flushed in groups per thread without
+// bounds checks: whole groups of cells
+constexpr int flush_group(bool copies) { return copies ? 2 : 8; }
 constexpr int spread_cells(int nr) {
-    constexpr int unit = kFlushGroup * kSpreadBlock;
+    const int unit = flush_group(spread_copies(nr)) * kSpreadBlock;
     return (kFuseDirs * nr + unit - 1) / unit * unit;
 }
 
 // Spread with projections computed in registers.  A workgroup owns the 16
 // directions 16 dgroup .. 16 dgroup + 15 and the sources of chunk `chunk`; grids are
-// kFuseDirs x nr int32 cells in LDS (fixed point per slice as in
+// nr x kFuseDirs int32 cells (COPIES: x 4) in LDS (fixed point per slice as in
 // spread_tile) flushed after every slice into per-thread FP32 accumulators.
 // v = <xi_p, x_n / R>; x~ = pscale v with pscale = tau R.  The range check
 // of these points was done when they were split; w holds the weights in
 // their slices' fixed point (slice_max_tile).
-template <int W, int KB, int ACC>
+template <int W, int KB, int ACC, bool COPIES>
 __device__ __forceinline__ void spread_fused_body(
     int* cells, const uint16_t* __restrict__ Xt, int64_t N, const uint16_t* __restrict__ At,
     const float* __restrict__ w, int P, const GridGeom& g, float pscale, int64_t chunk_len,
@@ -1359,10 +1413,18 @@ __device__ __forceinline__ void spread_fused_body(
     float acc[ACC];
 #pragma unroll
     for (int q = 0; q < ACC; ++q) acc[q] = 0.f;
-    for (int j = tid; j < ncell; j += kSpreadBlock) cells[j] = 0;
+    // cell j of direction p0 + c: entry 16 j + c, copy r of it if COPIES
+    constexpr int LOGS = COPIES ? 6 : 4, kFlushGroup = flush_group(COPIES);
+    cells += kSpareCells<W> << LOGS;
+    int4* cells4 = reinterpret_cast<int4*>(cells);
+    if constexpr (COPIES) {
+        for (int j = tid; j < ncell; j += kSpreadBlock) cells4[j] = make_int4(0, 0, 0, 0);
+    } else {
+        for (int j = tid; j < ncell; j += kSpreadBlock) cells[j] = 0;
+    }
     __syncthreads();
-    const WinEval<W> ev(g, win, pscale);
-    const int gcol = c * g.nr - ev.off;               // grid of direction p0 + c
+    const WinEval<W> ev(g, win, pscale, kSpareCells<W>);
+    const int gcol = (COPIES ? 4 * c + r : c) - (ev.off << LOGS);
     const int64_t i0 = (int64_t)chunk * chunk_len;   // multiple of 16
     const int len = (int)min(N - i0, chunk_len);           // <= 2^20 sources
     // the chunk's tiles and a few beyond (prefetch), within the tile array;
@@ -1377,9 +1439,10 @@ __device__ __forceinline__ void spread_fused_body(
     auto batch = [&](const SplitOp<KB>& xo, const u32x4& wv) {
         // C[point][dir]: lane holds points 4r + i of direction c
         const f32x4 pr = split_mfma<KB>(xo, dop, f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            spread_point<W>(pr[i], __uint_as_float(wv[i]), ev, win, cells, gcol);
+        spread_point<W, false, LOGS>(pr[0], __uint_as_float(wv[0]), ev, win, cells, gcol);
+        spread_point<W, true, LOGS>(pr[1], __uint_as_float(wv[1]), ev, win, cells, gcol);
+        spread_point<W, false, LOGS>(pr[2], __uint_as_float(wv[2]), ev, win, cells, gcol);
+        spread_point<W, true, LOGS>(pr[3], __uint_as_float(wv[3]), ev, win, cells, gcol);
     };
     auto load = [&](SplitOp<KB>& xo, u32x4& wv, int n0) {
         wv = __builtin_amdgcn_raw_buffer_load_b128(ws, (n0 + 4 * r) * 4, 0, 0);
@@ -1387,9 +1450,10 @@ __device__ __forceinline__ void spread_fused_body(
     };
     // the chunk's pieces inside fixed-point slices, [s0, s1) relative to i0
     // (chunks need not start on a slice; every piece starts on a batch of 16)
+    int held = 0;                                     // slices in the cells
     for (int s0 = 0; s0 < len;) {
         const int64_t slice = (i0 + s0) / kSlice;
-        const float unscale = ldexpf(1.f, -slice_exponent(slice_max[slice]));
+        const int k = slice_exponent(slice_max[slice]);
         const int s1 = (int)min((int64_t)len, (slice + 1) * kSlice - i0);
         // batches of 16 sources, wave-strided, two in flight: while one is
         // spread the other's operands load.  Each buffer is reloaded only
@@ -1412,31 +1476,54 @@ __device__ __forceinline__ void spread_fused_body(
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) asm volatile("" ::"v"(xb.hi[kb]), "v"(xb.lo[kb]));
         }
+        s0 = s1;
+        if constexpr (COPIES) {
+            if (++held < kHeldSlices && s1 < len && slice_exponent(slice_max[slice + 1]) == k) continue;
+            held = 0;
+        }
+        const float unscale = ldexpf(1.f, -k);
         __syncthreads();
         // kFlushGroup cells in flight at once: one by one, each waited for
         // its LDS read
 #pragma unroll
         for (int q0 = 0; q0 < ACC; q0 += kFlushGroup) {
             if (q0 * kSpreadBlock >= ncell) break;
-            int v[kFlushGroup];
+            if constexpr (COPIES) {
+                int4 v[kFlushGroup];
 #pragma unroll
-            for (int q = 0; q < kFlushGroup; ++q) v[q] = cells[tid + (q0 + q) * kSpreadBlock];
+                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells4[tid + (q0 + q) * kSpreadBlock];
 #pragma unroll
-            for (int q = 0; q < kFlushGroup; ++q) cells[tid + (q0 + q) * kSpreadBlock] = 0;
+                for (int q = 0; q < kFlushGroup; ++q)
+                    cells4[tid + (q0 + q) * kSpreadBlock] = make_int4(0, 0, 0, 0);
 #pragma unroll
-            for (int q = 0; q < kFlushGroup; ++q)
-                acc[q0 + q] = fmaf((float)v[q], unscale, acc[q0 + q]);
+                for (int q = 0; q < kFlushGroup; ++q) {
+                    acc[q0 + q] = fmaf((float)(v[q].x + v[q].y), unscale, acc[q0 + q]);
+                    acc[q0 + q] = fmaf((float)(v[q].z + v[q].w), unscale, acc[q0 + q]);
+                }
+            } else {
+                int v[kFlushGroup];
+#pragma unroll
+                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells[tid + (q0 + q) * kSpreadBlock];
+#pragma unroll
+                for (int q = 0; q < kFlushGroup; ++q) cells[tid + (q0 + q) * kSpreadBlock] = 0;
+#pragma unroll
+                for (int q = 0; q < kFlushGroup; ++q)
+                    acc[q0 + q] = fmaf((float)v[q], unscale, acc[q0 + q]);
+            }
         }
         __syncthreads();
-        s0 = s1;
     }
-    // cells j = dir * nr + (cell - lo): the block's rows of partial are contiguous
-    const int nvalid = min(kFuseDirs, P - p0) * g.nr;
-    float* __restrict__ dst = partial + ((int64_t)chunk * P + p0) * g.nr;
+    // the sums back through LDS (entry 16 j + c), so that each direction's
+    // row of partial is written in order
+    float* sums = reinterpret_cast<float*>(cells);
 #pragma unroll
-    for (int q = 0; q < ACC; ++q) {
-        const int j = tid + q * kSpreadBlock;
-        if (j < nvalid) dst[j] = acc[q];
+    for (int q = 0; q < ACC; ++q)
+        if (q * kSpreadBlock < ncell) sums[tid + q * kSpreadBlock] = acc[q];
+    __syncthreads();
+    const int nvalid = min(kFuseDirs, P - p0);
+    for (int dir = wave; dir < nvalid; dir += kSpreadWaves) {
+        float* __restrict__ dst = partial + ((int64_t)chunk * P + p0 + dir) * g.nr;
+        for (int j = lane; j < g.nr; j += 64) dst[j] = sums[j * kFuseDirs + dir];
     }
 }
 
@@ -1447,7 +1534,7 @@ __global__ __launch_bounds__(kSpreadBlock) void spread_fused_kernel(
     const float* __restrict__ w, int P, GridGeom g, float pscale, int64_t chunk_len,
     const float* __restrict__ slice_max, WindowArgs win, float* __restrict__ partial) {
     extern __shared__ int cells[];
-    spread_fused_body<W, KB, ACC>(cells, Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win,
+    spread_fused_body<W, KB, ACC, ACC == kFuseAccCopies>(cells, Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win,
                              partial, blockIdx.x, blockIdx.y);
 }
 
@@ -1732,7 +1819,7 @@ void launch_spread_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&spread_fused_kernel<W, KB, ACC>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  ACC * kSpreadBlock * (int)sizeof(int));
+                                  kSpreadMaxLds);
         attr_set = true;
     }
     hipLaunchKernelGGL((spread_fused_kernel<W, KB, ACC>), grid, dim3(kSpreadBlock), lds, stream,
@@ -1867,12 +1954,21 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
     const bool wide = fused_wide(nr);
     // occupancy is set by LDS and registers; the larger operand shape
     // stands for both
-    const void* sks[2][5] = {
-        {(const void*)&spread_fused_kernel<3, 2, kFuseAcc>, (const void*)&spread_fused_kernel<4, 2, kFuseAcc>,
-         (const void*)&spread_fused_kernel<5, 2, kFuseAcc>, (const void*)&spread_fused_kernel<6, 2, kFuseAcc>,
+    const void* sks[3][5] = {
+        {(const void*)&spread_fused_kernel<3, 2, kFuseAccCopies>,
+         (const void*)&spread_fused_kernel<4, 2, kFuseAccCopies>,
+         (const void*)&spread_fused_kernel<5, 2, kFuseAccCopies>,
+         (const void*)&spread_fused_kernel<6, 2, kFuseAccCopies>,
+         (const void*)&spread_fused_kernel<8, 2, kFuseAccCopies>},
+        {(const void*)&spread_fused_kernel<3, 2, kFuseAcc>,
+         (const void*)&spread_fused_kernel<4, 2, kFuseAcc>,
+         (const void*)&spread_fused_kernel<5, 2, kFuseAcc>,
+         (const void*)&spread_fused_kernel<6, 2, kFuseAcc>,
          (const void*)&spread_fused_kernel<8, 2, kFuseAcc>},
-        {(const void*)&spread_fused_kernel<3, 2, kFuseAccWide>, (const void*)&spread_fused_kernel<4, 2, kFuseAccWide>,
-         (const void*)&spread_fused_kernel<5, 2, kFuseAccWide>, (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
+        {(const void*)&spread_fused_kernel<3, 2, kFuseAccWide>,
+         (const void*)&spread_fused_kernel<4, 2, kFuseAccWide>,
+         (const void*)&spread_fused_kernel<5, 2, kFuseAccWide>,
+         (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
          (const void*)&spread_fused_kernel<8, 2, kFuseAccWide>}};
     const void* gks[2][5] = {
         {(const void*)&gather_fused_kernel<3, 2, false>, (const void*)&gather_fused_kernel<4, 2, false>,
@@ -1883,11 +1979,10 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
          (const void*)&gather_fused_kernel<8, 2, true>}};
     const int si = width_index(Ws), gi = width_index(Wg);
     if (si < 0 || gi < 0) return;
-    const void* sk = sks[wide][si];
+    const void* sk = sks[spread_copies(nr) ? 0 : wide ? 2 : 1][si];
     const void* gk = gks[wide][gi];
     const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
-    (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kFuseMaxCellsWide * (int)sizeof(int));
+    (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize, kSpreadMaxLds);
     (void)hipFuncSetAttribute(gk, hipFuncAttributeMaxDynamicSharedMemorySize,
                               2 * kFuseMaxCells * (int)sizeof(float));
     int b = 0;
@@ -1908,7 +2003,12 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
                        const float*, int, const GridGeom&, float, int64_t, const float*,
                        const WindowArgs&, float*);
-    static const L t[2][5][2] = {
+    static const L t[3][5][2] = {
+        {{launch_spread_fused_t<3, 1, kFuseAccCopies>, launch_spread_fused_t<3, 2, kFuseAccCopies>},
+         {launch_spread_fused_t<4, 1, kFuseAccCopies>, launch_spread_fused_t<4, 2, kFuseAccCopies>},
+         {launch_spread_fused_t<5, 1, kFuseAccCopies>, launch_spread_fused_t<5, 2, kFuseAccCopies>},
+         {launch_spread_fused_t<6, 1, kFuseAccCopies>, launch_spread_fused_t<6, 2, kFuseAccCopies>},
+         {launch_spread_fused_t<8, 1, kFuseAccCopies>, launch_spread_fused_t<8, 2, kFuseAccCopies>}},
         {{launch_spread_fused_t<3, 1, kFuseAcc>, launch_spread_fused_t<3, 2, kFuseAcc>},
          {launch_spread_fused_t<4, 1, kFuseAcc>, launch_spread_fused_t<4, 2, kFuseAcc>},
          {launch_spread_fused_t<5, 1, kFuseAcc>, launch_spread_fused_t<5, 2, kFuseAcc>},
@@ -1922,7 +2022,8 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     dim3 grid((unsigned)((P + kFuseDirs - 1) / kFuseDirs), (unsigned)nchunk);
-    t[fused_wide(g.nr)][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
+    const int kind = spread_copies(g.nr) ? 0 : fused_wide(g.nr) ? 2 : 1;
+    t[kind][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
                                                   Xt, N, At, wscaled, P, g, pscale, chunk_len,
                                                   slice_max, win, partial);
     return hipGetLastError();
@@ -2093,11 +2194,19 @@ batch_spread_fused_kernel(
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
         const WindowArgs win = pr.swin;
-        if (pr.kb == 1)
-            spread_fused_body<W, 1, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
+        if (spread_copies(pr.g.nr) && pr.kb == 1)
+            spread_fused_body<W, 1, kFuseAccCopies, true>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
+                                    pr.g, pr.pscale, pr.chunk_len, pr.slice_max, win, pr.partial,
+                                    tk.a, tk.b);
+        else if (spread_copies(pr.g.nr))
+            spread_fused_body<W, 2, kFuseAccCopies, true>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
+                                    pr.g, pr.pscale, pr.chunk_len, pr.slice_max, win, pr.partial,
+                                    tk.a, tk.b);
+        else if (pr.kb == 1)
+            spread_fused_body<W, 1, kFuseAcc, false>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         else
-            spread_fused_body<W, 2, kFuseAcc>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
+            spread_fused_body<W, 2, kFuseAcc, false>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         __syncthreads();
     }
@@ -2125,9 +2234,14 @@ __global__ __launch_bounds__(kGatherBlock) void batch_gather_fused_kernel(
     }
 }
 
-size_t fused_spread_lds(int nr) { return (size_t)spread_cells(nr) * sizeof(int); }
+size_t fused_spread_lds(int nr) {
+    return (size_t)(spread_cells(nr) + 2 * kMaxSpareCells * kFuseDirs) * sizeof(int) *
+           (spread_copies(nr) ? 4 : 1);
+}
 
-size_t stored_spread_lds(int nr) { return ((size_t)nr << kSpreadLogR) * sizeof(int); }
+size_t stored_spread_lds(int nr) {
+    return ((size_t)(nr + 2 * kMaxSpareCells) << kSpreadLogR) * sizeof(int);
+}
 
 size_t fused_gather_lds(int nr) {
     const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
@@ -2142,7 +2256,7 @@ void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&batch_spread_fused_kernel<W>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  kFuseMaxCells * (int)sizeof(int));
+                                  kSpreadMaxLds);
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&batch_gather_fused_kernel<W>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   2 * kFuseMaxCells * (int)sizeof(float));

@@ -1,12 +1,17 @@
-"""Edges of the work split: several direction pairs per FFT workgroup.
+"""Edges of the work split: several direction pairs per FFT workgroup, cells
+that hold several slices before they are flushed, and copied cells in narrow
+grids.
 
-Bars.  Gradients against the FP64 oracle: 1e-4, the bar of the other adjoint tests;
+Bars.  Fused against stored projections: the two differ in FP32 rounding
+order and in the rounding of the fixed point (half a unit of 2^-18 per tap and
+source, unbiased), 1e-6 of s_abs as in the other comparisons of the two.
+Gradients against the FP64 oracle: 1e-4, the bar of the other adjoint tests;
 values 2e-5, with six taps."""
 import numpy as np
 import pytest
 
 import oracle as O
-from helpers import rel_l2, gpu_plan, to_dev, oracle_inputs, DEFAULT_T
+from helpers import rel_l2, err_scale, gpu_plan, to_dev, oracle_inputs, DEFAULT_T
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +46,41 @@ def test_fft_pairs_and_gradients(P, n_ft, materialize):
             rel_l2(gx, O.grad_x_fourier("gauss", x, y, w, v, *a)))
     print("s %.2e grad_y %.2e grad_w %.2e grad_x %.2e" % ((e,) + errs))
     assert e < 2e-5 and max(errs) < 1e-4
+
+
+def _fused_against_stored(cfg, T, window_w=4):
+    import paper_2410_01316_amd as F
+    x, y, w = to_dev(cfg["x"], cfg["y"], cfg["w"])
+    out = []
+    for w_in, mat in ((w, False), (w, True), (w.abs(), True)):
+        plan = F.Plan(cfg["xi"], kernel=cfg["kernel"], n_ft=cfg["n_ft"], scale=cfg["scale"],
+                      R=cfg["R"], T=T, window_w=window_w, materialize=mat,
+                      n_max=cfg["x"].shape[0], m_max=cfg["y"].shape[0])
+        out.append(plan(x, w_in, y).cpu().numpy())
+        plan.check()
+    e = err_scale(out[0], out[1], out[2])
+    print("fused - stored %.2e" % e)
+    return e
+
+
+@pytest.mark.parametrize("scales", [(1, 1, 1, 1, 1, 1, 1, 1, 1, 1), (1, 1, 64, 64, 64, 64, 1, 8, 8, 8),
+                                    (1, 0, 0, 1, 1, 0, 1, 1, 1, 1)], ids=["equal", "steps", "zeros"])
+def test_cells_held_over_slices(scales):
+    """Ten slices per direction and workgroup, scales equal or changing from
+    one to the next; weights of one sign and size on a few points, so single
+    cells come near the fixed point's bound."""
+    N, S = 9 * 4096 + 11, 4096
+    cfg = _cfg("gauss", 4, N, 65, 1500, 256, 1, 2.0)
+    w = np.repeat(np.asarray(scales, float), S)[:N] * np.random.default_rng(2).choice([1.0, 0.999], N)
+    cfg["w"] = w
+    cfg["x"][: 5 * S] = cfg["x"][:3].repeat(5 * S // 3 + 1, 0)[: 5 * S]
+    assert _fused_against_stored(cfg, DEFAULT_T["gauss"]) < 1e-6
+
+
+@pytest.mark.parametrize("d", [3, 40])
+@pytest.mark.parametrize("T", [0.22, 0.27, 0.285, 0.3, 0.32, 0.4])
+def test_copied_cells_of_narrow_grids(T, d):
+    """Grids of 256 cells with about 120 to 210 of them stored."""
+    cfg = _cfg("energy", d, 9001, 70, 21, 128, d, 1.0)
+    cfg["w"] *= np.random.default_rng(3).choice([-1.0, 1.0], 9001)
+    assert _fused_against_stored(cfg, T) < 1e-6
