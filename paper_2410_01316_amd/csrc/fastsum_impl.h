@@ -255,7 +255,7 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
 // lane m + 16 k: 4 halves (xi_{16g + 4k + i})_{16q + m}, i < 4 (zero past P,
 // d).  dmax: the slots launch_fftconv filled with grid_d.
 // gpart: ceil(P / prange) x ldg x 16 DC floats of partial sums (ldg >= M).
-int64_t fused_grad_tile();    // targets per workgroup
+int64_t fused_grad_tile(int nr, int W, int d);    // targets per workgroup
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
                              const uint16_t* Ab, int P, GridGeom g, float pscale,
                              const float* grid_d, const unsigned* dmax, int prange,

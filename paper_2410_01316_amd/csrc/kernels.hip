@@ -1200,14 +1200,13 @@ constexpr int kFuseAccCopies = 8;
 constexpr int kFuseMaxCellsWide = kFuseAccWide * kSpreadBlock;
 // LDS of the widest spread: its cells and spare cells
 constexpr int kSpreadMaxLds = (kFuseMaxCellsWide + 2 * kMaxSpareCells * 16) * (int)sizeof(int);
-constexpr int kGatherBlock = 512;                          // 8 waves, one workgroup per CU
-constexpr int kGatherWaves = kGatherBlock / 64;
+constexpr int kGatherWaves = 8;
 constexpr int kGatherNB = 8;                               // 16-target batches per wave
 // wide grids: fewer batches (registers; W = 8 takes three).  Eight batches
 // fit at up to five taps, but 512-target tiles fill the rounds better: the
 // MMD energy gather (d = 20, M = 2e5, P = 512) took 198 us with eight, 180
 // with four
-constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : (W >= 8 ? 3 : 4); }
+constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : W >= 8 ? 3 : 4; }
 // row of the dispatch tables of window width W (-1: none)
 constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
 
@@ -1380,7 +1379,10 @@ __device__ __forceinline__ f32x4 split_mfma(const SplitOp<KB>& a, const SplitOp<
 // of each other at nr = 88).  Narrow grids keep four copies of each cell,
 // one per group of 16 lanes: then no two lanes of a wave share a bank or a
 // cell.  A copy takes a quarter of the points, so kHeldSlices slices of one
-// scale are held before a flush (as in spread_tile).
+// scale are held before a flush (as in spread_tile).  Spread of 60000 points,
+// d = 50: P = 3500, nr = 88: 245 us direction-major, 186 with copies; P = 1000,
+// nr = 364: 101 direction-major, 82 cell-major without copies, which at that
+// width would leave one workgroup per CU.
 constexpr int kCopyMaxCells = 160;                 // nr with copies: 48 KB, three workgroups per CU
 constexpr bool spread_copies(int nr) { return nr <= kCopyMaxCells; }
 // accumulators (16 nr / kSpreadBlock) are flushed in groups per thread without
@@ -1546,12 +1548,32 @@ __global__ __launch_bounds__(kSpreadBlock) void spread_fused_kernel(
 // flight wherever it needs one (lgkmcnt(0)), which undoes the pipeline of
 // gather_group.
 __device__ __forceinline__ void gather_stage(const float* __restrict__ grid, int p0, int nr,
-                                             float* buf, int wave, int lane) {
+                                             float* buf, int wave, int lane, int waves) {
     const int nbytes = kFuseDirs * nr * 4;
     const __amdgpu_buffer_rsrc_t gs = buffer_rsrc(grid + (int64_t)p0 * nr, nbytes);
-    for (int piece = wave; piece * kDmaBytes < nbytes; piece += kGatherWaves)
+    for (int piece = wave; piece * kDmaBytes < nbytes; piece += waves)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(gs, (lds_void*)(buf + piece * (kDmaBytes / 4)), 16,
                                                  lane * 16, piece * kDmaBytes, 0, 0);
+}
+
+// Half h of the group's grids, its directions 4r + 2h and 4r + 2h + 1, as
+// rows 2r and 2r + 1 (four runs of two contiguous grids).
+__device__ __forceinline__ void gather_stage_half(const float* __restrict__ grid, int p0, int h,
+                                                  int nr, float* buf, int wave, int lane, int waves) {
+    const int run = 2 * nr * 4, nbytes = 4 * run;
+    const __amdgpu_buffer_rsrc_t gs = buffer_rsrc(grid + (int64_t)p0 * nr, 2 * nbytes);
+    for (int piece = wave; piece * kDmaBytes < nbytes; piece += waves) {
+        const int x = piece * kDmaBytes + lane * 16;
+        const int skip = (x >= run) + (x >= 2 * run) + (x >= 3 * run) + h;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(gs, (lds_void*)(buf + piece * (kDmaBytes / 4)), 16,
+                                                 x + skip * run, 0, 0, 0);
+    }
+}
+
+// floats of one of the two staging buffers: a group's grids, or half of them
+__host__ __device__ constexpr int gather_stage_floats(int nr, bool wide) {
+    constexpr int unit = kDmaBytes / 4;
+    return ((wide ? kFuseDirs / 2 : kFuseDirs) * nr + unit - 1) / unit * unit;
 }
 
 // The batches of one group through a pipeline of half batches: the
@@ -1599,29 +1621,68 @@ __device__ __forceinline__ void gather_group(const float* lds, const int (&base)
     }
 }
 
+// As gather_group for half H of a group's directions (wide grids): H = 0 forms
+// the projections pr of all four directions, H = 1 uses the ones kept.
+template <int W, int KB, int NB, int H, class Use, class Reload>
+__device__ __forceinline__ void gather_half(const float* lds, int base0, int base1,
+                                            const SplitOp<KB>& dop, const SplitOp<KB> (&yop)[NB],
+                                            f32x4 (&pr)[NB], const WinEval<W>& ev,
+                                            const WindowArgs& win, Use use, Reload reload) {
+    static_assert(NB >= 3, "the pipeline holds two batches");
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+    TapRead<W> tr[2];
+    if constexpr (H == 0) {
+        pr[0] = split_mfma<KB>(dop, yop[0], zero);
+        pr[1] = split_mfma<KB>(dop, yop[1], zero);
+    }
+    tr[0].issue(pr[0][2 * H], pr[0][2 * H + 1], lds, base0, base1, ev);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (b + 1 < NB)
+            tr[(b + 1) & 1].issue(pr[b + 1][2 * H], pr[b + 1][2 * H + 1], lds, base0, base1, ev);
+        reads_ahead();
+        if (H == 0 && b + 2 < NB) {
+            pr[b + 2] = split_mfma<KB>(dop, yop[b + 2], zero);
+            if (b + 3 == NB) reload();
+        }
+        float v[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            v[i] = tr[b & 1].value(i, ev, win);
+            pin(v[i]);
+        }
+        use(b, v);
+    }
+}
+
 // Gather with projections computed in registers.  A workgroup owns the
-// TGT = 128 NB targets of tile `tile` (NB = gather_nb(WIDE, W)) and
+// TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(WIDE, W)) and
 // the direction range `range`
 // (prange directions, a multiple of kFuseDirs).  The grids of each group of 16
 // directions are staged in one of two LDS buffers while the previous group
-// is interpolated (WIDE: one buffer, refilled after each group); lane (c, r)
-// holds directions 4r .. 4r+3 of target c of each batch.  Per target the
-// four directions are summed in FP32, the groups in FP64.
+// is interpolated; lane (c, r) holds directions 4r .. 4r+3 of target c of each
+// batch.  Per target the four directions are summed in FP32, the groups in
+// FP64.  WIDE: two groups do not fit, so the buffers hold halves of a group
+// (gather_stage_half); a single buffer, refilled between two barriers, took
+// 193 us for the sum and 274 for the adjoint at M = 200000, d = 20, P = 512,
+// nr = 1856, halves take 187 and 258.
 template <int W, int KB, bool WIDE>
 __device__ __forceinline__ void gather_fused_body(
     float* gls, const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
     int P, const GridGeom& g, float pscale, const float* __restrict__ grid, int prange,
     int stage, const WindowArgs& win, double* __restrict__ spart, int64_t ldm, int tile,
     int range) {
-    constexpr int NB = gather_nb(WIDE, W);                         // batches per wave
-    constexpr int TGT = kGatherWaves * NB * 16;                    // targets per workgroup
+    constexpr int WAVES = kGatherWaves;
+    constexpr int NB = gather_nb(WIDE, W);                     // batches per wave
+    constexpr int TGT = WAVES * NB * 16;                           // targets per workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
     const int64_t mb = (int64_t)tile * TGT;
     const int64_t tw = (mb + wave * (NB * 16)) / 16;   // wave's first target tile
     const int p_begin = range * prange;
     const int p_end = min(P, p_begin + prange);
-    gather_stage(grid, p_begin, g.nr, gls, wave, lane);
+    if (WIDE) gather_stage_half(grid, p_begin, 0, g.nr, gls, wave, lane, WAVES);
+    else gather_stage(grid, p_begin, g.nr, gls, wave, lane, WAVES);
     // target tiles past the last one read as zero
     const int64_t ntiles = (M + 15) / 16;
     const __amdgpu_buffer_rsrc_t ys =
@@ -1643,10 +1704,31 @@ __device__ __forceinline__ void gather_fused_body(
         const int p1 = p0 + kFuseDirs;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (!WIDE && p1 < p_end) gather_stage(grid, p1, g.nr, gls + (k ^ 1) * stage, wave, lane);
+        auto reload = [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); };
+        if constexpr (WIDE) {
+            gather_stage_half(grid, p0, 1, g.nr, gls + stage, wave, lane, WAVES);
+            const int base = 2 * r * g.nr - ev.off;
+            f32x4 pr[NB];
+            float t[NB];
+            gather_half<W, KB, NB, 0>(
+                gls, base, base + g.nr, dop, yop, pr, ev, win,
+                [&](int b, const float (&v)[2]) { t[b] = v[0] + v[1]; }, reload);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (p1 < p_end) gather_stage_half(grid, p1, 0, g.nr, gls, wave, lane, WAVES);
+            gather_half<W, KB, NB, 1>(
+                gls + stage, base, base + g.nr, dop, yop, pr, ev, win,
+                [&](int b, const float (&v)[2]) {
+                    t[b] += v[0];
+                    accd[b] += (double)(t[b] + v[1]);
+                },
+                reload);
+            continue;
+        }
+        if (p1 < p_end) gather_stage(grid, p1, g.nr, gls + (k ^ 1) * stage, wave, lane, WAVES);
         int base[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) base[i] = (WIDE ? 0 : k * stage) + (4 * r + i) * g.nr - ev.off;
+        for (int i = 0; i < 4; ++i) base[i] = k * stage + (4 * r + i) * g.nr - ev.off;
         float t = 0.f;
         gather_group<W, KB, NB>(
             gls, base, dop, yop, ev, win,
@@ -1655,11 +1737,7 @@ __device__ __forceinline__ void gather_fused_body(
                 t += v[1];
                 if (h) accd[b] += (double)t;
             },
-            [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); });
-        if (WIDE && p1 < p_end) {
-            __syncthreads();
-            gather_stage(grid, p1, g.nr, gls, wave, lane);
-        }
+            reload);
     }
     // sum the four lane groups r holding the same targets
 #pragma unroll
@@ -1674,11 +1752,11 @@ __device__ __forceinline__ void gather_fused_body(
 
 // workgroup (x, y): target tile x, direction range y
 template <int W, int KB, bool WIDE>
-__global__ __launch_bounds__(kGatherBlock) void gather_fused_kernel(
+__global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At, int P,
     GridGeom g, float pscale, const float* __restrict__ grid, int prange, int stage,
     WindowArgs win, double* __restrict__ spart, int64_t ldm) {
-    extern __shared__ float gls[];                    // 2 x stage floats (WIDE: 1 x)
+    extern __shared__ float gls[];                    // 2 x stage floats
     gather_fused_body<W, KB, WIDE>(gls, Yt, M, At, P, g, pscale, grid, prange, stage, win, spart, ldm,
                              blockIdx.x, blockIdx.y);
 }
@@ -1696,39 +1774,49 @@ __global__ __launch_bounds__(kGatherBlock) void gather_fused_kernel(
 // interpolation.  Lane (c, r) holds t' of directions 4r + i of target c, the B
 // operand (column c, k = 4r + i); Ab holds per group, 16-coordinate chunk q
 // and part the A operand, lane m + 16k: (xi_{16 group + 4k + i})_{16 q + m},
-// i < 4 (zero past P and d).  Workgroup (x, y): kGradTargets targets of tile
+// i < 4 (zero past P and d).  Workgroup (x, y): grad_targets targets of tile
 // x, direction range y; writes gpart[(y * ldg + m) * 16 DC + i] (FP32, summed
 // over the ranges by grad_reduce_kernel).
-constexpr int kGradNB = 4;                                   // 16-target batches per wave
-constexpr int kGradTargets = kGatherWaves * kGradNB * 16;
-constexpr int kGradMaxDC = kSplitMaxD / 16;
+// waves of a workgroup: sixteen on wide grids where three batches fit in 128
+// registers (LDS holds one workgroup, eight waves are two per SIMD): the
+// adjoint above with the sum over the ranges 252 us with eight, 239 with sixteen
+constexpr int grad_waves(bool wide, int KB, int W) { return wide && KB == 1 && W <= 5 ? 16 : 8; }
+// 16-target batches per wave
+constexpr int grad_nb(bool wide, int KB, int W) { return grad_waves(wide, KB, W) == 16 ? 3 : 4; }
+constexpr int grad_targets(bool wide, int KB, int W) {
+    return grad_waves(wide, KB, W) * grad_nb(wide, KB, W) * 16;
+}
 
 template <int W, int KB, bool WIDE>
-__global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
+__global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
     const uint16_t* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
     const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, int prange, int stage,
     WindowArgs win, float* __restrict__ gpart, int64_t ldg) {
     extern __shared__ float gls[];                    // 2 x stage floats
+    constexpr int WAVES = grad_waves(WIDE, KB, W), NB = grad_nb(WIDE, KB, W);
+    constexpr int TGT = grad_targets(WIDE, KB, W);
+    constexpr int MAXDC = 2 * KB;                     // 16-coordinate chunks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
-    const int64_t mb = (int64_t)blockIdx.x * kGradTargets;
-    const int64_t tw = (mb + wave * (kGradNB * 16)) / 16;     // wave's first target tile
+    const int64_t mb = (int64_t)blockIdx.x * TGT;
+    const int64_t tw = (mb + wave * (NB * 16)) / 16;     // wave's first target tile
     const int p_begin = blockIdx.y * prange;
     const int p_end = min(P, p_begin + prange);
-    gather_stage(grid_d, p_begin, g.nr, gls, wave, lane);
+    if (WIDE) gather_stage_half(grid_d, p_begin, 0, g.nr, gls, wave, lane, WAVES);
+    else gather_stage(grid_d, p_begin, g.nr, gls, wave, lane, WAVES);
     const int64_t ntiles = (M + 15) / 16;
     const __amdgpu_buffer_rsrc_t ys =
         buffer_rsrc(Yt + tw * KB * 2 * (kSplitTileBytes / 2),
-                    max((int64_t)0, min((int64_t)kGradNB, ntiles - tw)) * KB * 2 * kSplitTileBytes);
-    SplitOp<KB> yop[kGradNB];
+                    max((int64_t)0, min((int64_t)NB, ntiles - tw)) * KB * 2 * kSplitTileBytes);
+    SplitOp<KB> yop[NB];
 #pragma unroll
-    for (int b = 0; b < kGradNB; ++b) load_split<KB>(yop[b], ys, b, lane);
-    f32x4 gacc[kGradNB][kGradMaxDC];
+    for (int b = 0; b < NB; ++b) load_split<KB>(yop[b], ys, b, lane);
+    f32x4 gacc[NB][MAXDC];
 #pragma unroll
-    for (int b = 0; b < kGradNB; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int q = 0; q < kGradMaxDC; ++q) gacc[b][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < MAXDC; ++q) gacc[b][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float tscale = ldexpf(1.f, -slots_exponent(dmax, lane));
     const WinEval<W> ev(g, win, pscale);
     SplitOp<KB> dop;
@@ -1740,53 +1828,75 @@ __global__ __launch_bounds__(kGatherBlock) void gather_grad_fused_kernel(
         __syncthreads();
         // this lane's back-projection operands of the group
         const h4* __restrict__ ag = reinterpret_cast<const h4*>(Ab) + (int64_t)(p0 / kFuseDirs) * DC * 128 + lane;
-        h4 abv[kGradMaxDC][2];
+        h4 abv[MAXDC][2];
 #pragma unroll
-        for (int q = 0; q < kGradMaxDC; ++q)
+        for (int q = 0; q < MAXDC; ++q)
             if (q < DC) {
                 abv[q][0] = ag[q * 128];
                 abv[q][1] = ag[q * 128 + 64];
             }
-        if (!WIDE && p1 < p_end) gather_stage(grid_d, p1, g.nr, gls + (k ^ 1) * stage, wave, lane);
+        auto reload = [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); };
+        auto split = [&](h4& thi, h4& tlo, int h, const float (&v)[2]) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float x = v[i] * tscale;
+                const _Float16 hi = (_Float16)x;
+                thi[2 * h + i] = hi;
+                tlo[2 * h + i] = (_Float16)(x - (float)hi);
+            }
+        };
+        auto backproject = [&](int b, const h4& thi, const h4& tlo) {
+#pragma unroll
+            for (int q = 0; q < MAXDC; ++q) {
+                if (q >= DC) break;
+                f32x4 a = gacc[b][q];
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], tlo, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][1], thi, a, 0, 0, 0);
+                gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], thi, a, 0, 0, 0);
+            }
+        };
+        if constexpr (WIDE) {
+            gather_stage_half(grid_d, p0, 1, g.nr, gls + stage, wave, lane, WAVES);
+            const int base = 2 * r * g.nr - ev.off;
+            f32x4 pr[NB];
+            h4 thi[NB], tlo[NB];
+            gather_half<W, KB, NB, 0>(
+                gls, base, base + g.nr, dop, yop, pr, ev, win,
+                [&](int b, const float (&v)[2]) { split(thi[b], tlo[b], 0, v); }, reload);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (p1 < p_end) gather_stage_half(grid_d, p1, 0, g.nr, gls, wave, lane, WAVES);
+            gather_half<W, KB, NB, 1>(
+                gls + stage, base, base + g.nr, dop, yop, pr, ev, win,
+                [&](int b, const float (&v)[2]) {
+                    split(thi[b], tlo[b], 1, v);
+                    backproject(b, thi[b], tlo[b]);
+                },
+                reload);
+            continue;
+        }
+        if (p1 < p_end) gather_stage(grid_d, p1, g.nr, gls + (k ^ 1) * stage, wave, lane, WAVES);
         int base[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) base[i] = (WIDE ? 0 : k * stage) + (4 * r + i) * g.nr - ev.off;
+        for (int i = 0; i < 4; ++i) base[i] = k * stage + (4 * r + i) * g.nr - ev.off;
         h4 thi, tlo;
-        gather_group<W, KB, kGradNB>(
+        gather_group<W, KB, NB>(
             gls, base, dop, yop, ev, win,
             [&](int b, int h, const float (&v)[2]) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const float x = v[i] * tscale;
-                    const _Float16 hi = (_Float16)x;
-                    thi[2 * h + i] = hi;
-                    tlo[2 * h + i] = (_Float16)(x - (float)hi);
-                }
-                if (h == 0) return;
-#pragma unroll
-                for (int q = 0; q < kGradMaxDC; ++q) {
-                    if (q >= DC) break;
-                    f32x4 a = gacc[b][q];
-                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], tlo, a, 0, 0, 0);
-                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][1], thi, a, 0, 0, 0);
-                    gacc[b][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(abv[q][0], thi, a, 0, 0, 0);
-                }
+                split(thi, tlo, h, v);
+                if (h) backproject(b, thi, tlo);
             },
-            [&]() { if (p1 < p_end) load_split<KB>(dop, At, p1 / kFuseDirs, lane); });
-        if (WIDE && p1 < p_end) {
-            __syncthreads();
-            gather_stage(grid_d, p1, g.nr, gls, wave, lane);
-        }
+            reload);
     }
     // lane (c, r) holds coordinates 16 q + 4 r + j of target c
     const int dcp = 16 * DC;
 #pragma unroll
-    for (int b = 0; b < kGradNB; ++b) {
-        const int64_t m = mb + wave * (kGradNB * 16) + 16 * b + c;
+    for (int b = 0; b < NB; ++b) {
+        const int64_t m = mb + wave * (NB * 16) + 16 * b + c;
         if (m >= M) continue;
         float* __restrict__ dst = gpart + ((int64_t)blockIdx.y * ldg + m) * dcp + 4 * r;
 #pragma unroll
-        for (int q = 0; q < kGradMaxDC; ++q) {
+        for (int q = 0; q < MAXDC; ++q) {
             if (q >= DC) break;
             *reinterpret_cast<float4*>(dst + 16 * q) =
                 make_float4(gacc[b][q][0], gacc[b][q][1], gacc[b][q][2], gacc[b][q][3]);
@@ -1838,7 +1948,7 @@ void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
                                   2 * kFuseMaxCells * (int)sizeof(float));
         attr_set = true;
     }
-    hipLaunchKernelGGL((gather_fused_kernel<W, KB, WIDE>), grid, dim3(kGatherBlock), lds, stream, Yt,
+    hipLaunchKernelGGL((gather_fused_kernel<W, KB, WIDE>), grid, dim3(64 * kGatherWaves), lds, stream, Yt,
                        M, At, P, g, pscale, gridv, prange, stage, win, spart, ldm);
 }
 
@@ -1855,11 +1965,11 @@ void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint1
                                   2 * kFuseMaxCells * (int)sizeof(float));
         attr_set = true;
     }
-    hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, WIDE>), grid, dim3(kGatherBlock), lds, stream,
+    hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, WIDE>), grid, dim3(64 * grad_waves(WIDE, KB, W)), lds, stream,
                        Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win, gpart, ldg);
 }
 
-int64_t fused_grad_tile() { return kGradTargets; }
+int64_t fused_grad_tile(int nr, int W, int d) { return grad_targets(fused_wide(nr), split_kblocks(d), W); }
 
 size_t abs_slots_uints() { return kAbsUints; }
 
@@ -1886,11 +1996,12 @@ hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const 
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     const int DC = (d + 15) / 16;
-    const int stage = (kFuseDirs * g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
-    const int nrange = (P + prange - 1) / prange;
-    dim3 gd((unsigned)((M + kGradTargets - 1) / kGradTargets), (unsigned)nrange);
     const bool wide = fused_wide(g.nr);
-    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)(wide ? 1 : 2) * stage * sizeof(float), stream,
+    const int stage = gather_stage_floats(g.nr, wide);
+    const int nrange = (P + prange - 1) / prange;
+    const int64_t tgt = fused_grad_tile(g.nr, W, d);
+    dim3 gd((unsigned)((M + tgt - 1) / tgt), (unsigned)nrange);
+    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)2 * stage * sizeof(float), stream,
                                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win,
                                       gpart, ldg);
     hipError_t e = hipGetLastError();
@@ -1981,7 +2092,7 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
     if (si < 0 || gi < 0) return;
     const void* sk = sks[spread_copies(nr) ? 0 : wide ? 2 : 1][si];
     const void* gk = gks[wide][gi];
-    const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
+    const int stage = gather_stage_floats(nr, wide);
     (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize, kSpreadMaxLds);
     (void)hipFuncSetAttribute(gk, hipFuncAttributeMaxDynamicSharedMemorySize,
                               2 * kFuseMaxCells * (int)sizeof(float));
@@ -1989,8 +2100,8 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, sk, kSpreadBlock,
                                                      fused_spread_lds(nr)) == hipSuccess && b > 0)
         *spread_blocks = b;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, gk, kGatherBlock,
-                                                     (size_t)(wide ? 1 : 2) * stage * sizeof(float)) == hipSuccess && b > 0)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, gk, 64 * kGatherWaves,
+                                                     (size_t)2 * stage * sizeof(float)) == hipSuccess && b > 0)
         *gather_blocks = b;
 }
 
@@ -2051,12 +2162,12 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     // one staging buffer: the group's grids rounded up to whole 1 KB pieces
-    const int stage = (kFuseDirs * g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
+    const bool wide = fused_wide(g.nr);
+    const int stage = gather_stage_floats(g.nr, wide);
     const int64_t tgt = fused_gather_tile(g.nr, W);
     dim3 gd((unsigned)((M + tgt - 1) / tgt),
             (unsigned)((P + prange - 1) / prange));
-    const bool wide = fused_wide(g.nr);
-    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)(wide ? 1 : 2) * stage * sizeof(float), stream,
+    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)2 * stage * sizeof(float), stream,
                                       Yt, M, At, P, g, pscale, grid, prange, stage, win, spart,
                                       ldm);
     return hipGetLastError();
@@ -2213,14 +2324,14 @@ batch_spread_fused_kernel(
 }
 
 template <int W>
-__global__ __launch_bounds__(kGatherBlock) void batch_gather_fused_kernel(
+__global__ __launch_bounds__(64 * kGatherWaves) void batch_gather_fused_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
     int P) {
     extern __shared__ float bgls[];
     for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
         const BatchTask tk = tasks[t];
         const BatchProblem& pr = probs[tk.prob];
-        const int stage = (kFuseDirs * pr.g.nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
+        const int stage = gather_stage_floats(pr.g.nr, false);
         const uint16_t* yt = pr.same_xy ? pr.xt : pr.yt;
         const WindowArgs win = pr.gwin;
         // no wave may still read the staging buffers of the previous task
@@ -2244,8 +2355,7 @@ size_t stored_spread_lds(int nr) {
 }
 
 size_t fused_gather_lds(int nr) {
-    const int stage = (kFuseDirs * nr + kDmaBytes / 4 - 1) / (kDmaBytes / 4) * (kDmaBytes / 4);
-    return (size_t)2 * stage * sizeof(float);
+    return (size_t)2 * gather_stage_floats(nr, false) * sizeof(float);
 }
 
 template <int W>
@@ -2266,7 +2376,7 @@ void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const
         hipLaunchKernelGGL((batch_spread_fused_kernel<W>), grid, dim3(kSpreadBlock), lds, stream,
                            probs, tasks, ntasks, P);
     else
-        hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(kGatherBlock), lds, stream,
+        hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(64 * kGatherWaves), lds, stream,
                            probs, tasks, ntasks, P);
 }
 

@@ -472,8 +472,8 @@ struct fastsum_plan_s {
     double xi_norm_max = 1.0;      // max_p |xi_p| (range check of the fused path)
     uint16_t* ab = nullptr;        // back-projection operands of the fused adjoint
     unsigned* dmax = nullptr;      // largest |grid_d|, |grid_wd| (two sets of slots)
-    float* gpart = nullptr;        // its per-range partial sums, kGradMaxRanges x ldg x 16 DC
-    int64_t ldg = 0;
+    float* gpart = nullptr;        // its per-range partial sums, 16 DC floats a row
+    int64_t gpart_rows = 0;
     // stored projections by the tile GEMM (BF16, or FP32 with d > 64):
     // direction tiles (BF16 tau xi, or f16 hi / lo of xi) and a point-tile
     // buffer for one point set at a time
@@ -707,16 +707,34 @@ fastsum_status fused_pass(fastsum_plan_s* pl, const float* x, const float* w, in
                      (pl->r.p.flags & FASTSUM_FLAG_GRAD) ? pl->grid_d : nullptr, pl->dmax, bc, st);
 }
 
-// direction ranges of the fused adjoint gather: at least three rounds of
-// workgroups when P allows, at most kGradMaxRanges ranges
-constexpr int kGradMaxRanges = 4;
+// Direction ranges of the fused adjoint gather (whole 16-direction groups),
+// one partial sum of a target's gradient each: the fullest rounds of
+// workgroups, less 2% per range (M rows more to write and to sum), within the
+// rows that gpart holds.  "Three rounds, four ranges at most" left 47% of the
+// slots at work at M = 15013, d = 50, P = 1000 and 76% at M = 200000, d = 20,
+// P = 512: 58 + 7 us (kernel, sum over the ranges) against 40 + 9 with eight
+// ranges, 258 + 19 against 230 + 22 with three (five: 232 + 31).
+constexpr int kGradMaxRanges = 16;
 
-int fused_grad_range(int64_t M, int P, int64_t slots) {
-    const int64_t tiles = (M + fused_grad_tile() - 1) / fused_grad_tile();
+// gpart rows (one target's partial sum each) of a plan of cap targets: four
+// ranges of any call, more of smaller ones
+int64_t grad_rows(int64_t cap) {
+    return std::max<int64_t>(4 * cap, std::min<int64_t>(kGradMaxRanges * cap, 1 << 18));
+}
+
+int fused_grad_range(const fastsum_plan_s* pl, int64_t M) {
+    const int64_t tile = fused_grad_tile(pl->geom.nr, pl->Wd, pl->d), tiles = (M + tile - 1) / tile;
+    const int64_t P = pl->P, slots = pl->gather_slots;
     const int64_t groups = (P + kFuseDirs - 1) / kFuseDirs;
-    const int64_t want = std::min<int64_t>(kGradMaxRanges, (3 * slots + tiles - 1) / tiles);
-    const int64_t ranges = std::max<int64_t>(1, std::min(groups, want));
-    return (int)round_up((P + ranges - 1) / ranges, kFuseDirs);
+    const int64_t most = std::min({(int64_t)kGradMaxRanges, groups, pl->gpart_rows / M});
+    int64_t best_pr = groups * kFuseDirs;
+    double best = -1.0;
+    for (int64_t r = 1; r <= most; ++r) {
+        const int64_t pr = round_up((P + r - 1) / r, kFuseDirs);
+        const double score = round_efficiency(tiles * ((P + pr - 1) / pr), slots) - 0.02 * r;
+        if (score > best) { best = score; best_pr = pr; }
+    }
+    return (int)best_pr;
 }
 
 // Stored projections of X into out (row stride ld); sink: the bound check's
@@ -966,7 +984,7 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
              dev_alloc(&pl->gpt, project_tiles_bytes(cap, pl->d, bf16) / 2);
     }
     const int DC = (pl->d + 15) / 16;
-    pl->ldg = cap;       // the source adjoint back-projects at the sources
+    pl->gpart_rows = grad_rows(cap);   // the source adjoint back-projects at the sources
     if (ok && grad && pl->sorted)
         ok = dev_alloc(&pl->sty, (size_t)P * pl->ldm) && dev_alloc(&pl->stx, (size_t)P * pl->ldm) &&
              dev_alloc(&pl->styb, (size_t)P * pl->ldm) && dev_alloc(&pl->styo, (size_t)P * pl->ldm) &&
@@ -977,7 +995,7 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
              dev_alloc(&pl->mult_d, (size_t)n) &&
              (pl->fused ? dev_alloc(&pl->ab, (size_t)gtiles * DC * 512) &&
                               dev_alloc(&pl->dmax, 2 * abs_slots_uints()) &&
-                              dev_alloc(&pl->gpart, (size_t)kGradMaxRanges * pl->ldg * 16 * DC)
+                              dev_alloc(&pl->gpart, (size_t)pl->gpart_rows * 16 * DC)
                         : dev_alloc(&pl->tprime, (size_t)P * std::max(pl->ld_x, pl->ld_y)));
     if (ok && grad && pl->d > kSplitMaxD) {
         const int64_t rows = pl->sorted ? pl->ldm : std::max(pl->ld_x, pl->ld_y);
@@ -1172,8 +1190,8 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         if (grad_y) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, yt, M, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
-                                     pl->grid_d, pl->dmax, fused_grad_range(M, P, pl->gather_slots),
-                                     pl->dwin, pl->gpart, pl->ldg, fcoef, grad_s, grad_y, st));
+                                     pl->grid_d, pl->dmax, fused_grad_range(pl, M),
+                                     pl->dwin, pl->gpart, M, fcoef, grad_s, grad_y, st));
         }
         if (grad_w || grad_x) {
             {
@@ -1189,9 +1207,9 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         if (grad_x) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, pl->xt, N, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
-                                     pl->grid_wd, pl->dmax + abs_slots_uints(), fused_grad_range(N, P, pl->gather_slots),
-                                     pl->dwin, pl->gpart, pl->ldg, fcoef, pl->last_w, grad_x,
-                                     st));
+                                     pl->grid_wd, pl->dmax + abs_slots_uints(),
+                                     fused_grad_range(pl, N),
+                                     pl->dwin, pl->gpart, N, fcoef, pl->last_w, grad_x, st));
         }
         return FASTSUM_OK;
     }
