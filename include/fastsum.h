@@ -162,7 +162,7 @@ typedef struct {
     int32_t grid_lo;     /* first grid cell that points inside the bound touch */
     int32_t grid_nr;     /* number of such cells (stored grids hold these)    */
     int32_t last_spread_chunks;  /* source chunks of the last exec's spread   */
-    int32_t last_gather_groups;  /* direction groups of the last exec's gather */
+    int32_t last_gather_groups;  /* partial sums per target of the last exec's gather, at most */
     int32_t fused;       /* 1: projections are computed inside spread/gather  */
 } fastsum_plan_info;
 

@@ -25,6 +25,17 @@ struct WindowArgs {
 // Grid geometry: n cells, position u = x~ * n + n/2 for x~ in [-1/2, 1/2).
 // Only cells [lo, lo + nr) can receive or serve weight for points inside the
 // plan's bound; the kernels clamp every point's taps into that range.
+// How the work of a fused gather is cut: units (target tile, `step`
+// directions), tile by tile, in runs of equal length, one per workgroup.  A
+// tile's partial sums are one row per run that meets it.  units < 2^31.
+struct GatherSplit {
+    unsigned units = 0;
+    unsigned tile = 64;     // targets per tile, a multiple of 64
+    unsigned groups = 1;    // units per tile
+    unsigned run = 0;       // units per workgroup (launch_reduce: 0, no split)
+    unsigned step = 16;     // directions per unit, a multiple of kFuseDirs
+};
+
 struct GridGeom {
     int n;
     int lo;
@@ -176,8 +187,9 @@ hipError_t launch_gather(int W, const float* proj, int64_t ld, int64_t M,
 
 // s[m] = (float)(scale * sum_b spart[b*ldm + m]), b < nb; then the bound
 // check bc (BoundCheck; bc.norms == nullptr: none).
-hipError_t launch_reduce(const double* spart, int nb, int64_t ldm, int64_t M,
-                         double scale, float* s, const BoundCheck& bc, hipStream_t stream);
+hipError_t launch_reduce(const double* spart, int nb, const GatherSplit& split, int64_t ldm,
+                         int64_t M, double scale, float* s, const BoundCheck& bc,
+                         hipStream_t stream);
 
 // grad_y[m*d + i] = v[m] * coef * sum_p tprime[p*ld + m] * A[p*dpad + i]
 hipError_t launch_backproject(const float* tprime, int64_t ld, int64_t M,
@@ -206,9 +218,10 @@ bool fused_supported(int d, int nr);
 bool fused_wide(int nr);
 // targets per fused gather workgroup (grids of nr cells, window width W)
 int64_t fused_gather_tile(int nr, int W);
-// resident workgroups per CU of the fused spread and gather kernels
-// (Ws, Wg: window widths of the spread and of the gather)
-void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gather_blocks);
+// resident workgroups per CU of the fused spread, gather and adjoint kernels
+// (Ws, Wg, Wd: their window widths)
+void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, int* gather_blocks,
+                     int* grad_blocks);
 // bytes of the split tiles of `rows` rows of dimension d
 int64_t split_tiles_bytes(int64_t rows, int d);
 
@@ -240,11 +253,13 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
                                int64_t chunk_len, const float* slice_max, const float* wscaled,
                                const WindowArgs& win, float* partial, hipStream_t stream);
 
-// spart[b*ldm + m] = sum over directions p of range b (prange per range, a
-// multiple of kFuseDirs; grid holds round_up(P, kFuseDirs) rows, zero past P) of the interpolated grid at tau <xi_p, y_m>, FP64.
+// The split's partial sums of the interpolated grid at tau <xi_p, y_m>, FP64:
+// row r of spart holds, for the targets of each tile, the directions of the
+// r-th run that meets the tile (grid holds round_up(P, kFuseDirs) rows, zero
+// past P).
 hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
-                               int P, GridGeom g, float pscale, const float* grid, int prange,
-                               const WindowArgs& win, double* spart, int64_t ldm,
+                               int P, GridGeom g, float pscale, const float* grid,
+                               const GatherSplit& split, const WindowArgs& win, double* spart, int64_t ldm,
                                hipStream_t stream);
 
 // Adjoint in the targets on the fused path:
@@ -254,11 +269,12 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
 // group g, 16-coordinate chunk q (DC = ceil(d/16)) and part (f16 hi, lo),
 // lane m + 16 k: 4 halves (xi_{16g + 4k + i})_{16q + m}, i < 4 (zero past P,
 // d).  dmax: the slots launch_fftconv filled with grid_d.
-// gpart: ceil(P / prange) x ldg x 16 DC floats of partial sums (ldg >= M).
-int64_t fused_grad_tile(int nr, int W, int d);    // targets per workgroup
+// gpart: a row of ldg x 16 DC floats (ldg >= M) of partial sums per run that
+// meets a tile.
+int64_t fused_grad_tile(int nr, int W, int d);    // targets per tile
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
                              const uint16_t* Ab, int P, GridGeom g, float pscale,
-                             const float* grid_d, const unsigned* dmax, int prange,
+                             const float* grid_d, const unsigned* dmax, const GatherSplit& split,
                              const WindowArgs& win, float* gpart, int64_t ldg, float coef, const float* v,
                              float* grad_y, hipStream_t stream);
 

@@ -1074,18 +1074,32 @@ __device__ __forceinline__ void reduce_tile(const double* __restrict__ spart, in
     s[m] = (float)(acc * scale);
 }
 
+// rows of partial sums of target tile t: the runs that meet it
+__device__ __forceinline__ int split_rows(const GatherSplit& sp, unsigned t) {
+    const unsigned u = t * sp.groups;
+    return (int)((u + sp.groups - 1) / sp.run - u / sp.run) + 1;
+}
+
+// split.run != 0: as many rows as runs meet the target's tile, else nb
 __global__ __launch_bounds__(kBlock) void reduce_kernel(
-    const double* __restrict__ spart, int nb, int64_t ldm, int64_t M,
+    const double* __restrict__ spart, int nb, GatherSplit split, int64_t ldm, int64_t M,
     double scale, float* __restrict__ s, BoundCheck bc) {
-    reduce_tile(spart, nb, ldm, M, scale, s, (int64_t)blockIdx.x * kBlock + threadIdx.x);
+    const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (split.run) {
+        // tiles are multiples of 64 targets: one tile per wave
+        const unsigned t = (unsigned)(m >> 6) / (split.tile >> 6);
+        nb = split_rows(split, __builtin_amdgcn_readfirstlane(t));
+    }
+    reduce_tile(spart, nb, ldm, M, scale, s, m);
     if (blockIdx.x == 0 && threadIdx.x < 64) finish_bound_check(bc);
 }
 
-hipError_t launch_reduce(const double* spart, int nb, int64_t ldm, int64_t M,
-                         double scale, float* s, const BoundCheck& bc, hipStream_t stream) {
+hipError_t launch_reduce(const double* spart, int nb, const GatherSplit& split, int64_t ldm,
+                         int64_t M, double scale, float* s, const BoundCheck& bc,
+                         hipStream_t stream) {
     dim3 grid((unsigned)((M + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(reduce_kernel, grid, dim3(kBlock), 0, stream, spart, nb, ldm, M, scale, s,
-                       bc);
+    hipLaunchKernelGGL(reduce_kernel, grid, dim3(kBlock), 0, stream, spart, nb, split, ldm, M,
+                       scale, s, bc);
     return hipGetLastError();
 }
 
@@ -1657,8 +1671,8 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 
 // Gather with projections computed in registers.  A workgroup owns the
 // TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(WIDE, W)) and
-// the direction range `range`
-// (prange directions, a multiple of kFuseDirs).  The grids of each group of 16
+// the directions p_begin .. p_end - 1
+// (p_begin a multiple of kFuseDirs), whose sums are row `row` of spart.  The grids of each group of 16
 // directions are staged in one of two LDS buffers while the previous group
 // is interpolated; lane (c, r) holds directions 4r .. 4r+3 of target c of each
 // batch.  Per target the four directions are summed in FP32, the groups in
@@ -1669,9 +1683,9 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 template <int W, int KB, bool WIDE>
 __device__ __forceinline__ void gather_fused_body(
     float* gls, const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
-    int P, const GridGeom& g, float pscale, const float* __restrict__ grid, int prange,
-    int stage, const WindowArgs& win, double* __restrict__ spart, int64_t ldm, int tile,
-    int range) {
+    const GridGeom& g, float pscale, const float* __restrict__ grid, int stage,
+    const WindowArgs& win, double* __restrict__ spart, int64_t ldm, int tile, int p_begin, int p_end,
+    int row) {
     constexpr int WAVES = kGatherWaves;
     constexpr int NB = gather_nb(WIDE, W);                     // batches per wave
     constexpr int TGT = WAVES * NB * 16;                           // targets per workgroup
@@ -1679,8 +1693,6 @@ __device__ __forceinline__ void gather_fused_body(
     const int c = lane & 15, r = lane >> 4;
     const int64_t mb = (int64_t)tile * TGT;
     const int64_t tw = (mb + wave * (NB * 16)) / 16;   // wave's first target tile
-    const int p_begin = range * prange;
-    const int p_end = min(P, p_begin + prange);
     if (WIDE) gather_stage_half(grid, p_begin, 0, g.nr, gls, wave, lane, WAVES);
     else gather_stage(grid, p_begin, g.nr, gls, wave, lane, WAVES);
     // target tiles past the last one read as zero
@@ -1746,19 +1758,37 @@ __device__ __forceinline__ void gather_fused_body(
         v += __shfl_xor(v, 16);
         v += __shfl_xor(v, 32);
         const int64_t m = mb + wave * (NB * 16) + 16 * b + c;
-        if (r == 0 && m < M) spart[(int64_t)range * ldm + m] = v;
+        if (r == 0 && m < M) spart[(int64_t)row * ldm + m] = v;
     }
 }
 
-// workgroup (x, y): target tile x, direction range y
+// Workgroup b: units b run .. (b + 1) run - 1 of the split, body(tile, first
+// direction, end, row) for each target tile they meet.
+template <class Body>
+__device__ __forceinline__ void for_run(const GatherSplit& sp, int P, Body body) {
+    unsigned u = blockIdx.x * sp.run;
+    const unsigned end = min(u + sp.run, sp.units);
+    while (true) {
+        const unsigned tile = u / sp.groups, u0 = tile * sp.groups;
+        const unsigned g0 = u - u0, g1 = min(sp.groups, end - u0);
+        body((int)tile, (int)(g0 * sp.step), min(P, (int)(g1 * sp.step)),
+             (int)(blockIdx.x - u0 / sp.run));
+        u += g1 - g0;
+        if (u >= end) break;
+        __syncthreads();               // no wave may still read the staging buffers
+    }
+}
+
 template <int W, int KB, bool WIDE>
 __global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At, int P,
-    GridGeom g, float pscale, const float* __restrict__ grid, int prange, int stage,
+    GridGeom g, float pscale, const float* __restrict__ grid, GatherSplit split, int stage,
     WindowArgs win, double* __restrict__ spart, int64_t ldm) {
     extern __shared__ float gls[];                    // 2 x stage floats
-    gather_fused_body<W, KB, WIDE>(gls, Yt, M, At, P, g, pscale, grid, prange, stage, win, spart, ldm,
-                             blockIdx.x, blockIdx.y);
+    for_run(split, P, [&](int tile, int p_begin, int p_end, int row) {
+        gather_fused_body<W, KB, WIDE>(gls, Yt, M, At, g, pscale, grid, stage, win, spart, ldm, tile,
+                                       p_begin, p_end, row);
+    });
 }
 
 // Adjoint in the targets, fused: t'_{m,p}, the derivative grid of direction
@@ -1774,9 +1804,9 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
 // interpolation.  Lane (c, r) holds t' of directions 4r + i of target c, the B
 // operand (column c, k = 4r + i); Ab holds per group, 16-coordinate chunk q
 // and part the A operand, lane m + 16k: (xi_{16 group + 4k + i})_{16 q + m},
-// i < 4 (zero past P and d).  Workgroup (x, y): grad_targets targets of tile
-// x, direction range y; writes gpart[(y * ldg + m) * 16 DC + i] (FP32, summed
-// over the ranges by grad_reduce_kernel).
+// i < 4 (zero past P and d).  Per tile of grad_targets
+// targets and run: row `row` of gpart, gpart[(row * ldg + m) * 16 DC + i] (FP32,
+// summed by grad_reduce_kernel).
 // waves of a workgroup: sixteen on wide grids where three batches fit in 128
 // registers (LDS holds one workgroup, eight waves are two per SIMD): the
 // adjoint above with the sum over the ranges 252 us with eight, 239 with sixteen
@@ -1788,21 +1818,19 @@ constexpr int grad_targets(bool wide, int KB, int W) {
 }
 
 template <int W, int KB, bool WIDE>
-__global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fused_kernel(
-    const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
-    const uint16_t* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
-    const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, int prange, int stage,
-    WindowArgs win, float* __restrict__ gpart, int64_t ldg) {
-    extern __shared__ float gls[];                    // 2 x stage floats
+__device__ __forceinline__ void gather_grad_body(
+    float* gls, const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
+    const uint16_t* __restrict__ Ab, int DC, const GridGeom& g, float pscale,
+    const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, int stage,
+    const WindowArgs& win, float* __restrict__ gpart, int64_t ldg, int tile, int p_begin, int p_end,
+    int row) {
     constexpr int WAVES = grad_waves(WIDE, KB, W), NB = grad_nb(WIDE, KB, W);
     constexpr int TGT = grad_targets(WIDE, KB, W);
     constexpr int MAXDC = 2 * KB;                     // 16-coordinate chunks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
-    const int64_t mb = (int64_t)blockIdx.x * TGT;
+    const int64_t mb = (int64_t)tile * TGT;
     const int64_t tw = (mb + wave * (NB * 16)) / 16;     // wave's first target tile
-    const int p_begin = blockIdx.y * prange;
-    const int p_end = min(P, p_begin + prange);
     if (WIDE) gather_stage_half(grid_d, p_begin, 0, g.nr, gls, wave, lane, WAVES);
     else gather_stage(grid_d, p_begin, g.nr, gls, wave, lane, WAVES);
     const int64_t ntiles = (M + 15) / 16;
@@ -1894,7 +1922,7 @@ __global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fuse
     for (int b = 0; b < NB; ++b) {
         const int64_t m = mb + wave * (NB * 16) + 16 * b + c;
         if (m >= M) continue;
-        float* __restrict__ dst = gpart + ((int64_t)blockIdx.y * ldg + m) * dcp + 4 * r;
+        float* __restrict__ dst = gpart + ((int64_t)row * ldg + m) * dcp + 4 * r;
 #pragma unroll
         for (int q = 0; q < MAXDC; ++q) {
             if (q >= DC) break;
@@ -1904,20 +1932,50 @@ __global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fuse
     }
 }
 
-// grad_y[m * d + i] = coef 2^e * v[m] * sum over ranges of gpart[(r * ldg + m) * 16 DC + i]
+template <int W, int KB, bool WIDE>
+__global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fused_kernel(
+    const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
+    const uint16_t* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
+    const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, GatherSplit split,
+    int stage, WindowArgs win, float* __restrict__ gpart, int64_t ldg) {
+    extern __shared__ float gls[];                    // 2 x stage floats
+    for_run(split, P, [&](int tile, int p_begin, int p_end, int row) {
+        gather_grad_body<W, KB, WIDE>(gls, Yt, M, At, Ab, DC, g, pscale, grid_d, dmax, stage, win,
+                                      gpart, ldg, tile, p_begin, p_end, row);
+    });
+}
+
+// grad_y[m * d + i] = coef 2^e * v[m] * sum over the rows r of m's tile of
+// gpart[(r * ldg + m) * 16 DC + i]: a thread per target and four coordinates
 __global__ __launch_bounds__(kBlock) void grad_reduce_kernel(
-    const float* __restrict__ gpart, int nrange, int64_t ldg, int DC, int64_t M, int d,
+    const float* __restrict__ gpart, GatherSplit split, int64_t ldg, int DC, int64_t M, int d,
     float coef, const unsigned* __restrict__ dmax, const float* __restrict__ v,
     float* __restrict__ grad_y) {
     coef = ldexpf(coef, slots_exponent(dmax, threadIdx.x & 63));
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= M * d) return;
-    const int64_t m = e / d;
-    const int i = (int)(e - m * d);
-    const int dcp = 16 * DC;
-    float s = 0.f;
-    for (int q = 0; q < nrange; ++q) s += gpart[((int64_t)q * ldg + m) * dcp + i];
-    grad_y[e] = coef * v[m] * s;
+    const int quads = 4 * DC, per = kBlock / quads;
+    const int64_t m0 = (int64_t)blockIdx.x * per;
+    const int mi = threadIdx.x / quads, i = 4 * (threadIdx.x - mi * quads);
+    // the block's targets lie in one tile or on both sides of its end
+    const unsigned t = (unsigned)(m0 >> 6) / (split.tile >> 6);
+    const int n0 = split_rows(split, t), n1 = split_rows(split, t + 1);
+    const int64_t m = m0 + mi;
+    if (mi >= per || m >= M || i >= d) return;
+    const int n = m < (int64_t)(t + 1) * split.tile ? n0 : n1;
+    const float4* __restrict__ src =
+        reinterpret_cast<const float4*>(gpart + m * 16 * DC + i);
+    const int64_t step = ldg * quads;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int q = 0; q < n; ++q) {
+        const float4 x = src[q * step];
+        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+    }
+    const float cv = coef * v[m];
+    float* __restrict__ dst = grad_y + m * d + i;
+    dst[0] = cv * s.x;
+    if (i + 1 < d) dst[1] = cv * s.y;
+    if (i + 2 < d) dst[2] = cv * s.z;
+    if (i + 3 < d) dst[3] = cv * s.w;
 }
 
 template <int W, int KB, int ACC>
@@ -1939,7 +1997,7 @@ void launch_spread_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
 template <int W, int KB, bool WIDE>
 void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Yt,
                            int64_t M, const uint16_t* At, int P, const GridGeom& g, float pscale,
-                           const float* gridv, int prange, int stage, const WindowArgs& win,
+                           const float* gridv, const GatherSplit& split, int stage, const WindowArgs& win,
                            double* spart, int64_t ldm) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
@@ -1949,14 +2007,14 @@ void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
         attr_set = true;
     }
     hipLaunchKernelGGL((gather_fused_kernel<W, KB, WIDE>), grid, dim3(64 * kGatherWaves), lds, stream, Yt,
-                       M, At, P, g, pscale, gridv, prange, stage, win, spart, ldm);
+                       M, At, P, g, pscale, gridv, split, stage, win, spart, ldm);
 }
 
 template <int W, int KB, bool WIDE>
 void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Yt,
                           int64_t M, const uint16_t* At, const uint16_t* Ab, int DC, int P,
                           const GridGeom& g, float pscale, const float* grid_d,
-                          const unsigned* dmax, int prange, int stage, const WindowArgs& win,
+                          const unsigned* dmax, const GatherSplit& split, int stage, const WindowArgs& win,
                           float* gpart, int64_t ldg) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
@@ -1966,22 +2024,28 @@ void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint1
         attr_set = true;
     }
     hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, WIDE>), grid, dim3(64 * grad_waves(WIDE, KB, W)), lds, stream,
-                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win, gpart, ldg);
+                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, split, stage, win, gpart, ldg);
 }
 
 int64_t fused_grad_tile(int nr, int W, int d) { return grad_targets(fused_wide(nr), split_kblocks(d), W); }
 
 size_t abs_slots_uints() { return kAbsUints; }
 
+namespace {
+dim3 split_grid(const GatherSplit& sp) { return dim3((unsigned)((sp.units + sp.run - 1) / sp.run)); }
+}  // namespace
+
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
                              const uint16_t* Ab, int P, GridGeom g, float pscale,
-                             const float* grid_d, const unsigned* dmax, int prange,
+                             const float* grid_d, const unsigned* dmax, const GatherSplit& split,
                              const WindowArgs& win, float* gpart, int64_t ldg, float coef, const float* v,
                              float* grad_y, hipStream_t stream) {
-    if (!fused_supported(d, g.nr) || prange % kFuseDirs != 0 || M > ldg) return hipErrorInvalidValue;
+    if (!fused_supported(d, g.nr) || M > ldg || (int64_t)split.tile != fused_grad_tile(g.nr, W, d))
+        return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
                        const uint16_t*, int, int, const GridGeom&, float, const float*,
-                       const unsigned*, int, int, const WindowArgs&, float*, int64_t);
+                       const unsigned*, const GatherSplit&, int, const WindowArgs&, float*,
+                       int64_t);
     static const L t[2][5][2] = {
         {{launch_gather_grad_t<3, 1, false>, launch_gather_grad_t<3, 2, false>},
          {launch_gather_grad_t<4, 1, false>, launch_gather_grad_t<4, 2, false>},
@@ -1998,17 +2062,14 @@ hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const 
     const int DC = (d + 15) / 16;
     const bool wide = fused_wide(g.nr);
     const int stage = gather_stage_floats(g.nr, wide);
-    const int nrange = (P + prange - 1) / prange;
-    const int64_t tgt = fused_grad_tile(g.nr, W, d);
-    dim3 gd((unsigned)((M + tgt - 1) / tgt), (unsigned)nrange);
-    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)2 * stage * sizeof(float), stream,
-                                      Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, prange, stage, win,
+    t[wide][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
+                                      Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, split, stage, win,
                                       gpart, ldg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((M * d + kBlock - 1) / kBlock)),
-                       dim3(kBlock), 0, stream, gpart, nrange, ldg, DC, M, d, coef, dmax, v,
-                       grad_y);
+    const int per = kBlock / (4 * DC);
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((M + per - 1) / per)), dim3(kBlock), 0,
+                       stream, gpart, split, ldg, DC, M, d, coef, dmax, v, grad_y);
     return hipGetLastError();
 }
 
@@ -2058,13 +2119,13 @@ hipError_t launch_slice_max(const float* w, int64_t N, float* slice_max, float* 
     return hipGetLastError();
 }
 
-void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gather_blocks) {
-    *spread_blocks = 1;
-    *gather_blocks = 1;
+void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, int* gather_blocks,
+                     int* grad_blocks) {
+    *spread_blocks = *gather_blocks = *grad_blocks = 1;
     if (!fused_supported(d, nr)) return;
     const bool wide = fused_wide(nr);
-    // occupancy is set by LDS and registers; the larger operand shape
-    // stands for both
+    // the spread's occupancy is set by LDS and registers; the larger operand
+    // shape stands for both
     const void* sks[3][5] = {
         {(const void*)&spread_fused_kernel<3, 2, kFuseAccCopies>,
          (const void*)&spread_fused_kernel<4, 2, kFuseAccCopies>,
@@ -2081,28 +2142,48 @@ void fused_occupancy(int Ws, int Wg, int d, int nr, int* spread_blocks, int* gat
          (const void*)&spread_fused_kernel<5, 2, kFuseAccWide>,
          (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
          (const void*)&spread_fused_kernel<8, 2, kFuseAccWide>}};
-    const void* gks[2][5] = {
-        {(const void*)&gather_fused_kernel<3, 2, false>, (const void*)&gather_fused_kernel<4, 2, false>,
-         (const void*)&gather_fused_kernel<5, 2, false>, (const void*)&gather_fused_kernel<6, 2, false>,
-         (const void*)&gather_fused_kernel<8, 2, false>},
-        {(const void*)&gather_fused_kernel<3, 2, true>, (const void*)&gather_fused_kernel<4, 2, true>,
-         (const void*)&gather_fused_kernel<5, 2, true>, (const void*)&gather_fused_kernel<6, 2, true>,
-         (const void*)&gather_fused_kernel<8, 2, true>}};
-    const int si = width_index(Ws), gi = width_index(Wg);
-    if (si < 0 || gi < 0) return;
+    using K = const void*;
+    const K gks[2][5][2] = {
+        {{(K)&gather_fused_kernel<3, 1, false>, (K)&gather_fused_kernel<3, 2, false>},
+         {(K)&gather_fused_kernel<4, 1, false>, (K)&gather_fused_kernel<4, 2, false>},
+         {(K)&gather_fused_kernel<5, 1, false>, (K)&gather_fused_kernel<5, 2, false>},
+         {(K)&gather_fused_kernel<6, 1, false>, (K)&gather_fused_kernel<6, 2, false>},
+         {(K)&gather_fused_kernel<8, 1, false>, (K)&gather_fused_kernel<8, 2, false>}},
+        {{(K)&gather_fused_kernel<3, 1, true>, (K)&gather_fused_kernel<3, 2, true>},
+         {(K)&gather_fused_kernel<4, 1, true>, (K)&gather_fused_kernel<4, 2, true>},
+         {(K)&gather_fused_kernel<5, 1, true>, (K)&gather_fused_kernel<5, 2, true>},
+         {(K)&gather_fused_kernel<6, 1, true>, (K)&gather_fused_kernel<6, 2, true>},
+         {(K)&gather_fused_kernel<8, 1, true>, (K)&gather_fused_kernel<8, 2, true>}}};
+    const K dks[2][5][2] = {
+        {{(K)&gather_grad_fused_kernel<3, 1, false>, (K)&gather_grad_fused_kernel<3, 2, false>},
+         {(K)&gather_grad_fused_kernel<4, 1, false>, (K)&gather_grad_fused_kernel<4, 2, false>},
+         {(K)&gather_grad_fused_kernel<5, 1, false>, (K)&gather_grad_fused_kernel<5, 2, false>},
+         {(K)&gather_grad_fused_kernel<6, 1, false>, (K)&gather_grad_fused_kernel<6, 2, false>},
+         {(K)&gather_grad_fused_kernel<8, 1, false>, (K)&gather_grad_fused_kernel<8, 2, false>}},
+        {{(K)&gather_grad_fused_kernel<3, 1, true>, (K)&gather_grad_fused_kernel<3, 2, true>},
+         {(K)&gather_grad_fused_kernel<4, 1, true>, (K)&gather_grad_fused_kernel<4, 2, true>},
+         {(K)&gather_grad_fused_kernel<5, 1, true>, (K)&gather_grad_fused_kernel<5, 2, true>},
+         {(K)&gather_grad_fused_kernel<6, 1, true>, (K)&gather_grad_fused_kernel<6, 2, true>},
+         {(K)&gather_grad_fused_kernel<8, 1, true>, (K)&gather_grad_fused_kernel<8, 2, true>}}};
+    const int si = width_index(Ws), gi = width_index(Wg), di = width_index(Wd);
+    if (si < 0 || gi < 0 || di < 0) return;
+    const int kb = split_kblocks(d);
     const void* sk = sks[spread_copies(nr) ? 0 : wide ? 2 : 1][si];
-    const void* gk = gks[wide][gi];
-    const int stage = gather_stage_floats(nr, wide);
     (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize, kSpreadMaxLds);
-    (void)hipFuncSetAttribute(gk, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              2 * kFuseMaxCells * (int)sizeof(float));
     int b = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, sk, kSpreadBlock,
                                                      fused_spread_lds(nr)) == hipSuccess && b > 0)
         *spread_blocks = b;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, gk, 64 * kGatherWaves,
-                                                     (size_t)2 * stage * sizeof(float)) == hipSuccess && b > 0)
-        *gather_blocks = b;
+    const size_t lds = (size_t)2 * gather_stage_floats(nr, wide) * sizeof(float);
+    auto gather_blocks_of = [&](K k, int threads, int* out) {
+        (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  2 * kFuseMaxCells * (int)sizeof(float));
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds) == hipSuccess && n > 0)
+            *out = n;
+    };
+    gather_blocks_of(gks[wide][gi][kb - 1], 64 * kGatherWaves, gather_blocks);
+    gather_blocks_of(dks[wide][di][kb - 1], 64 * grad_waves(wide, kb, Wd), grad_blocks);
 }
 
 hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, const uint16_t* At,
@@ -2141,12 +2222,14 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
 }
 
 hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
-                               int P, GridGeom g, float pscale, const float* grid, int prange,
+                               int P, GridGeom g, float pscale, const float* grid,
+                               const GatherSplit& split,
                                const WindowArgs& win, double* spart, int64_t ldm,
                                hipStream_t stream) {
-    if (!fused_supported(d, g.nr) || prange % kFuseDirs != 0) return hipErrorInvalidValue;
+    if (!fused_supported(d, g.nr) || (int64_t)split.tile != fused_gather_tile(g.nr, W))
+        return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*, int,
-                       const GridGeom&, float, const float*, int, int, const WindowArgs&, double*,
+                       const GridGeom&, float, const float*, const GatherSplit&, int, const WindowArgs&, double*,
                        int64_t);
     static const L t[2][5][2] = {
         {{launch_gather_fused_t<3, 1, false>, launch_gather_fused_t<3, 2, false>},
@@ -2164,11 +2247,8 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
     // one staging buffer: the group's grids rounded up to whole 1 KB pieces
     const bool wide = fused_wide(g.nr);
     const int stage = gather_stage_floats(g.nr, wide);
-    const int64_t tgt = fused_gather_tile(g.nr, W);
-    dim3 gd((unsigned)((M + tgt - 1) / tgt),
-            (unsigned)((P + prange - 1) / prange));
-    t[wide][wi][split_kblocks(d) - 1](gd, (size_t)2 * stage * sizeof(float), stream,
-                                      Yt, M, At, P, g, pscale, grid, prange, stage, win, spart,
+    t[wide][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
+                                      Yt, M, At, P, g, pscale, grid, split, stage, win, spart,
                                       ldm);
     return hipGetLastError();
 }
@@ -2334,14 +2414,15 @@ __global__ __launch_bounds__(64 * kGatherWaves) void batch_gather_fused_kernel(
         const int stage = gather_stage_floats(pr.g.nr, false);
         const uint16_t* yt = pr.same_xy ? pr.xt : pr.yt;
         const WindowArgs win = pr.gwin;
+        const int p0 = tk.b * pr.pg, p1 = min(P, p0 + pr.pg);
         // no wave may still read the staging buffers of the previous task
         __syncthreads();
         if (pr.kb == 1)
-            gather_fused_body<W, 1, false>(bgls, yt, pr.M, pr.at, P, pr.g, pr.pscale, pr.grid, pr.pg,
-                                    stage, win, pr.spart, pr.ldm, tk.a, tk.b);
+            gather_fused_body<W, 1, false>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
+                                           pr.spart, pr.ldm, tk.a, p0, p1, tk.b);
         else
-            gather_fused_body<W, 2, false>(bgls, yt, pr.M, pr.at, P, pr.g, pr.pscale, pr.grid, pr.pg,
-                                    stage, win, pr.spart, pr.ldm, tk.a, tk.b);
+            gather_fused_body<W, 2, false>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
+                                           pr.spart, pr.ldm, tk.a, p0, p1, tk.b);
     }
 }
 

@@ -459,7 +459,7 @@ struct fastsum_plan_s {
     bool sorted = false;              // exact energy sums by sorting, no Fourier buffers
     bool have_proj = false;           // last exec stored its projections
     int64_t tune_chunk_len = 0;       // fastsum_set_launch overrides (0: rule)
-    int64_t spread_slots = 1, gather_slots = 1;   // resident fused workgroups on the device
+    int64_t spread_slots = 1, gather_slots = 1, grad_slots = 1;   // resident fused workgroups on the device
     int tune_dir_range = 0;
     float bound = 0.f;
     int device = 0;
@@ -637,7 +637,7 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
                              pl->gwin, pl->spart, pl->ldm, nullptr, 0, st));
     }
     PhaseTimer t(pl, FASTSUM_PHASE_REDUCE, st);
-    FS_TRY(launch_reduce(pl->spart, ng, pl->ldm, Mtgt, 1.0 / P, out, bc, st));
+    FS_TRY(launch_reduce(pl->spart, ng, GatherSplit{}, pl->ldm, Mtgt, 1.0 / P, out, bc, st));
     return FASTSUM_OK;
 }
 
@@ -649,6 +649,40 @@ fastsum_status sum_pass(fastsum_plan_s* pl, const float* src_proj, int64_t ld_sr
 // prefix of the sources (0 otherwise): their norms are checked as targets'.
 int64_t prefix_rows(const float* x, int64_t N, const float* y, int64_t M) {
     return x == y && M < N ? M : 0;
+}
+
+// The split of a fused gather over `slots` resident workgroups: one run each,
+// all within a unit of the same length, at most max_rows rows per tile.
+// dir_range (fastsum_set_launch): that many directions of one tile per run
+// (beyond P: all).
+// Rounds of (tile, direction range) workgroups left slots idle in the last
+// round and loaded a tile's targets once per range.
+GatherSplit gather_split(int64_t M, int P, int64_t tile, int64_t slots, int max_rows, int dir_range) {
+    GatherSplit sp;
+    const int64_t tiles = (M + tile - 1) / tile;
+    sp.tile = (unsigned)tile;
+    sp.step = kFuseDirs;
+    if (dir_range > 0) sp.step = (unsigned)std::min<int64_t>(dir_range, round_up(P, kFuseDirs));
+    auto groups = [&] { return ((int64_t)P + sp.step - 1) / sp.step; };
+    while (dir_range <= 0 && tiles * groups() > INT32_MAX) sp.step *= 2;
+    sp.groups = (unsigned)groups();
+    sp.units = (unsigned)(tiles * sp.groups);
+    sp.run = 1;
+    if (dir_range > 0) return sp;
+    int64_t run = (sp.units + slots - 1) / slots;
+    // `groups` units meet at most ceil((groups - 1) / run) + 1 runs
+    if (max_rows < (int)sp.groups)
+        run = max_rows < 2 ? round_up(run, (int64_t)sp.groups)
+                           : std::max<int64_t>(run, ((int64_t)sp.groups + max_rows - 3) / (max_rows - 1));
+    sp.run = (unsigned)std::min<int64_t>(run, sp.units);
+    return sp;
+}
+
+// rows of spart, at most; `even`: as many for every tile
+int split_max_rows(const GatherSplit& sp, bool* even) {
+    *even = sp.groups % sp.run == 0;
+    if (*even) return (int)(sp.groups / sp.run);
+    return (int)std::min<unsigned>(sp.groups, (sp.groups - 1 + sp.run - 1) / sp.run + 1);
 }
 
 // Spread (sources xt, weights w in pl->wscaled), FFT convolution (and the derivative grids
@@ -673,18 +707,18 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, cons
                               grid_d ? pl->mult_d : nullptr, grid, grid_d, grid_d ? dmax : nullptr,
                               st));
     }
-    const int prange = pl->tune_dir_range > 0 ? pl->tune_dir_range
-                                              : fused_dir_range(M, P, pl->gather_slots, pl->geom.nr, pl->Wg);
-    const int nrange = (P + prange - 1) / prange;
+    const GatherSplit split = gather_split(M, P, fused_gather_tile(pl->geom.nr, pl->Wg),
+                                           pl->gather_slots, pl->ngroup_cap, pl->tune_dir_range);
     pl->last_nchunk = nchunk;
-    pl->last_ngroup = nrange;
+    bool even = false;
+    pl->last_ngroup = split_max_rows(split, &even);
     {
         PhaseTimer t(pl, FASTSUM_PHASE_GATHER, st);
         FS_TRY(launch_gather_fused(pl->Wg, yt, M, pl->d, pl->at, P, pl->geom, pscale, grid,
-                                   prange, pl->gwin, pl->spart, pl->ldm, st));
+                                   split, pl->gwin, pl->spart, pl->ldm, st));
     }
     PhaseTimer t(pl, FASTSUM_PHASE_REDUCE, st);
-    FS_TRY(launch_reduce(pl->spart, nrange, pl->ldm, M, 1.0 / P, out, bc, st));
+    FS_TRY(launch_reduce(pl->spart, pl->last_ngroup, even ? GatherSplit{} : split, pl->ldm, M, 1.0 / P, out, bc, st));
     return FASTSUM_OK;
 }
 
@@ -707,34 +741,17 @@ fastsum_status fused_pass(fastsum_plan_s* pl, const float* x, const float* w, in
                      (pl->r.p.flags & FASTSUM_FLAG_GRAD) ? pl->grid_d : nullptr, pl->dmax, bc, st);
 }
 
-// Direction ranges of the fused adjoint gather (whole 16-direction groups),
-// one partial sum of a target's gradient each: the fullest rounds of
-// workgroups, less 2% per range (M rows more to write and to sum), within the
-// rows that gpart holds.  "Three rounds, four ranges at most" left 47% of the
-// slots at work at M = 15013, d = 50, P = 1000 and 76% at M = 200000, d = 20,
-// P = 512: 58 + 7 us (kernel, sum over the ranges) against 40 + 9 with eight
-// ranges, 258 + 19 against 230 + 22 with three (five: 232 + 31).
-constexpr int kGradMaxRanges = 16;
+constexpr int kGradMaxRows = 16;
 
-// gpart rows (one target's partial sum each) of a plan of cap targets: four
-// ranges of any call, more of smaller ones
+// gpart rows (one target's partial sum each) of a plan of cap targets: four per
+// target of any call, more of smaller ones
 int64_t grad_rows(int64_t cap) {
-    return std::max<int64_t>(4 * cap, std::min<int64_t>(kGradMaxRanges * cap, 1 << 18));
+    return std::max<int64_t>(4 * cap, std::min<int64_t>(kGradMaxRows * cap, 1 << 18));
 }
 
-int fused_grad_range(const fastsum_plan_s* pl, int64_t M) {
-    const int64_t tile = fused_grad_tile(pl->geom.nr, pl->Wd, pl->d), tiles = (M + tile - 1) / tile;
-    const int64_t P = pl->P, slots = pl->gather_slots;
-    const int64_t groups = (P + kFuseDirs - 1) / kFuseDirs;
-    const int64_t most = std::min({(int64_t)kGradMaxRanges, groups, pl->gpart_rows / M});
-    int64_t best_pr = groups * kFuseDirs;
-    double best = -1.0;
-    for (int64_t r = 1; r <= most; ++r) {
-        const int64_t pr = round_up((P + r - 1) / r, kFuseDirs);
-        const double score = round_efficiency(tiles * ((P + pr - 1) / pr), slots) - 0.02 * r;
-        if (score > best) { best = score; best_pr = pr; }
-    }
-    return (int)best_pr;
+GatherSplit grad_split(const fastsum_plan_s* pl, int64_t M) {
+    return gather_split(M, pl->P, fused_grad_tile(pl->geom.nr, pl->Wd, pl->d), pl->grad_slots,
+                        (int)std::min<int64_t>(kGradMaxRows, pl->gpart_rows / M), 0);
 }
 
 // Stored projections of X into out (row stride ld); sink: the bound check's
@@ -924,12 +941,13 @@ fastsum_status fastsum_plan_create(const fastsum_params* prm, const float* xi, i
                 r.p.proj == FASTSUM_PROJ_FP32 &&
                 fused_supported(pl->d, nr);
     if (pl->fused) {
-        int ncu = 0, sb = 1, gb = 1;
+        int ncu = 0, sb = 1, gb = 1, db = 1;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess || ncu < 1)
             ncu = 1;
-        fused_occupancy(pl->Ws, pl->Wg, pl->d, nr, &sb, &gb);
+        fused_occupancy(pl->Ws, pl->Wg, pl->Wd, pl->d, nr, &sb, &gb, &db);
         pl->spread_slots = (int64_t)ncu * sb;
         pl->gather_slots = (int64_t)ncu * gb;
+        pl->grad_slots = (int64_t)ncu * db;
         // the rule never takes more than kFusedMaxChunks (or N / 2^20) chunks
         pl->nchunk_cap = std::max<int>(pl->nchunk_cap, (int)std::max<int64_t>(
                                            kFusedMaxChunks, (cap + kMaxChunk - 1) / kMaxChunk));
@@ -1190,7 +1208,7 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
         if (grad_y) {
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, yt, M, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
-                                     pl->grid_d, pl->dmax, fused_grad_range(pl, M),
+                                     pl->grid_d, pl->dmax, grad_split(pl, M),
                                      pl->dwin, pl->gpart, M, fcoef, grad_s, grad_y, st));
         }
         if (grad_w || grad_x) {
@@ -1208,7 +1226,7 @@ fastsum_status fastsum_grad_xyw(fastsum_plan pl, const float* grad_s, float* gra
             PhaseTimer t(pl, FASTSUM_PHASE_BACKPROJECT, st);
             FS_TRY(launch_grad_fused(pl->Wd, pl->xt, N, pl->d, pl->at, pl->ab, P, pl->geom, pscale,
                                      pl->grid_wd, pl->dmax + abs_slots_uints(),
-                                     fused_grad_range(pl, N),
+                                     grad_split(pl, N),
                                      pl->dwin, pl->gpart, N, fcoef, pl->last_w, grad_x, st));
         }
         return FASTSUM_OK;

@@ -857,7 +857,7 @@ hipError_t launch_sorted_bucket_reduce(const float* stv, const unsigned short* s
                        dim3(kBucketThreads), 0, stream, stv, sti, P, prange, ldm, M, part);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce(part, (P + prange - 1) / prange, ldm, M, scale, s, bc, stream);
+    return launch_reduce(part, (P + prange - 1) / prange, GatherSplit{}, ldm, M, scale, s, bc, stream);
 }
 
 }  // namespace fastsum
