@@ -216,8 +216,9 @@ bool fused_supported(int d, int nr);
 // grids too wide for the narrow fused kernels (16 nr > 16384 cells): the
 // wide variants (batched plans take only narrow grids)
 bool fused_wide(int nr);
-// targets per fused gather workgroup (grids of nr cells, window width W)
-int64_t fused_gather_tile(int nr, int W);
+// targets per tile of the fused gather (grids of nr cells, window width W);
+// few: the small tiles of problems that leave workgroups without work
+int64_t fused_gather_tile(int nr, int W, bool few);
 // resident workgroups per CU of the fused spread, gather and adjoint kernels
 // (Ws, Wg, Wd: their window widths)
 void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, int* gather_blocks,
@@ -271,7 +272,7 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
 // d).  dmax: the slots launch_fftconv filled with grid_d.
 // gpart: a row of ldg x 16 DC floats (ldg >= M) of partial sums per run that
 // meets a tile.
-int64_t fused_grad_tile(int nr, int W, int d);    // targets per tile
+int64_t fused_grad_tile(int nr, int W, int d, bool few);    // targets per tile
 hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const uint16_t* At,
                              const uint16_t* Ab, int P, GridGeom g, float pscale,
                              const float* grid_d, const unsigned* dmax, const GatherSplit& split,

@@ -1207,7 +1207,7 @@ constexpr int kFuseAcc = 32;                               // FP32 cell accumula
 constexpr int kFuseMaxCells = kFuseAcc * kSpreadBlock;     // kFuseDirs * nr <= this
 // wide grids (kFuseDirs * nr up to 16 x 2048, e.g. the energy kernel at
 // T = 0.45): twice the accumulators, one workgroup per CU, and the gathers
-// stage one group's grids at a time (two would not fit in LDS)
+// stage half a group of grids at a time
 constexpr int kFuseAccWide = 64;
 // grids with copies (at most kCopyMaxCells cells): fewer accumulators
 constexpr int kFuseAccCopies = 8;
@@ -1215,12 +1215,19 @@ constexpr int kFuseMaxCellsWide = kFuseAccWide * kSpreadBlock;
 // LDS of the widest spread: its cells and spare cells
 constexpr int kSpreadMaxLds = (kFuseMaxCellsWide + 2 * kMaxSpareCells * 16) * (int)sizeof(int);
 constexpr int kGatherWaves = 8;
-constexpr int kGatherNB = 8;                               // 16-target batches per wave
-// wide grids: fewer batches (registers; W = 8 takes three).  Eight batches
+// Modes of the gathers.  kWide: wide grids (fused_wide).  kFew: problems with
+// less than a tile and group of the large mode per resident workgroup take
+// tiles of a quarter or half of the targets instead (M = 3001, P = 256: 48 of
+// 256 CUs had work, the gather took 7.1 us, 4.4 with small tiles).
+enum GatherMode { kLarge = 0, kWide = 1, kFew = 2 };
+// 16-target batches per wave: eight, two in small tiles, and on
+// wide grids four (registers; W = 8 takes three).  Eight batches there
 // fit at up to five taps, but 512-target tiles fill the rounds better: the
 // MMD energy gather (d = 20, M = 2e5, P = 512) took 198 us with eight, 180
 // with four
-constexpr int gather_nb(bool wide, int W) { return !wide ? kGatherNB : W >= 8 ? 3 : 4; }
+constexpr int gather_nb(int mode, int W) {
+    return mode == kLarge ? 8 : mode == kFew ? 2 : W >= 8 ? 3 : 4;
+}
 // row of the dispatch tables of window width W (-1: none)
 constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
 
@@ -1670,7 +1677,7 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 }
 
 // Gather with projections computed in registers.  A workgroup owns the
-// TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(WIDE, W)) and
+// TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(MODE, W)) and
 // the directions p_begin .. p_end - 1
 // (p_begin a multiple of kFuseDirs), whose sums are row `row` of spart.  The grids of each group of 16
 // directions are staged in one of two LDS buffers while the previous group
@@ -1680,14 +1687,15 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 // (gather_stage_half); a single buffer, refilled between two barriers, took
 // 193 us for the sum and 274 for the adjoint at M = 200000, d = 20, P = 512,
 // nr = 1856, halves take 187 and 258.
-template <int W, int KB, bool WIDE>
+template <int W, int KB, int MODE>
 __device__ __forceinline__ void gather_fused_body(
     float* gls, const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
     const GridGeom& g, float pscale, const float* __restrict__ grid, int stage,
     const WindowArgs& win, double* __restrict__ spart, int64_t ldm, int tile, int p_begin, int p_end,
     int row) {
     constexpr int WAVES = kGatherWaves;
-    constexpr int NB = gather_nb(WIDE, W);                     // batches per wave
+    constexpr bool WIDE = MODE == kWide;
+    constexpr int NB = gather_nb(MODE, W);                     // batches per wave
     constexpr int TGT = WAVES * NB * 16;                           // targets per workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
@@ -1779,14 +1787,14 @@ __device__ __forceinline__ void for_run(const GatherSplit& sp, int P, Body body)
     }
 }
 
-template <int W, int KB, bool WIDE>
+template <int W, int KB, int MODE>
 __global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At, int P,
     GridGeom g, float pscale, const float* __restrict__ grid, GatherSplit split, int stage,
     WindowArgs win, double* __restrict__ spart, int64_t ldm) {
     extern __shared__ float gls[];                    // 2 x stage floats
     for_run(split, P, [&](int tile, int p_begin, int p_end, int row) {
-        gather_fused_body<W, KB, WIDE>(gls, Yt, M, At, g, pscale, grid, stage, win, spart, ldm, tile,
+        gather_fused_body<W, KB, MODE>(gls, Yt, M, At, g, pscale, grid, stage, win, spart, ldm, tile,
                                        p_begin, p_end, row);
     });
 }
@@ -1810,22 +1818,27 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
 // waves of a workgroup: sixteen on wide grids where three batches fit in 128
 // registers (LDS holds one workgroup, eight waves are two per SIMD): the
 // adjoint above with the sum over the ranges 252 us with eight, 239 with sixteen
-constexpr int grad_waves(bool wide, int KB, int W) { return wide && KB == 1 && W <= 5 ? 16 : 8; }
+constexpr int grad_waves(int mode, int KB, int W) {
+    return mode == kWide && KB == 1 && W <= 5 ? 16 : 8;
+}
 // 16-target batches per wave
-constexpr int grad_nb(bool wide, int KB, int W) { return grad_waves(wide, KB, W) == 16 ? 3 : 4; }
-constexpr int grad_targets(bool wide, int KB, int W) {
-    return grad_waves(wide, KB, W) * grad_nb(wide, KB, W) * 16;
+constexpr int grad_nb(int mode, int KB, int W) {
+    return mode == kFew ? 2 : grad_waves(mode, KB, W) == 16 ? 3 : 4;
+}
+constexpr int grad_targets(int mode, int KB, int W) {
+    return grad_waves(mode, KB, W) * grad_nb(mode, KB, W) * 16;
 }
 
-template <int W, int KB, bool WIDE>
+template <int W, int KB, int MODE>
 __device__ __forceinline__ void gather_grad_body(
     float* gls, const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
     const uint16_t* __restrict__ Ab, int DC, const GridGeom& g, float pscale,
     const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, int stage,
     const WindowArgs& win, float* __restrict__ gpart, int64_t ldg, int tile, int p_begin, int p_end,
     int row) {
-    constexpr int WAVES = grad_waves(WIDE, KB, W), NB = grad_nb(WIDE, KB, W);
-    constexpr int TGT = grad_targets(WIDE, KB, W);
+    constexpr bool WIDE = MODE == kWide;
+    constexpr int WAVES = grad_waves(MODE, KB, W), NB = grad_nb(MODE, KB, W);
+    constexpr int TGT = grad_targets(MODE, KB, W);
     constexpr int MAXDC = 2 * KB;                     // 16-coordinate chunks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
@@ -1932,15 +1945,15 @@ __device__ __forceinline__ void gather_grad_body(
     }
 }
 
-template <int W, int KB, bool WIDE>
-__global__ __launch_bounds__(64 * grad_waves(WIDE, KB, W)) void gather_grad_fused_kernel(
+template <int W, int KB, int MODE>
+__global__ __launch_bounds__(64 * grad_waves(MODE, KB, W)) void gather_grad_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At,
     const uint16_t* __restrict__ Ab, int DC, int P, GridGeom g, float pscale,
     const float* __restrict__ grid_d, const unsigned* __restrict__ dmax, GatherSplit split,
     int stage, WindowArgs win, float* __restrict__ gpart, int64_t ldg) {
     extern __shared__ float gls[];                    // 2 x stage floats
     for_run(split, P, [&](int tile, int p_begin, int p_end, int row) {
-        gather_grad_body<W, KB, WIDE>(gls, Yt, M, At, Ab, DC, g, pscale, grid_d, dmax, stage, win,
+        gather_grad_body<W, KB, MODE>(gls, Yt, M, At, Ab, DC, g, pscale, grid_d, dmax, stage, win,
                                       gpart, ldg, tile, p_begin, p_end, row);
     });
 }
@@ -1994,23 +2007,23 @@ void launch_spread_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
                        Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win, partial);
 }
 
-template <int W, int KB, bool WIDE>
+template <int W, int KB, int MODE>
 void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Yt,
                            int64_t M, const uint16_t* At, int P, const GridGeom& g, float pscale,
                            const float* gridv, const GatherSplit& split, int stage, const WindowArgs& win,
                            double* spart, int64_t ldm) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_fused_kernel<W, KB, WIDE>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_fused_kernel<W, KB, MODE>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   2 * kFuseMaxCells * (int)sizeof(float));
         attr_set = true;
     }
-    hipLaunchKernelGGL((gather_fused_kernel<W, KB, WIDE>), grid, dim3(64 * kGatherWaves), lds, stream, Yt,
+    hipLaunchKernelGGL((gather_fused_kernel<W, KB, MODE>), grid, dim3(64 * kGatherWaves), lds, stream, Yt,
                        M, At, P, g, pscale, gridv, split, stage, win, spart, ldm);
 }
 
-template <int W, int KB, bool WIDE>
+template <int W, int KB, int MODE>
 void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Yt,
                           int64_t M, const uint16_t* At, const uint16_t* Ab, int DC, int P,
                           const GridGeom& g, float pscale, const float* grid_d,
@@ -2018,16 +2031,18 @@ void launch_gather_grad_t(dim3 grid, size_t lds, hipStream_t stream, const uint1
                           float* gpart, int64_t ldg) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_grad_fused_kernel<W, KB, WIDE>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gather_grad_fused_kernel<W, KB, MODE>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   2 * kFuseMaxCells * (int)sizeof(float));
         attr_set = true;
     }
-    hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, WIDE>), grid, dim3(64 * grad_waves(WIDE, KB, W)), lds, stream,
+    hipLaunchKernelGGL((gather_grad_fused_kernel<W, KB, MODE>), grid, dim3(64 * grad_waves(MODE, KB, W)), lds, stream,
                        Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, split, stage, win, gpart, ldg);
 }
 
-int64_t fused_grad_tile(int nr, int W, int d) { return grad_targets(fused_wide(nr), split_kblocks(d), W); }
+int64_t fused_grad_tile(int nr, int W, int d, bool few) {
+    return grad_targets(fused_wide(nr) ? kWide : few ? kFew : kLarge, split_kblocks(d), W);
+}
 
 size_t abs_slots_uints() { return kAbsUints; }
 
@@ -2040,29 +2055,35 @@ hipError_t launch_grad_fused(int W, const uint16_t* Yt, int64_t M, int d, const 
                              const float* grid_d, const unsigned* dmax, const GatherSplit& split,
                              const WindowArgs& win, float* gpart, int64_t ldg, float coef, const float* v,
                              float* grad_y, hipStream_t stream) {
-    if (!fused_supported(d, g.nr) || M > ldg || (int64_t)split.tile != fused_grad_tile(g.nr, W, d))
+    const bool few = !fused_wide(g.nr) && (int64_t)split.tile == fused_grad_tile(g.nr, W, d, true);
+    if (!fused_supported(d, g.nr) || M > ldg || (int64_t)split.tile != fused_grad_tile(g.nr, W, d, few))
         return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*,
                        const uint16_t*, int, int, const GridGeom&, float, const float*,
                        const unsigned*, const GatherSplit&, int, const WindowArgs&, float*,
                        int64_t);
-    static const L t[2][5][2] = {
-        {{launch_gather_grad_t<3, 1, false>, launch_gather_grad_t<3, 2, false>},
-         {launch_gather_grad_t<4, 1, false>, launch_gather_grad_t<4, 2, false>},
-         {launch_gather_grad_t<5, 1, false>, launch_gather_grad_t<5, 2, false>},
-         {launch_gather_grad_t<6, 1, false>, launch_gather_grad_t<6, 2, false>},
-         {launch_gather_grad_t<8, 1, false>, launch_gather_grad_t<8, 2, false>}},
-        {{launch_gather_grad_t<3, 1, true>, launch_gather_grad_t<3, 2, true>},
-         {launch_gather_grad_t<4, 1, true>, launch_gather_grad_t<4, 2, true>},
-         {launch_gather_grad_t<5, 1, true>, launch_gather_grad_t<5, 2, true>},
-         {launch_gather_grad_t<6, 1, true>, launch_gather_grad_t<6, 2, true>},
-         {launch_gather_grad_t<8, 1, true>, launch_gather_grad_t<8, 2, true>}}};
+    static const L t[3][5][2] = {
+        {{launch_gather_grad_t<3, 1, kLarge>, launch_gather_grad_t<3, 2, kLarge>},
+         {launch_gather_grad_t<4, 1, kLarge>, launch_gather_grad_t<4, 2, kLarge>},
+         {launch_gather_grad_t<5, 1, kLarge>, launch_gather_grad_t<5, 2, kLarge>},
+         {launch_gather_grad_t<6, 1, kLarge>, launch_gather_grad_t<6, 2, kLarge>},
+         {launch_gather_grad_t<8, 1, kLarge>, launch_gather_grad_t<8, 2, kLarge>}},
+        {{launch_gather_grad_t<3, 1, kWide>, launch_gather_grad_t<3, 2, kWide>},
+         {launch_gather_grad_t<4, 1, kWide>, launch_gather_grad_t<4, 2, kWide>},
+         {launch_gather_grad_t<5, 1, kWide>, launch_gather_grad_t<5, 2, kWide>},
+         {launch_gather_grad_t<6, 1, kWide>, launch_gather_grad_t<6, 2, kWide>},
+         {launch_gather_grad_t<8, 1, kWide>, launch_gather_grad_t<8, 2, kWide>}},
+        {{launch_gather_grad_t<3, 1, kFew>, launch_gather_grad_t<3, 2, kFew>},
+         {launch_gather_grad_t<4, 1, kFew>, launch_gather_grad_t<4, 2, kFew>},
+         {launch_gather_grad_t<5, 1, kFew>, launch_gather_grad_t<5, 2, kFew>},
+         {launch_gather_grad_t<6, 1, kFew>, launch_gather_grad_t<6, 2, kFew>},
+         {launch_gather_grad_t<8, 1, kFew>, launch_gather_grad_t<8, 2, kFew>}}};
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     const int DC = (d + 15) / 16;
     const bool wide = fused_wide(g.nr);
     const int stage = gather_stage_floats(g.nr, wide);
-    t[wide][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
+    t[wide ? kWide : few ? kFew : kLarge][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
                                       Yt, M, At, Ab, DC, P, g, pscale, grid_d, dmax, split, stage, win,
                                       gpart, ldg);
     hipError_t e = hipGetLastError();
@@ -2079,8 +2100,8 @@ bool fused_supported(int d, int nr) {
 
 bool fused_wide(int nr) { return kFuseDirs * nr > kFuseMaxCells; }
 
-int64_t fused_gather_tile(int nr, int W) {
-    return (int64_t)kGatherWaves * 16 * gather_nb(fused_wide(nr), W);
+int64_t fused_gather_tile(int nr, int W, bool few) {
+    return (int64_t)kGatherWaves * 16 * gather_nb(fused_wide(nr) ? kWide : few ? kFew : kLarge, W);
 }
 
 int64_t split_tiles_bytes(int64_t rows, int d) {
@@ -2143,28 +2164,38 @@ void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, 
          (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
          (const void*)&spread_fused_kernel<8, 2, kFuseAccWide>}};
     using K = const void*;
-    const K gks[2][5][2] = {
-        {{(K)&gather_fused_kernel<3, 1, false>, (K)&gather_fused_kernel<3, 2, false>},
-         {(K)&gather_fused_kernel<4, 1, false>, (K)&gather_fused_kernel<4, 2, false>},
-         {(K)&gather_fused_kernel<5, 1, false>, (K)&gather_fused_kernel<5, 2, false>},
-         {(K)&gather_fused_kernel<6, 1, false>, (K)&gather_fused_kernel<6, 2, false>},
-         {(K)&gather_fused_kernel<8, 1, false>, (K)&gather_fused_kernel<8, 2, false>}},
-        {{(K)&gather_fused_kernel<3, 1, true>, (K)&gather_fused_kernel<3, 2, true>},
-         {(K)&gather_fused_kernel<4, 1, true>, (K)&gather_fused_kernel<4, 2, true>},
-         {(K)&gather_fused_kernel<5, 1, true>, (K)&gather_fused_kernel<5, 2, true>},
-         {(K)&gather_fused_kernel<6, 1, true>, (K)&gather_fused_kernel<6, 2, true>},
-         {(K)&gather_fused_kernel<8, 1, true>, (K)&gather_fused_kernel<8, 2, true>}}};
-    const K dks[2][5][2] = {
-        {{(K)&gather_grad_fused_kernel<3, 1, false>, (K)&gather_grad_fused_kernel<3, 2, false>},
-         {(K)&gather_grad_fused_kernel<4, 1, false>, (K)&gather_grad_fused_kernel<4, 2, false>},
-         {(K)&gather_grad_fused_kernel<5, 1, false>, (K)&gather_grad_fused_kernel<5, 2, false>},
-         {(K)&gather_grad_fused_kernel<6, 1, false>, (K)&gather_grad_fused_kernel<6, 2, false>},
-         {(K)&gather_grad_fused_kernel<8, 1, false>, (K)&gather_grad_fused_kernel<8, 2, false>}},
-        {{(K)&gather_grad_fused_kernel<3, 1, true>, (K)&gather_grad_fused_kernel<3, 2, true>},
-         {(K)&gather_grad_fused_kernel<4, 1, true>, (K)&gather_grad_fused_kernel<4, 2, true>},
-         {(K)&gather_grad_fused_kernel<5, 1, true>, (K)&gather_grad_fused_kernel<5, 2, true>},
-         {(K)&gather_grad_fused_kernel<6, 1, true>, (K)&gather_grad_fused_kernel<6, 2, true>},
-         {(K)&gather_grad_fused_kernel<8, 1, true>, (K)&gather_grad_fused_kernel<8, 2, true>}}};
+    const K gks[3][5][2] = {
+        {{(K)&gather_fused_kernel<3, 1, kLarge>, (K)&gather_fused_kernel<3, 2, kLarge>},
+         {(K)&gather_fused_kernel<4, 1, kLarge>, (K)&gather_fused_kernel<4, 2, kLarge>},
+         {(K)&gather_fused_kernel<5, 1, kLarge>, (K)&gather_fused_kernel<5, 2, kLarge>},
+         {(K)&gather_fused_kernel<6, 1, kLarge>, (K)&gather_fused_kernel<6, 2, kLarge>},
+         {(K)&gather_fused_kernel<8, 1, kLarge>, (K)&gather_fused_kernel<8, 2, kLarge>}},
+        {{(K)&gather_fused_kernel<3, 1, kWide>, (K)&gather_fused_kernel<3, 2, kWide>},
+         {(K)&gather_fused_kernel<4, 1, kWide>, (K)&gather_fused_kernel<4, 2, kWide>},
+         {(K)&gather_fused_kernel<5, 1, kWide>, (K)&gather_fused_kernel<5, 2, kWide>},
+         {(K)&gather_fused_kernel<6, 1, kWide>, (K)&gather_fused_kernel<6, 2, kWide>},
+         {(K)&gather_fused_kernel<8, 1, kWide>, (K)&gather_fused_kernel<8, 2, kWide>}},
+        {{(K)&gather_fused_kernel<3, 1, kFew>, (K)&gather_fused_kernel<3, 2, kFew>},
+         {(K)&gather_fused_kernel<4, 1, kFew>, (K)&gather_fused_kernel<4, 2, kFew>},
+         {(K)&gather_fused_kernel<5, 1, kFew>, (K)&gather_fused_kernel<5, 2, kFew>},
+         {(K)&gather_fused_kernel<6, 1, kFew>, (K)&gather_fused_kernel<6, 2, kFew>},
+         {(K)&gather_fused_kernel<8, 1, kFew>, (K)&gather_fused_kernel<8, 2, kFew>}}};
+    const K dks[3][5][2] = {
+        {{(K)&gather_grad_fused_kernel<3, 1, kLarge>, (K)&gather_grad_fused_kernel<3, 2, kLarge>},
+         {(K)&gather_grad_fused_kernel<4, 1, kLarge>, (K)&gather_grad_fused_kernel<4, 2, kLarge>},
+         {(K)&gather_grad_fused_kernel<5, 1, kLarge>, (K)&gather_grad_fused_kernel<5, 2, kLarge>},
+         {(K)&gather_grad_fused_kernel<6, 1, kLarge>, (K)&gather_grad_fused_kernel<6, 2, kLarge>},
+         {(K)&gather_grad_fused_kernel<8, 1, kLarge>, (K)&gather_grad_fused_kernel<8, 2, kLarge>}},
+        {{(K)&gather_grad_fused_kernel<3, 1, kWide>, (K)&gather_grad_fused_kernel<3, 2, kWide>},
+         {(K)&gather_grad_fused_kernel<4, 1, kWide>, (K)&gather_grad_fused_kernel<4, 2, kWide>},
+         {(K)&gather_grad_fused_kernel<5, 1, kWide>, (K)&gather_grad_fused_kernel<5, 2, kWide>},
+         {(K)&gather_grad_fused_kernel<6, 1, kWide>, (K)&gather_grad_fused_kernel<6, 2, kWide>},
+         {(K)&gather_grad_fused_kernel<8, 1, kWide>, (K)&gather_grad_fused_kernel<8, 2, kWide>}},
+        {{(K)&gather_grad_fused_kernel<3, 1, kFew>, (K)&gather_grad_fused_kernel<3, 2, kFew>},
+         {(K)&gather_grad_fused_kernel<4, 1, kFew>, (K)&gather_grad_fused_kernel<4, 2, kFew>},
+         {(K)&gather_grad_fused_kernel<5, 1, kFew>, (K)&gather_grad_fused_kernel<5, 2, kFew>},
+         {(K)&gather_grad_fused_kernel<6, 1, kFew>, (K)&gather_grad_fused_kernel<6, 2, kFew>},
+         {(K)&gather_grad_fused_kernel<8, 1, kFew>, (K)&gather_grad_fused_kernel<8, 2, kFew>}}};
     const int si = width_index(Ws), gi = width_index(Wg), di = width_index(Wd);
     if (si < 0 || gi < 0 || di < 0) return;
     const int kb = split_kblocks(d);
@@ -2226,28 +2257,34 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
                                const GatherSplit& split,
                                const WindowArgs& win, double* spart, int64_t ldm,
                                hipStream_t stream) {
-    if (!fused_supported(d, g.nr) || (int64_t)split.tile != fused_gather_tile(g.nr, W))
+    const bool few = !fused_wide(g.nr) && (int64_t)split.tile == fused_gather_tile(g.nr, W, true);
+    if (!fused_supported(d, g.nr) || (int64_t)split.tile != fused_gather_tile(g.nr, W, few))
         return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*, int,
                        const GridGeom&, float, const float*, const GatherSplit&, int, const WindowArgs&, double*,
                        int64_t);
-    static const L t[2][5][2] = {
-        {{launch_gather_fused_t<3, 1, false>, launch_gather_fused_t<3, 2, false>},
-         {launch_gather_fused_t<4, 1, false>, launch_gather_fused_t<4, 2, false>},
-         {launch_gather_fused_t<5, 1, false>, launch_gather_fused_t<5, 2, false>},
-         {launch_gather_fused_t<6, 1, false>, launch_gather_fused_t<6, 2, false>},
-         {launch_gather_fused_t<8, 1, false>, launch_gather_fused_t<8, 2, false>}},
-        {{launch_gather_fused_t<3, 1, true>, launch_gather_fused_t<3, 2, true>},
-         {launch_gather_fused_t<4, 1, true>, launch_gather_fused_t<4, 2, true>},
-         {launch_gather_fused_t<5, 1, true>, launch_gather_fused_t<5, 2, true>},
-         {launch_gather_fused_t<6, 1, true>, launch_gather_fused_t<6, 2, true>},
-         {launch_gather_fused_t<8, 1, true>, launch_gather_fused_t<8, 2, true>}}};
+    static const L t[3][5][2] = {
+        {{launch_gather_fused_t<3, 1, kLarge>, launch_gather_fused_t<3, 2, kLarge>},
+         {launch_gather_fused_t<4, 1, kLarge>, launch_gather_fused_t<4, 2, kLarge>},
+         {launch_gather_fused_t<5, 1, kLarge>, launch_gather_fused_t<5, 2, kLarge>},
+         {launch_gather_fused_t<6, 1, kLarge>, launch_gather_fused_t<6, 2, kLarge>},
+         {launch_gather_fused_t<8, 1, kLarge>, launch_gather_fused_t<8, 2, kLarge>}},
+        {{launch_gather_fused_t<3, 1, kWide>, launch_gather_fused_t<3, 2, kWide>},
+         {launch_gather_fused_t<4, 1, kWide>, launch_gather_fused_t<4, 2, kWide>},
+         {launch_gather_fused_t<5, 1, kWide>, launch_gather_fused_t<5, 2, kWide>},
+         {launch_gather_fused_t<6, 1, kWide>, launch_gather_fused_t<6, 2, kWide>},
+         {launch_gather_fused_t<8, 1, kWide>, launch_gather_fused_t<8, 2, kWide>}},
+        {{launch_gather_fused_t<3, 1, kFew>, launch_gather_fused_t<3, 2, kFew>},
+         {launch_gather_fused_t<4, 1, kFew>, launch_gather_fused_t<4, 2, kFew>},
+         {launch_gather_fused_t<5, 1, kFew>, launch_gather_fused_t<5, 2, kFew>},
+         {launch_gather_fused_t<6, 1, kFew>, launch_gather_fused_t<6, 2, kFew>},
+         {launch_gather_fused_t<8, 1, kFew>, launch_gather_fused_t<8, 2, kFew>}}};
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     // one staging buffer: the group's grids rounded up to whole 1 KB pieces
     const bool wide = fused_wide(g.nr);
     const int stage = gather_stage_floats(g.nr, wide);
-    t[wide][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
+    t[wide ? kWide : few ? kFew : kLarge][wi][split_kblocks(d) - 1](split_grid(split), (size_t)2 * stage * sizeof(float), stream,
                                       Yt, M, At, P, g, pscale, grid, split, stage, win, spart,
                                       ldm);
     return hipGetLastError();
@@ -2418,10 +2455,10 @@ __global__ __launch_bounds__(64 * kGatherWaves) void batch_gather_fused_kernel(
         // no wave may still read the staging buffers of the previous task
         __syncthreads();
         if (pr.kb == 1)
-            gather_fused_body<W, 1, false>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
+            gather_fused_body<W, 1, kLarge>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
                                            pr.spart, pr.ldm, tk.a, p0, p1, tk.b);
         else
-            gather_fused_body<W, 2, false>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
+            gather_fused_body<W, 2, kLarge>(bgls, yt, pr.M, pr.at, pr.g, pr.pscale, pr.grid, stage, win,
                                            pr.spart, pr.ldm, tk.a, p0, p1, tk.b);
     }
 }

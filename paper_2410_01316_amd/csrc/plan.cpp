@@ -343,7 +343,7 @@ int fused_dir_range(int64_t M, int P, int64_t slots, int nr, int W) {
     // ranges of whole 16-direction groups; at least three rounds of
     // workgroups when P allows, then the fullest rounds (fewest ranges
     // among near ties: each range re-reads the targets)
-    const int64_t tiles = (M + fused_gather_tile(nr, W) - 1) / fused_gather_tile(nr, W);
+    const int64_t tiles = (M + fused_gather_tile(nr, W, false) - 1) / fused_gather_tile(nr, W, false);
     const int64_t groups = (P + kFuseDirs - 1) / kFuseDirs;
     int64_t best_pr = groups * kFuseDirs;
     double best_eff = -1.0;
@@ -652,13 +652,16 @@ int64_t prefix_rows(const float* x, int64_t N, const float* y, int64_t M) {
 }
 
 // The split of a fused gather over `slots` resident workgroups: one run each,
-// all within a unit of the same length, at most max_rows rows per tile.
+// all within a unit of the same length, at most max_rows rows per tile; tiles
+// of few_tile targets if those of `tile` give fewer units than workgroups.
 // dir_range (fastsum_set_launch): that many directions of one tile per run
 // (beyond P: all).
 // Rounds of (tile, direction range) workgroups left slots idle in the last
 // round and loaded a tile's targets once per range.
-GatherSplit gather_split(int64_t M, int P, int64_t tile, int64_t slots, int max_rows, int dir_range) {
+GatherSplit gather_split(int64_t M, int P, int64_t tile, int64_t few_tile, int64_t slots,
+                         int max_rows, int dir_range) {
     GatherSplit sp;
+    if ((M + tile - 1) / tile * ((P + kFuseDirs - 1) / kFuseDirs) < slots) tile = few_tile;
     const int64_t tiles = (M + tile - 1) / tile;
     sp.tile = (unsigned)tile;
     sp.step = kFuseDirs;
@@ -707,8 +710,9 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, cons
                               grid_d ? pl->mult_d : nullptr, grid, grid_d, grid_d ? dmax : nullptr,
                               st));
     }
-    const GatherSplit split = gather_split(M, P, fused_gather_tile(pl->geom.nr, pl->Wg),
-                                           pl->gather_slots, pl->ngroup_cap, pl->tune_dir_range);
+    const GatherSplit split = gather_split(M, P, fused_gather_tile(pl->geom.nr, pl->Wg, false),
+                                           fused_gather_tile(pl->geom.nr, pl->Wg, true), pl->gather_slots,
+                                           pl->ngroup_cap, pl->tune_dir_range);
     pl->last_nchunk = nchunk;
     bool even = false;
     pl->last_ngroup = split_max_rows(split, &even);
@@ -750,7 +754,8 @@ int64_t grad_rows(int64_t cap) {
 }
 
 GatherSplit grad_split(const fastsum_plan_s* pl, int64_t M) {
-    return gather_split(M, pl->P, fused_grad_tile(pl->geom.nr, pl->Wd, pl->d), pl->grad_slots,
+    return gather_split(M, pl->P, fused_grad_tile(pl->geom.nr, pl->Wd, pl->d, false),
+                        fused_grad_tile(pl->geom.nr, pl->Wd, pl->d, true), pl->grad_slots,
                         (int)std::min<int64_t>(kGradMaxRows, pl->gpart_rows / M), 0);
 }
 
