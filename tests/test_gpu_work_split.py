@@ -84,3 +84,26 @@ def test_copied_cells_of_narrow_grids(T, d):
     cfg = _cfg("energy", d, 9001, 70, 21, 128, d, 1.0)
     cfg["w"] *= np.random.default_rng(3).choice([-1.0, 1.0], 9001)
     assert _fused_against_stored(cfg, T) < 1e-6
+
+
+@pytest.mark.parametrize("kernel,n_ft,d,M,P,W", [
+    ("gauss", 128, 20, 2051, 4100, 4), ("gauss", 128, 40, 1027, 8200, 6),
+    ("gauss", 256, 33, 3000, 2050, 8), ("energy", 1024, 7, 1500, 4003, 4),
+    ("energy", 1024, 40, 1025, 2100, 6), ("laplace", 256, 40, 5000, 1501, 0)])
+def test_runs_that_cross_tiles(kernel, n_ft, d, M, P, W):
+    """More units of work than workgroups: runs that end inside a tile and
+    cross into the next, values and all gradients, fused against stored."""
+    cfg = _cfg(kernel, d, 301, M, P, n_ft, d, 1.5 * np.sqrt(d))
+    v = np.random.default_rng(M).random(M) + 0.1
+    res = []
+    for mat in (False, True):
+        plan = gpu_plan(cfg, grad=True, materialize=mat, window_w=W)
+        x, y, w, vd = to_dev(cfg["x"], cfg["y"], cfg["w"], v)
+        s = plan(x, w, y)
+        gx, gy, gw = plan.grad(vd, want_x=True)
+        plan.check()
+        res.append([t.cpu().numpy() for t in (s, gy, gw, gx)])
+    errs = [rel_l2(a, b) for a, b in zip(*res)]
+    print("s %.2e grad_y %.2e grad_w %.2e grad_x %.2e" % tuple(errs))
+    assert errs[0] < 1e-6 and errs[2] < 1e-6
+    assert errs[1] < 5e-5 and errs[3] < 5e-5
