@@ -168,7 +168,7 @@ void fused_tasks(int i, const BatchProblem& d, const fastsum_problem_io& q, int 
         }
     }
     for (int a = 0; a < (P + 1) / 2; a += fftconv_pairs(d.g.n)) ph[kBatchFftconv].push_back({i, a, 0, 0});
-    const int64_t tile = fused_gather_tile(0, 4, false);    // batched plans: narrow grids
+    const int64_t tile = fused_gather_tile(0, 4, 32 * d.kb, false);    // batched plans: narrow grids
     const int gtiles = (int)((q.M + tile - 1) / tile);
     for (int r = 0; r < d.ngroup; ++r)
         for (int t = 0; t < gtiles; ++t) {

@@ -218,7 +218,7 @@ bool fused_supported(int d, int nr);
 bool fused_wide(int nr);
 // targets per tile of the fused gather (grids of nr cells, window width W);
 // few: the small tiles of problems that leave workgroups without work
-int64_t fused_gather_tile(int nr, int W, bool few);
+int64_t fused_gather_tile(int nr, int W, int d, bool few);
 // resident workgroups per CU of the fused spread, gather and adjoint kernels
 // (Ws, Wg, Wd: their window widths)
 void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, int* gather_blocks,

@@ -1214,19 +1214,24 @@ constexpr int kFuseAccCopies = 8;
 constexpr int kFuseMaxCellsWide = kFuseAccWide * kSpreadBlock;
 // LDS of the widest spread: its cells and spare cells
 constexpr int kSpreadMaxLds = (kFuseMaxCellsWide + 2 * kMaxSpareCells * 16) * (int)sizeof(int);
-constexpr int kGatherWaves = 8;
 // Modes of the gathers.  kWide: wide grids (fused_wide).  kFew: problems with
 // less than a tile and group of the large mode per resident workgroup take
 // tiles of a quarter or half of the targets instead (M = 3001, P = 256: 48 of
 // 256 CUs had work, the gather took 7.1 us, 4.4 with small tiles).
 enum GatherMode { kLarge = 0, kWide = 1, kFew = 2 };
-// 16-target batches per wave: eight, two in small tiles, and on
-// wide grids four (registers; W = 8 takes three).  Eight batches there
-// fit at up to five taps, but 512-target tiles fill the rounds better: the
-// MMD energy gather (d = 20, M = 2e5, P = 512) took 198 us with eight, 180
-// with four
-constexpr int gather_nb(int mode, int W) {
-    return mode == kLarge ? 8 : mode == kFew ? 2 : W >= 8 ? 3 : 4;
+// The gathers are bound by VALU and LDS together, and two waves per SIMD do
+// not overlap them: 16 waves in 128 registers with few batches each beat 8
+// waves with many.  Gather of the sum, d = 50, N = M = 60000, P = 3500, three
+// taps: 164 us with eight waves of eight batches, 150 with sixteen of two;
+// wide, d = 20, M = 200000, P = 512, four taps: 161 with eight waves, 119 with
+// sixteen, of four batches each.  Wide grids with two k-blocks or more than
+// five taps do not fit in 128 registers.
+constexpr int gather_waves(int mode, int KB, int W) {
+    return mode == kFew || (mode == kWide && (KB == 2 || W > 5)) ? 8 : 16;
+}
+// 16-target batches per wave
+constexpr int gather_nb(int mode, int KB, int W) {
+    return mode == kLarge ? (KB == 1 ? 4 : 2) : mode == kFew ? 2 : W >= 8 ? 3 : 4;
 }
 // row of the dispatch tables of window width W (-1: none)
 constexpr int width_index(int W) { return W >= 3 && W <= 6 ? W - 3 : W == 8 ? 4 : -1; }
@@ -1677,7 +1682,7 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 }
 
 // Gather with projections computed in registers.  A workgroup owns the
-// TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(MODE, W)) and
+// TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(MODE, KB, W)) and
 // the directions p_begin .. p_end - 1
 // (p_begin a multiple of kFuseDirs), whose sums are row `row` of spart.  The grids of each group of 16
 // directions are staged in one of two LDS buffers while the previous group
@@ -1693,9 +1698,9 @@ __device__ __forceinline__ void gather_fused_body(
     const GridGeom& g, float pscale, const float* __restrict__ grid, int stage,
     const WindowArgs& win, double* __restrict__ spart, int64_t ldm, int tile, int p_begin, int p_end,
     int row) {
-    constexpr int WAVES = kGatherWaves;
+    constexpr int WAVES = gather_waves(MODE, KB, W);
     constexpr bool WIDE = MODE == kWide;
-    constexpr int NB = gather_nb(MODE, W);                     // batches per wave
+    constexpr int NB = gather_nb(MODE, KB, W);                     // batches per wave
     constexpr int TGT = WAVES * NB * 16;                           // targets per workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
@@ -1788,7 +1793,7 @@ __device__ __forceinline__ void for_run(const GatherSplit& sp, int P, Body body)
 }
 
 template <int W, int KB, int MODE>
-__global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
+__global__ __launch_bounds__(64 * gather_waves(MODE, KB, W)) void gather_fused_kernel(
     const uint16_t* __restrict__ Yt, int64_t M, const uint16_t* __restrict__ At, int P,
     GridGeom g, float pscale, const float* __restrict__ grid, GatherSplit split, int stage,
     WindowArgs win, double* __restrict__ spart, int64_t ldm) {
@@ -1817,7 +1822,9 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_fused_kernel(
 // summed by grad_reduce_kernel).
 // waves of a workgroup: sixteen on wide grids where three batches fit in 128
 // registers (LDS holds one workgroup, eight waves are two per SIMD): the
-// adjoint above with the sum over the ranges 252 us with eight, 239 with sixteen
+// adjoint above with the sum over the ranges 252 us with eight, 239 with
+// sixteen.  Narrow grids with two k-blocks keep eight: two batches of sixteen
+// waves spill 34 registers, 58 us against 41 at M = 20011, d = 50, P = 1000.
 constexpr int grad_waves(int mode, int KB, int W) {
     return mode == kWide && KB == 1 && W <= 5 ? 16 : 8;
 }
@@ -2019,7 +2026,7 @@ void launch_gather_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint
                                   2 * kFuseMaxCells * (int)sizeof(float));
         attr_set = true;
     }
-    hipLaunchKernelGGL((gather_fused_kernel<W, KB, MODE>), grid, dim3(64 * kGatherWaves), lds, stream, Yt,
+    hipLaunchKernelGGL((gather_fused_kernel<W, KB, MODE>), grid, dim3(64 * gather_waves(MODE, KB, W)), lds, stream, Yt,
                        M, At, P, g, pscale, gridv, split, stage, win, spart, ldm);
 }
 
@@ -2100,8 +2107,9 @@ bool fused_supported(int d, int nr) {
 
 bool fused_wide(int nr) { return kFuseDirs * nr > kFuseMaxCells; }
 
-int64_t fused_gather_tile(int nr, int W, bool few) {
-    return (int64_t)kGatherWaves * 16 * gather_nb(fused_wide(nr) ? kWide : few ? kFew : kLarge, W);
+int64_t fused_gather_tile(int nr, int W, int d, bool few) {
+    const int mode = fused_wide(nr) ? kWide : few ? kFew : kLarge;
+    return (int64_t)gather_waves(mode, split_kblocks(d), W) * 16 * gather_nb(mode, split_kblocks(d), W);
 }
 
 int64_t split_tiles_bytes(int64_t rows, int d) {
@@ -2213,7 +2221,7 @@ void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, 
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds) == hipSuccess && n > 0)
             *out = n;
     };
-    gather_blocks_of(gks[wide][gi][kb - 1], 64 * kGatherWaves, gather_blocks);
+    gather_blocks_of(gks[wide][gi][kb - 1], 64 * gather_waves(wide, kb, Wg), gather_blocks);
     gather_blocks_of(dks[wide][di][kb - 1], 64 * grad_waves(wide, kb, Wd), grad_blocks);
 }
 
@@ -2257,8 +2265,8 @@ hipError_t launch_gather_fused(int W, const uint16_t* Yt, int64_t M, int d, cons
                                const GatherSplit& split,
                                const WindowArgs& win, double* spart, int64_t ldm,
                                hipStream_t stream) {
-    const bool few = !fused_wide(g.nr) && (int64_t)split.tile == fused_gather_tile(g.nr, W, true);
-    if (!fused_supported(d, g.nr) || (int64_t)split.tile != fused_gather_tile(g.nr, W, few))
+    const bool few = !fused_wide(g.nr) && (int64_t)split.tile == fused_gather_tile(g.nr, W, d, true);
+    if (!fused_supported(d, g.nr) || (int64_t)split.tile != fused_gather_tile(g.nr, W, d, few))
         return hipErrorInvalidValue;
     using L = void (*)(dim3, size_t, hipStream_t, const uint16_t*, int64_t, const uint16_t*, int,
                        const GridGeom&, float, const float*, const GatherSplit&, int, const WindowArgs&, double*,
@@ -2441,7 +2449,7 @@ batch_spread_fused_kernel(
 }
 
 template <int W>
-__global__ __launch_bounds__(64 * kGatherWaves) void batch_gather_fused_kernel(
+__global__ __launch_bounds__(64 * gather_waves(kLarge, 2, W)) void batch_gather_fused_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
     int P) {
     extern __shared__ float bgls[];
@@ -2494,7 +2502,7 @@ void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const
         hipLaunchKernelGGL((batch_spread_fused_kernel<W>), grid, dim3(kSpreadBlock), lds, stream,
                            probs, tasks, ntasks, P);
     else
-        hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(64 * kGatherWaves), lds, stream,
+        hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(64 * gather_waves(kLarge, 2, W)), lds, stream,
                            probs, tasks, ntasks, P);
 }
 

@@ -339,26 +339,6 @@ int fused_chunks(int64_t N, int P, int64_t slots, int nr) {
     return (int)best;
 }
 
-int fused_dir_range(int64_t M, int P, int64_t slots, int nr, int W) {
-    // ranges of whole 16-direction groups; at least three rounds of
-    // workgroups when P allows, then the fullest rounds (fewest ranges
-    // among near ties: each range re-reads the targets)
-    const int64_t tiles = (M + fused_gather_tile(nr, W, false) - 1) / fused_gather_tile(nr, W, false);
-    const int64_t groups = (P + kFuseDirs - 1) / kFuseDirs;
-    int64_t best_pr = groups * kFuseDirs;
-    double best_eff = -1.0;
-    for (int64_t r = 1; r <= groups; ++r) {
-        const int64_t pr = round_up((P + r - 1) / r, kFuseDirs);
-        const int64_t ranges = (P + pr - 1) / pr;
-        if (ranges != r) continue;
-        const int64_t blocks = tiles * ranges;
-        if (blocks < 3 * slots && r < groups) continue;
-        const double eff = round_efficiency(blocks, slots);
-        if (eff > best_eff + 0.02) { best_eff = eff; best_pr = pr; }
-    }
-    return (int)best_pr;
-}
-
 int gather_group(int64_t M, int P, int pstage) {
     // aim for about 1024 workgroups; group size a multiple of pstage, <= 128
     const int64_t tiles = (M + kGatherTile - 1) / kGatherTile;
@@ -710,8 +690,8 @@ fastsum_status fused_sum(fastsum_plan_s* pl, const uint16_t* xt, int64_t N, cons
                               grid_d ? pl->mult_d : nullptr, grid, grid_d, grid_d ? dmax : nullptr,
                               st));
     }
-    const GatherSplit split = gather_split(M, P, fused_gather_tile(pl->geom.nr, pl->Wg, false),
-                                           fused_gather_tile(pl->geom.nr, pl->Wg, true), pl->gather_slots,
+    const GatherSplit split = gather_split(M, P, fused_gather_tile(pl->geom.nr, pl->Wg, pl->d, false),
+                                           fused_gather_tile(pl->geom.nr, pl->Wg, pl->d, true), pl->gather_slots,
                                            pl->ngroup_cap, pl->tune_dir_range);
     pl->last_nchunk = nchunk;
     bool even = false;
