@@ -1201,17 +1201,18 @@ hipError_t launch_backproject(const float* tprime, int64_t ld, int64_t M,
 // 1 KB wave access.
 // ---------------------------------------------------------------------------
 
-constexpr int kSpreadBlock = 512;                          // 8 waves
-constexpr int kSpreadWaves = kSpreadBlock / 64;
+// Kinds of the fused spread by the width of the grid.  kCopies: narrow grids
+// with four copies of each cell.  kWideCells (16 nr above 16384 cells, up to
+// 16 x 2048, e.g. the energy kernel at T = 0.45): LDS holds one workgroup, of
+// sixteen waves: with eight, two per SIMD, the spread at d = 20, N = 400000,
+// P = 512, four taps took 236 us, 212 with sixteen.  The gathers of such
+// grids stage half a group of grids at a time.
+enum SpreadKind { kCopies = 0, kCells = 1, kWideCells = 2 };
+constexpr int spread_threads(int kind) { return kind == kWideCells ? 1024 : 512; }
 constexpr int kFuseAcc = 32;                               // FP32 cell accumulators per thread
-constexpr int kFuseMaxCells = kFuseAcc * kSpreadBlock;     // kFuseDirs * nr <= this
-// wide grids (kFuseDirs * nr up to 16 x 2048, e.g. the energy kernel at
-// T = 0.45): twice the accumulators, one workgroup per CU, and the gathers
-// stage half a group of grids at a time
-constexpr int kFuseAccWide = 64;
-// grids with copies (at most kCopyMaxCells cells): fewer accumulators
-constexpr int kFuseAccCopies = 8;
-constexpr int kFuseMaxCellsWide = kFuseAccWide * kSpreadBlock;
+constexpr int spread_acc(int kind) { return kind == kCopies ? 8 : kFuseAcc; }
+constexpr int kFuseMaxCells = kFuseAcc * spread_threads(kCells);          // narrow: kFuseDirs * nr <= this
+constexpr int kFuseMaxCellsWide = kFuseAcc * spread_threads(kWideCells);
 // LDS of the widest spread: its cells and spare cells
 constexpr int kSpreadMaxLds = (kFuseMaxCellsWide + 2 * kMaxSpareCells * 16) * (int)sizeof(int);
 // Modes of the gathers.  kWide: wide grids (fused_wide).  kFew: problems with
@@ -1411,11 +1412,14 @@ __device__ __forceinline__ f32x4 split_mfma(const SplitOp<KB>& a, const SplitOp<
 // width would leave one workgroup per CU.
 constexpr int kCopyMaxCells = 160;                 // nr with copies: 48 KB, three workgroups per CU
 constexpr bool spread_copies(int nr) { return nr <= kCopyMaxCells; }
-// accumulators (16 nr / kSpreadBlock) are flushed in groups per thread without
+constexpr int spread_kind(int nr) {
+    return spread_copies(nr) ? kCopies : kFuseDirs * nr > kFuseMaxCells ? kWideCells : kCells;
+}
+// accumulators (16 nr / threads) are flushed in groups per thread without
 // bounds checks: whole groups of cells
-constexpr int flush_group(bool copies) { return copies ? 2 : 8; }
+constexpr int flush_group(int kind) { return kind == kCopies ? 2 : 8; }
 constexpr int spread_cells(int nr) {
-    const int unit = flush_group(spread_copies(nr)) * kSpreadBlock;
+    const int kind = spread_kind(nr), unit = flush_group(kind) * spread_threads(kind);
     return (kFuseDirs * nr + unit - 1) / unit * unit;
 }
 
@@ -1426,12 +1430,14 @@ constexpr int spread_cells(int nr) {
 // v = <xi_p, x_n / R>; x~ = pscale v with pscale = tau R.  The range check
 // of these points was done when they were split; w holds the weights in
 // their slices' fixed point (slice_max_tile).
-template <int W, int KB, int ACC, bool COPIES>
+template <int W, int KB, int KIND>
 __device__ __forceinline__ void spread_fused_body(
     int* cells, const uint16_t* __restrict__ Xt, int64_t N, const uint16_t* __restrict__ At,
     const float* __restrict__ w, int P, const GridGeom& g, float pscale, int64_t chunk_len,
     const float* __restrict__ slice_max, const WindowArgs& win, float* __restrict__ partial,
     int dgroup, int chunk) {
+    constexpr bool COPIES = KIND == kCopies;
+    constexpr int THREADS = spread_threads(KIND), WAVES = THREADS / 64, ACC = spread_acc(KIND);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, r = lane >> 4;
     const int p0 = dgroup * kFuseDirs;
@@ -1442,13 +1448,13 @@ __device__ __forceinline__ void spread_fused_body(
 #pragma unroll
     for (int q = 0; q < ACC; ++q) acc[q] = 0.f;
     // cell j of direction p0 + c: entry 16 j + c, copy r of it if COPIES
-    constexpr int LOGS = COPIES ? 6 : 4, kFlushGroup = flush_group(COPIES);
+    constexpr int LOGS = COPIES ? 6 : 4, kFlushGroup = flush_group(KIND);
     cells += kSpareCells<W> << LOGS;
     int4* cells4 = reinterpret_cast<int4*>(cells);
     if constexpr (COPIES) {
-        for (int j = tid; j < ncell; j += kSpreadBlock) cells4[j] = make_int4(0, 0, 0, 0);
+        for (int j = tid; j < ncell; j += THREADS) cells4[j] = make_int4(0, 0, 0, 0);
     } else {
-        for (int j = tid; j < ncell; j += kSpreadBlock) cells[j] = 0;
+        for (int j = tid; j < ncell; j += THREADS) cells[j] = 0;
     }
     __syncthreads();
     const WinEval<W> ev(g, win, pscale, kSpareCells<W>);
@@ -1459,7 +1465,7 @@ __device__ __forceinline__ void spread_fused_body(
     // the weights of the chunk only, so sources past it spread nothing
     const int64_t t0 = i0 / 16;
     const int64_t ntiles = (N + 15) / 16;
-    const int64_t trange = min(ntiles - t0, (int64_t)(len + 15) / 16 + 2 * kSpreadWaves);
+    const int64_t trange = min(ntiles - t0, (int64_t)(len + 15) / 16 + 2 * WAVES);
     const __amdgpu_buffer_rsrc_t xs =
         buffer_rsrc(Xt + t0 * KB * 2 * (kSplitTileBytes / 2), trange * KB * 2 * kSplitTileBytes);
     const __amdgpu_buffer_rsrc_t ws = buffer_rsrc(w + i0, (int64_t)len * 4);
@@ -1488,7 +1494,7 @@ __device__ __forceinline__ void spread_fused_body(
         // after its batch is done, so loads land in place (no copies that
         // would wait on them).  The last loads of a slice fetch the next
         // slice's first tiles, harmlessly (loaded again at its start).
-        constexpr int stride = kSpreadWaves * 16;
+        constexpr int stride = WAVES * 16;
         int n0 = s0 + wave * 16;
         SplitOp<KB> xa, xb;
         u32x4 wa, wb;
@@ -1515,14 +1521,14 @@ __device__ __forceinline__ void spread_fused_body(
         // its LDS read
 #pragma unroll
         for (int q0 = 0; q0 < ACC; q0 += kFlushGroup) {
-            if (q0 * kSpreadBlock >= ncell) break;
+            if (q0 * THREADS >= ncell) break;
             if constexpr (COPIES) {
                 int4 v[kFlushGroup];
 #pragma unroll
-                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells4[tid + (q0 + q) * kSpreadBlock];
+                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells4[tid + (q0 + q) * THREADS];
 #pragma unroll
                 for (int q = 0; q < kFlushGroup; ++q)
-                    cells4[tid + (q0 + q) * kSpreadBlock] = make_int4(0, 0, 0, 0);
+                    cells4[tid + (q0 + q) * THREADS] = make_int4(0, 0, 0, 0);
 #pragma unroll
                 for (int q = 0; q < kFlushGroup; ++q) {
                     acc[q0 + q] = fmaf((float)(v[q].x + v[q].y), unscale, acc[q0 + q]);
@@ -1531,9 +1537,9 @@ __device__ __forceinline__ void spread_fused_body(
             } else {
                 int v[kFlushGroup];
 #pragma unroll
-                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells[tid + (q0 + q) * kSpreadBlock];
+                for (int q = 0; q < kFlushGroup; ++q) v[q] = cells[tid + (q0 + q) * THREADS];
 #pragma unroll
-                for (int q = 0; q < kFlushGroup; ++q) cells[tid + (q0 + q) * kSpreadBlock] = 0;
+                for (int q = 0; q < kFlushGroup; ++q) cells[tid + (q0 + q) * THREADS] = 0;
 #pragma unroll
                 for (int q = 0; q < kFlushGroup; ++q)
                     acc[q0 + q] = fmaf((float)v[q], unscale, acc[q0 + q]);
@@ -1546,24 +1552,24 @@ __device__ __forceinline__ void spread_fused_body(
     float* sums = reinterpret_cast<float*>(cells);
 #pragma unroll
     for (int q = 0; q < ACC; ++q)
-        if (q * kSpreadBlock < ncell) sums[tid + q * kSpreadBlock] = acc[q];
+        if (q * THREADS < ncell) sums[tid + q * THREADS] = acc[q];
     __syncthreads();
     const int nvalid = min(kFuseDirs, P - p0);
-    for (int dir = wave; dir < nvalid; dir += kSpreadWaves) {
+    for (int dir = wave; dir < nvalid; dir += WAVES) {
         float* __restrict__ dst = partial + ((int64_t)chunk * P + p0 + dir) * g.nr;
         for (int j = lane; j < g.nr; j += 64) dst[j] = sums[j * kFuseDirs + dir];
     }
 }
 
 // workgroup (x, y): direction group x, source chunk y
-template <int W, int KB, int ACC>
-__global__ __launch_bounds__(kSpreadBlock) void spread_fused_kernel(
+template <int W, int KB, int KIND>
+__global__ __launch_bounds__(spread_threads(KIND)) void spread_fused_kernel(
     const uint16_t* __restrict__ Xt, int64_t N, const uint16_t* __restrict__ At,
     const float* __restrict__ w, int P, GridGeom g, float pscale, int64_t chunk_len,
     const float* __restrict__ slice_max, WindowArgs win, float* __restrict__ partial) {
     extern __shared__ int cells[];
-    spread_fused_body<W, KB, ACC, ACC == kFuseAccCopies>(cells, Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win,
-                             partial, blockIdx.x, blockIdx.y);
+    spread_fused_body<W, KB, KIND>(cells, Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win,
+                                   partial, blockIdx.x, blockIdx.y);
 }
 
 // Copies the grids of the 16 directions from p0 (contiguous; a plan's last
@@ -1998,19 +2004,19 @@ __global__ __launch_bounds__(kBlock) void grad_reduce_kernel(
     if (i + 3 < d) dst[3] = cv * s.w;
 }
 
-template <int W, int KB, int ACC>
+template <int W, int KB, int KIND>
 void launch_spread_fused_t(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* Xt,
                            int64_t N, const uint16_t* At, const float* w, int P,
                            const GridGeom& g, float pscale, int64_t chunk_len,
                            const float* slice_max, const WindowArgs& win, float* partial) {
     static bool attr_set = false;      // dynamic LDS above 64 KB must be enabled per kernel
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&spread_fused_kernel<W, KB, ACC>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&spread_fused_kernel<W, KB, KIND>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   kSpreadMaxLds);
         attr_set = true;
     }
-    hipLaunchKernelGGL((spread_fused_kernel<W, KB, ACC>), grid, dim3(kSpreadBlock), lds, stream,
+    hipLaunchKernelGGL((spread_fused_kernel<W, KB, KIND>), grid, dim3(spread_threads(KIND)), lds, stream,
                        Xt, N, At, w, P, g, pscale, chunk_len, slice_max, win, partial);
 }
 
@@ -2156,21 +2162,21 @@ void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, 
     // the spread's occupancy is set by LDS and registers; the larger operand
     // shape stands for both
     const void* sks[3][5] = {
-        {(const void*)&spread_fused_kernel<3, 2, kFuseAccCopies>,
-         (const void*)&spread_fused_kernel<4, 2, kFuseAccCopies>,
-         (const void*)&spread_fused_kernel<5, 2, kFuseAccCopies>,
-         (const void*)&spread_fused_kernel<6, 2, kFuseAccCopies>,
-         (const void*)&spread_fused_kernel<8, 2, kFuseAccCopies>},
-        {(const void*)&spread_fused_kernel<3, 2, kFuseAcc>,
-         (const void*)&spread_fused_kernel<4, 2, kFuseAcc>,
-         (const void*)&spread_fused_kernel<5, 2, kFuseAcc>,
-         (const void*)&spread_fused_kernel<6, 2, kFuseAcc>,
-         (const void*)&spread_fused_kernel<8, 2, kFuseAcc>},
-        {(const void*)&spread_fused_kernel<3, 2, kFuseAccWide>,
-         (const void*)&spread_fused_kernel<4, 2, kFuseAccWide>,
-         (const void*)&spread_fused_kernel<5, 2, kFuseAccWide>,
-         (const void*)&spread_fused_kernel<6, 2, kFuseAccWide>,
-         (const void*)&spread_fused_kernel<8, 2, kFuseAccWide>}};
+        {(const void*)&spread_fused_kernel<3, 2, kCopies>,
+         (const void*)&spread_fused_kernel<4, 2, kCopies>,
+         (const void*)&spread_fused_kernel<5, 2, kCopies>,
+         (const void*)&spread_fused_kernel<6, 2, kCopies>,
+         (const void*)&spread_fused_kernel<8, 2, kCopies>},
+        {(const void*)&spread_fused_kernel<3, 2, kCells>,
+         (const void*)&spread_fused_kernel<4, 2, kCells>,
+         (const void*)&spread_fused_kernel<5, 2, kCells>,
+         (const void*)&spread_fused_kernel<6, 2, kCells>,
+         (const void*)&spread_fused_kernel<8, 2, kCells>},
+        {(const void*)&spread_fused_kernel<3, 2, kWideCells>,
+         (const void*)&spread_fused_kernel<4, 2, kWideCells>,
+         (const void*)&spread_fused_kernel<5, 2, kWideCells>,
+         (const void*)&spread_fused_kernel<6, 2, kWideCells>,
+         (const void*)&spread_fused_kernel<8, 2, kWideCells>}};
     using K = const void*;
     const K gks[3][5][2] = {
         {{(K)&gather_fused_kernel<3, 1, kLarge>, (K)&gather_fused_kernel<3, 2, kLarge>},
@@ -2207,10 +2213,10 @@ void fused_occupancy(int Ws, int Wg, int Wd, int d, int nr, int* spread_blocks, 
     const int si = width_index(Ws), gi = width_index(Wg), di = width_index(Wd);
     if (si < 0 || gi < 0 || di < 0) return;
     const int kb = split_kblocks(d);
-    const void* sk = sks[spread_copies(nr) ? 0 : wide ? 2 : 1][si];
+    const void* sk = sks[spread_kind(nr)][si];
     (void)hipFuncSetAttribute(sk, hipFuncAttributeMaxDynamicSharedMemorySize, kSpreadMaxLds);
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, sk, kSpreadBlock,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, sk, spread_threads(spread_kind(nr)),
                                                      fused_spread_lds(nr)) == hipSuccess && b > 0)
         *spread_blocks = b;
     const size_t lds = (size_t)2 * gather_stage_floats(nr, wide) * sizeof(float);
@@ -2235,26 +2241,25 @@ hipError_t launch_spread_fused(int W, const uint16_t* Xt, int64_t N, int d, cons
                        const float*, int, const GridGeom&, float, int64_t, const float*,
                        const WindowArgs&, float*);
     static const L t[3][5][2] = {
-        {{launch_spread_fused_t<3, 1, kFuseAccCopies>, launch_spread_fused_t<3, 2, kFuseAccCopies>},
-         {launch_spread_fused_t<4, 1, kFuseAccCopies>, launch_spread_fused_t<4, 2, kFuseAccCopies>},
-         {launch_spread_fused_t<5, 1, kFuseAccCopies>, launch_spread_fused_t<5, 2, kFuseAccCopies>},
-         {launch_spread_fused_t<6, 1, kFuseAccCopies>, launch_spread_fused_t<6, 2, kFuseAccCopies>},
-         {launch_spread_fused_t<8, 1, kFuseAccCopies>, launch_spread_fused_t<8, 2, kFuseAccCopies>}},
-        {{launch_spread_fused_t<3, 1, kFuseAcc>, launch_spread_fused_t<3, 2, kFuseAcc>},
-         {launch_spread_fused_t<4, 1, kFuseAcc>, launch_spread_fused_t<4, 2, kFuseAcc>},
-         {launch_spread_fused_t<5, 1, kFuseAcc>, launch_spread_fused_t<5, 2, kFuseAcc>},
-         {launch_spread_fused_t<6, 1, kFuseAcc>, launch_spread_fused_t<6, 2, kFuseAcc>},
-         {launch_spread_fused_t<8, 1, kFuseAcc>, launch_spread_fused_t<8, 2, kFuseAcc>}},
-        {{launch_spread_fused_t<3, 1, kFuseAccWide>, launch_spread_fused_t<3, 2, kFuseAccWide>},
-         {launch_spread_fused_t<4, 1, kFuseAccWide>, launch_spread_fused_t<4, 2, kFuseAccWide>},
-         {launch_spread_fused_t<5, 1, kFuseAccWide>, launch_spread_fused_t<5, 2, kFuseAccWide>},
-         {launch_spread_fused_t<6, 1, kFuseAccWide>, launch_spread_fused_t<6, 2, kFuseAccWide>},
-         {launch_spread_fused_t<8, 1, kFuseAccWide>, launch_spread_fused_t<8, 2, kFuseAccWide>}}};
+        {{launch_spread_fused_t<3, 1, kCopies>, launch_spread_fused_t<3, 2, kCopies>},
+         {launch_spread_fused_t<4, 1, kCopies>, launch_spread_fused_t<4, 2, kCopies>},
+         {launch_spread_fused_t<5, 1, kCopies>, launch_spread_fused_t<5, 2, kCopies>},
+         {launch_spread_fused_t<6, 1, kCopies>, launch_spread_fused_t<6, 2, kCopies>},
+         {launch_spread_fused_t<8, 1, kCopies>, launch_spread_fused_t<8, 2, kCopies>}},
+        {{launch_spread_fused_t<3, 1, kCells>, launch_spread_fused_t<3, 2, kCells>},
+         {launch_spread_fused_t<4, 1, kCells>, launch_spread_fused_t<4, 2, kCells>},
+         {launch_spread_fused_t<5, 1, kCells>, launch_spread_fused_t<5, 2, kCells>},
+         {launch_spread_fused_t<6, 1, kCells>, launch_spread_fused_t<6, 2, kCells>},
+         {launch_spread_fused_t<8, 1, kCells>, launch_spread_fused_t<8, 2, kCells>}},
+        {{launch_spread_fused_t<3, 1, kWideCells>, launch_spread_fused_t<3, 2, kWideCells>},
+         {launch_spread_fused_t<4, 1, kWideCells>, launch_spread_fused_t<4, 2, kWideCells>},
+         {launch_spread_fused_t<5, 1, kWideCells>, launch_spread_fused_t<5, 2, kWideCells>},
+         {launch_spread_fused_t<6, 1, kWideCells>, launch_spread_fused_t<6, 2, kWideCells>},
+         {launch_spread_fused_t<8, 1, kWideCells>, launch_spread_fused_t<8, 2, kWideCells>}}};
     const int wi = width_index(W);
     if (wi < 0) return hipErrorInvalidValue;
     dim3 grid((unsigned)((P + kFuseDirs - 1) / kFuseDirs), (unsigned)nchunk);
-    const int kind = spread_copies(g.nr) ? 0 : fused_wide(g.nr) ? 2 : 1;
-    t[kind][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
+    t[spread_kind(g.nr)][wi][split_kblocks(d) - 1](grid, fused_spread_lds(g.nr), stream,
                                                   Xt, N, At, wscaled, P, g, pscale, chunk_len,
                                                   slice_max, win, partial);
     return hipGetLastError();
@@ -2421,7 +2426,7 @@ __global__ __launch_bounds__(kBlock) void batch_split_kernel(
 
 // two workgroups per CU (at most 128 VGPRs), as the single-problem kernel
 template <int W>
-__global__ __launch_bounds__(kSpreadBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+__global__ __launch_bounds__(spread_threads(kCells)) __attribute__((amdgpu_waves_per_eu(4))) void
 batch_spread_fused_kernel(
     const BatchProblem* __restrict__ probs, const BatchTask* __restrict__ tasks, int ntasks,
     int P) {
@@ -2431,18 +2436,18 @@ batch_spread_fused_kernel(
         const BatchProblem& pr = probs[tk.prob];
         const WindowArgs win = pr.swin;
         if (spread_copies(pr.g.nr) && pr.kb == 1)
-            spread_fused_body<W, 1, kFuseAccCopies, true>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
+            spread_fused_body<W, 1, kCopies>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
                                     pr.g, pr.pscale, pr.chunk_len, pr.slice_max, win, pr.partial,
                                     tk.a, tk.b);
         else if (spread_copies(pr.g.nr))
-            spread_fused_body<W, 2, kFuseAccCopies, true>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
+            spread_fused_body<W, 2, kCopies>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P,
                                     pr.g, pr.pscale, pr.chunk_len, pr.slice_max, win, pr.partial,
                                     tk.a, tk.b);
         else if (pr.kb == 1)
-            spread_fused_body<W, 1, kFuseAcc, false>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
+            spread_fused_body<W, 1, kCells>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         else
-            spread_fused_body<W, 2, kFuseAcc, false>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
+            spread_fused_body<W, 2, kCells>(bcells, pr.xt, pr.N, pr.at, pr.wscaled, P, pr.g, pr.pscale,
                                     pr.chunk_len, pr.slice_max, win, pr.partial, tk.a, tk.b);
         __syncthreads();
     }
@@ -2499,7 +2504,7 @@ void launch_batch_fused_t(int phase, dim3 grid, const BatchProblem* probs, const
         attr_set = true;
     }
     if (phase == kBatchSpread)
-        hipLaunchKernelGGL((batch_spread_fused_kernel<W>), grid, dim3(kSpreadBlock), lds, stream,
+        hipLaunchKernelGGL((batch_spread_fused_kernel<W>), grid, dim3(spread_threads(kCells)), lds, stream,
                            probs, tasks, ntasks, P);
     else
         hipLaunchKernelGGL((batch_gather_fused_kernel<W>), grid, dim3(64 * gather_waves(kLarge, 2, W)), lds, stream,
