@@ -44,11 +44,20 @@ PEAK = {"hbm_GBs": 8000.0, "fp32_mfma_TFs": 157.3, "f16_mfma_TFs": 2500.0,
 # Horner) + 2x2 (the two taps); spreading adds the W weight products, the
 # gather W interpolation FMAs
 WINDOW_FLOPS = {"spread": 2 + 1 + 2 * (4 + 2 + 4) + 4, "gather": 2 + 1 + 2 * (4 + 2 + 4) + 2 * 4}
+# the fitted windows: three taps of degree 3 (even and odd part 2 coefficients
+# each), five of degree 4, with a middle tap that has an even part only
+FITTED_FLOPS = {3: {"spread": 2 + 1 + (2 + 2 + 4) + 2 + 3, "gather": 2 + 1 + (2 + 2 + 4) + 2 + 2 * 3},
+                5: {"spread": 2 + 1 + 2 * (4 + 2 + 4) + 4 + 5,
+                    "gather": 2 + 1 + 2 * (4 + 2 + 4) + 4 + 2 * 5}}
 KERNEL_SRC = os.path.join(ROOT, "paper_2410_01316_amd", "csrc", "kernels.hip")
-# int32 LDS atomic adds per clock per CU that a random-address probe sustains
-# on MI355X (4 consecutive cells per lane, as in spreading)
-LDS_ATOMIC_CEILING = 5.8
+# int32 LDS atomic adds per clock per CU that a probe sustains on MI355X when
+# the lanes of a wave fall into different banks, as the spread's cells do
+LDS_ATOMIC_CEILING = 12.0
 PROFILES = os.path.join(ROOT, "profiles")
+
+
+def window_flops(phase, info):
+    return FITTED_FLOPS.get(info.get("window_w", 4), WINDOW_FLOPS)[phase]
 
 
 def log(msg):
@@ -103,14 +112,14 @@ def algorithmic(phase, info, N, M, d, P, proj):
     if phase == "spread":
         out = info["last_spread_chunks"] * P * nr * 4
         if fused:
-            return N * kb * 2048 / 16 + N * 4 + out, WINDOW_FLOPS["spread"] * N * P, "alu"
+            return N * kb * 2048 / 16 + N * 4 + out, window_flops("spread", info) * N * P, "alu"
         return P * N * 4 + N * 4 + out, 0.0, "hbm"
     if phase == "fftconv":
         return info["last_spread_chunks"] * P * nr * 4 + P * nr * 4, 0.0, "hbm"
     if phase == "gather":
         out = info["last_gather_groups"] * M * 8
         if fused:
-            return M * kb * 2048 / 16 + P * nr * 4 + out, WINDOW_FLOPS["gather"] * M * P, "alu"
+            return M * kb * 2048 / 16 + P * nr * 4 + out, window_flops("gather", info) * M * P, "alu"
         return P * M * 4 + P * nr * 4 + out, 0.0, "hbm"
     if phase == "reduce":
         return info["last_gather_groups"] * M * 8 + M * 4, 0.0, "hbm"
@@ -651,13 +660,13 @@ def main():
                                        "per FP32-equivalent product; f16 dense peak 2500")
         if dom == "spread":
             # the resource that binds spreading: W integer LDS atomics per
-            # (source, direction), against the rate a random-address probe
+            # (source, direction), against the rate a conflict-free probe
             # sustains on this chip
-            rate = 4.0 * N * P / avg_s / (256 * 2.4e9)
+            rate = float(info["window_w"]) * N * P / avg_s / (256 * 2.4e9)
             roof["lds_atomics"] = dict(achieved=rate, ceiling=LDS_ATOMIC_CEILING,
                                        unit="lane-ops/clk/CU", frac=rate / LDS_ATOMIC_CEILING,
-                                       note="4 ds_add_u32 per (source, direction); ceiling "
-                                            "measured with random addresses")
+                                       note="one LDS atomic per tap and (source, direction); "
+                                            "ceiling measured with addresses in distinct banks")
     phase_report = {}
     for p, (t, c) in phases.items():
         if c:

@@ -118,9 +118,12 @@ typedef enum {
  *   P            number of directions (1 <= P <= 65536)
  *   n_ft         number of Fourier modes N_ft, even, 16..1024; modes |k| <= N_ft/2
  *                are kept, with half weight at |k| = N_ft/2 (App. I Step 3)
- *   window_w     window width in grid cells: 4, 6 or 8; default 6 for Laplace,
- *                4 otherwise
- *   oversample   grid size n = oversample * n_ft, 2 (default) or 4; n <= 2048
+ *   window_w     window width in grid cells: 4, 6 or 8; 0: a window of 3, 5 or 4
+ *                cells fitted to the kernel's coefficients where that moves the
+ *                result by less than 5e-7 of them (never for the energy
+ *                kernel), else 6 for Laplace and 4 otherwise
+ *   oversample   grid size n = oversample * n_ft, 2 (default) or 4; n <= 2048; a
+ *                fitted window may come with a smaller grid
  *   kernel       fastsum_kernel
  *   proj         fastsum_precision
  *   flags        FASTSUM_FLAG_*
