@@ -1223,7 +1223,8 @@ enum GatherMode { kLarge = 0, kWide = 1, kFew = 2 };
 // The gathers are bound by VALU and LDS together, and two waves per SIMD do
 // not overlap them: 16 waves in 128 registers with few batches each beat 8
 // waves with many.  Gather of the sum, d = 50, N = M = 60000, P = 3500, three
-// taps: 164 us with eight waves of eight batches, 150 with sixteen of two;
+// taps: 168 us with eight waves of eight batches, 154 to 165 with sixteen of
+// two, 156 with sixteen of three;
 // wide, d = 20, M = 200000, P = 512, four taps: 161 with eight waves, 119 with
 // sixteen, of four batches each.  Wide grids with two k-blocks or more than
 // five taps do not fit in 128 registers.
@@ -1689,9 +1690,9 @@ __device__ __forceinline__ void gather_half(const float* lds, int base0, int bas
 
 // Gather with projections computed in registers.  A workgroup owns the
 // TGT = 16 NB targets per wave of tile `tile` (NB = gather_nb(MODE, KB, W)) and
-// the directions p_begin .. p_end - 1
-// (p_begin a multiple of kFuseDirs), whose sums are row `row` of spart.  The grids of each group of 16
-// directions are staged in one of two LDS buffers while the previous group
+// the directions p_begin .. p_end - 1 (p_begin a multiple of kFuseDirs), whose
+// sums are row `row` of spart.  The grids of each group of 16 directions are
+// staged in one of two LDS buffers while the previous group
 // is interpolated; lane (c, r) holds directions 4r .. 4r+3 of target c of each
 // batch.  Per target the four directions are summed in FP32, the groups in
 // FP64.  WIDE: two groups do not fit, so the buffers hold halves of a group
