@@ -647,10 +647,12 @@ GatherSplit gather_split(int64_t M, int P, int64_t tile, int64_t few_tile, int64
     sp.step = kFuseDirs;
     if (dir_range > 0) sp.step = (unsigned)std::min<int64_t>(dir_range, round_up(P, kFuseDirs));
     auto groups = [&] { return ((int64_t)P + sp.step - 1) / sp.step; };
-    while (dir_range <= 0 && tiles * groups() > INT32_MAX) sp.step *= 2;
+    while (tiles * groups() > INT32_MAX) sp.step *= 2;
     sp.groups = (unsigned)groups();
     sp.units = (unsigned)(tiles * sp.groups);
     sp.run = 1;
+    // one range per run, as long as the grid holds less than 2^32 threads
+    while (dir_range > 0 && sp.units / sp.run >= (1u << 21)) sp.run *= 2;
     if (dir_range > 0) return sp;
     int64_t run = (sp.units + slots - 1) / slots;
     // `groups` units meet at most ceil((groups - 1) / run) + 1 runs
